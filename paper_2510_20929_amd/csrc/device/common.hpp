@@ -55,6 +55,14 @@ struct BufFrame {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0)), v),
                                           r, voff, soff, 0);
   }
+  // two neighbouring complex values (any 4-byte alignment)
+  __device__ __forceinline__ float4 ld2(int voff, int soff) const {
+    return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+  }
+  __device__ __forceinline__ void st2(float4 x, int voff, int soff) const {
+    __builtin_amdgcn_raw_buffer_store_b128(
+        __builtin_bit_cast(decltype(__builtin_amdgcn_raw_buffer_load_b128(r, 0, 0, 0)), x), r, voff, soff, 0);
+  }
   __device__ __forceinline__ float ldf(int voff, int soff) const {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
   }
@@ -71,11 +79,18 @@ __device__ __forceinline__ int opaque(int x) {
   asm volatile("" : "+v"(x));
   return x;
 }
+__device__ __forceinline__ int opaque_scalar(int x) {  // the same for a value in a scalar register
+  asm volatile("" : "+s"(x));
+  return x;
+}
 template <typename T>
 __device__ __forceinline__ const T* opaque_ptr(const T* p) {
   asm volatile("" : "+s"(p));
   return p;
 }
+// Computes a value here: without it the arithmetic may be sunk past following branches to
+// its first use, which keeps all of its operands live instead.
+__device__ __forceinline__ void pin(float2& x) { asm volatile("" : "+v"(x.x), "+v"(x.y)); }
 __device__ __forceinline__ int opaque_tid() { return opaque(int(threadIdx.x)); }
 
 // ----------------------------------------------------------------------------- compile-time loops
@@ -171,6 +186,15 @@ __device__ __forceinline__ void scatter_add(float2* base, size_t copy_stride, bo
                                             float2 v) {
   if (l2) atomic_add_c_l2(base + size_t(xcc) * copy_stride + i, v);
   else atomic_add_c(base + i, v);
+}
+
+// Workgroups go to the 8 XCDs in turn, each with its own L2. The place of workgroup `wg` of
+// `nwg` in an order that takes one XCD's workgroups after another's: persistent kernels
+// hand out consecutive work items by it, so that neighbouring scan positions, whose windows
+// overlap, share an L2. (Only the order depends on the distribution, no result does.)
+__device__ __forceinline__ int xcd_rank(int wg, int nwg) {
+  const int s = wg & 7, q = nwg >> 3, rem = nwg & 7;
+  return s * q + min(s, rem) + (wg >> 3);
 }
 
 // ----------------------------------------------------------------------------- reductions

@@ -312,15 +312,8 @@ struct LineTile {
   // which in natural order would all hit one bank.
   __device__ __forceinline__ static int sw(int n1, int k2) { return N1 * k2 + (n1 ^ (k2 & (N1 - 1))); }
 
-  // twiddle W_N^{n1 k2}: natural table tw[n1 k2], or (TWT) the transposed table with
-  // entry (k2, n1) at k2 N1 + n1, whose reads by the N1 lanes of a line are contiguous
-  template <bool TWT>
-  __device__ __forceinline__ static float2 twid(const float2* __restrict__ tw, int n1, int k2) {
-    return TWT ? tw[k2 * N1 + n1] : tw[n1 * k2];
-  }
-
   // In-place transform of all NL lines. Caller syncs before (data in LDS) and after.
-  template <bool INV, bool TWT = false>
+  template <bool INV>
   __device__ __forceinline__ static void run(float2* lds, int LS, int ES, const float2* __restrict__ tw_) {
     const int t = opaque_tid();
     const float2* __restrict__ tw = tw_;
@@ -335,7 +328,7 @@ struct LineTile {
         for (int n2 = 0; n2 < N2; ++n2) u[n2] = base[(q + N1 * n2) * ES];
         Dft<N2, false>::run(u);
 #pragma unroll
-        for (int k2 = 1; k2 < N2; ++k2) u[k2] = cmul(u[k2], twid<TWT>(tw, q, k2));
+        for (int k2 = 1; k2 < N2; ++k2) u[k2] = cmul(u[k2], tw[q * k2]);
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) base[sw(q, k2) * ES] = u[k2];
       }
@@ -394,7 +387,7 @@ struct LineTile {
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) u[k2] = base[sw(q, k2) * ES];
 #pragma unroll
-        for (int k2 = 1; k2 < N2; ++k2) u[k2] = cmul_conjb(u[k2], twid<TWT>(tw, q, k2));
+        for (int k2 = 1; k2 < N2; ++k2) u[k2] = cmul_conjb(u[k2], tw[q * k2]);
         Dft<N2, true>::run(u);
 #pragma unroll
         for (int n2 = 0; n2 < N2; ++n2) base[(q + N1 * n2) * ES] = u[n2];
@@ -403,86 +396,73 @@ struct LineTile {
   }
 };
 
-// ----------------------------------------------------------------------------- wide line tiles
-// As LineTile, but each line of N = N1 N2 points is served by N1 = 2 N2 threads, so that
-// T threads cover T / N1 lines per round with only N2 elements each (for 512 points,
-// 1024 threads cover 32 lines, a block that fits the LDS). Stage 1 is unchanged: thread
-// n1 runs a register DFT of size N2 over x[n1 + N1 n2] and applies W_N^{n1 k2}. Stage 2
-// needs one DFT of size N1 per k2, shared by the adjacent threads (2 k2, 2 k2 + 1): by
-// decimation in frequency, the even outputs are the DFT of size N2 of Y[n] + Y[n + N2]
-// and the odd outputs the DFT of size N2 of (Y[n] - Y[n + N2]) W_N1^n, one half per
-// thread. The inverse runs the adjoint: each thread of the pair inverts its half (the odd
-// half then multiplied by conj W_N1^n), the pair swaps halves with a lane shuffle and forms
-// Y[n] = A[n] + B[n] or Y[n + N2] = A[n] - B[n]. Stage-1 outputs are stored at
-// N1 k2 + (n1 XOR k2) against LDS bank conflicts, as in LineTile.
-template <int N, int NL, int T>
-struct LineTileW {
-  static constexpr int N2 = N == 512 ? 16 : (N == 128 ? 8 : 4);
-  static constexpr int N1 = 2 * N2;
-  static_assert(N1 * N2 == N, "N must be 2 N2^2");
-  static_assert(T % N1 == 0 && NL == T / N1, "a block is one round of T / N1 lines");
-  static_assert(WAVE % N1 == 0, "the threads of a line must share a wavefront");
-  __device__ __forceinline__ static int sw(int n1, int k2) { return N1 * k2 + (n1 ^ k2); }
+// ----------------------------------------------------------------------------- wave lines
+// 1D transforms of four lines of N = 16 N2 points by one wavefront (256 and 512 points),
+// input and output in registers. Stage 1: thread (line, n1) holds x[n1 + 16 n2] in
+// u[n2], runs a register DFT of size N2 and multiplies by W_N^{n1 k2}; the wave exchanges
+// through its own 4 N cells of LDS (no block barrier: a wave's LDS operations execute in
+// order); stage 2: thread (line, kq) runs N2 / 16 DFTs of size 16 and holds frequency
+// kq + 16 kk in v[kk]. The inverse runs the adjoint stages in reverse order.
+// Cell of the intermediate (line, n1, k2): the XORs put the 32 lanes of a half-wave into
+// distinct 8-byte banks in both stages, for lanes that are 16 consecutive n1 (or k2) of two
+// lines, 8 of four lines (column order), or 4 + 4 of four lines (tile order).
+template <int N>
+struct WaveLines {
+  static constexpr int N1 = 16, N2 = N / 16;
+  static_assert(N2 == 16 || N2 == 32, "256- and 512-point lines");
+  __device__ __forceinline__ static int cell0(int line, int i) {  // XORed with (k2, n1 ^ k2) parts
+    return line * N + 16 * (line & 1) + (i ^ ((line >> 1) << 3));
+  }
+  __device__ __forceinline__ static void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
-  // In-place transform of all NL lines. Caller syncs before (data in LDS) and after.
-  // `tw` is the transposed twiddle table: W_N^{n1 k2} at k2 N1 + n1 (N entries); the
-  // stage-2 twiddle W_N1^n = W_N^{(N / N1) n} is its entry (k2 = n, n1 = N / N1).
-  template <bool INV, bool TWT = true>
-  __device__ __forceinline__ static void run(float2* lds, int LS, int ES, const float2* __restrict__ tw) {
-    static_assert(TWT, "the wide line transform reads the transposed twiddle table");
-    const int t = opaque_tid();
-    const int q = t % N1, lr = t / N1;
-    const int k2 = q >> 1, h = q & 1;
-    float2* base = lds + lr * LS;
-    if constexpr (!INV) {
-      float2 u[N2];
+  // `ex`: the wave's cells; `tw`: W_N^{n1 k2} at k2 16 + n1 (LDS)
+  __device__ __forceinline__ static void forward(float2* ex, const float2* tw, int line1, int n1, int line2, int kq,
+                                                 float2 (&u)[N2], float2 (&v)[N2]) {
+    Dft<N2, false>::run(u);
+    const int c1 = opaque(cell0(line1, n1));
+    wave_fence();
 #pragma unroll
-      for (int n2 = 0; n2 < N2; ++n2) u[n2] = base[(q + N1 * n2) * ES];
-      Dft<N2, false>::run(u);
-#pragma unroll
-      for (int j = 1; j < N2; ++j) u[j] = cmul(u[j], tw[j * N1 + q]);
-#pragma unroll
-      for (int j = 0; j < N2; ++j) base[sw(q, j) * ES] = u[j];
-      __syncthreads();
-      float2 v[N2];
-#pragma unroll
-      for (int n = 0; n < N2; ++n) {
-        const float2 a = base[sw(n, k2) * ES], b = base[sw(n + N2, k2) * ES];
-        v[n] = h == 0 ? cadd(a, b) : cmul(csub(a, b), tw[n * N1 + N / N1]);
-      }
-      Dft<N2, false>::run(v);
-      __syncthreads();
-#pragma unroll
-      for (int m = 0; m < N2; ++m) base[(k2 + N2 * (2 * m + h)) * ES] = v[m];
-    } else {
-      float2 v[N2];
-#pragma unroll
-      for (int m = 0; m < N2; ++m) v[m] = base[(k2 + N2 * (2 * m + h)) * ES];
-      Dft<N2, true>::run(v);
-      if (h) {
-#pragma unroll
-        for (int n = 0; n < N2; ++n) v[n] = cmul_conjb(v[n], tw[n * N1 + N / N1]);
-      }
-#pragma unroll
-      for (int n = 0; n < N2; ++n) {
-        float2 o;
-        o.x = __shfl_xor(v[n].x, 1);
-        o.y = __shfl_xor(v[n].y, 1);
-        v[n] = h == 0 ? cadd(v[n], o) : csub(o, v[n]);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int n = 0; n < N2; ++n) base[sw(n + N2 * h, k2) * ES] = v[n];
-      __syncthreads();
-      float2 u[N2];
-#pragma unroll
-      for (int j = 0; j < N2; ++j) u[j] = base[sw(q, j) * ES];
-#pragma unroll
-      for (int j = 1; j < N2; ++j) u[j] = cmul_conjb(u[j], tw[j * N1 + q]);
-      Dft<N2, true>::run(u);
-#pragma unroll
-      for (int n2 = 0; n2 < N2; ++n2) base[(q + N1 * n2) * ES] = u[n2];
+    for (int k2 = 0; k2 < N2; ++k2) {
+      if (k2 > 0) u[k2] = cmul(u[k2], tw[k2 * 16 + n1]);
+      ex[c1 ^ (16 * k2 + (k2 & 15))] = u[k2];
+      if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
+    wave_fence();
+#pragma unroll
+    for (int jj = 0; jj < N2 / 16; ++jj) {
+      const int c2 = opaque(cell0(line2, 0) ^ (16 * (kq + 16 * jj) + kq));
+      float2 w[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) w[i] = ex[c2 ^ i];
+      Dft<16, false>::run(w);
+#pragma unroll
+      for (int k1 = 0; k1 < 16; ++k1) v[jj + (N2 / 16) * k1] = w[k1];
+    }
+    wave_fence();
+  }
+  __device__ __forceinline__ static void inverse(float2* ex, const float2* tw, int line2, int kq, int line1, int n1,
+                                                 float2 (&v)[N2], float2 (&u)[N2]) {
+    wave_fence();
+#pragma unroll
+    for (int jj = 0; jj < N2 / 16; ++jj) {
+      const int c2 = opaque(cell0(line2, 0) ^ (16 * (kq + 16 * jj) + kq));
+      float2 w[16];
+#pragma unroll
+      for (int k1 = 0; k1 < 16; ++k1) w[k1] = v[jj + (N2 / 16) * k1];
+      Dft<16, true>::run(w);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) ex[c2 ^ i] = w[i];
+    }
+    const int c1 = opaque(cell0(line1, n1));
+    wave_fence();
+#pragma unroll
+    for (int k2 = 0; k2 < N2; ++k2) {
+      u[k2] = ex[c1 ^ (16 * k2 + (k2 & 15))];
+      if (k2 > 0) u[k2] = cmul_conjb(u[k2], tw[k2 * 16 + n1]);
+      if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    wave_fence();
+    Dft<N2, true>::run(u);
   }
 };
 

@@ -36,6 +36,25 @@ __device__ __forceinline__ PosInfo parse_position(const float* __restrict__ pos,
   return p;
 }
 
+// The same for a position that the whole wave shares, moved to scalar registers: a buffer
+// resource or branch that depends on values in vector registers costs a loop over the
+// lanes at every access.
+__device__ __forceinline__ PosInfo wave_position(const float* __restrict__ pos, int k, int N, int H, int W,
+                                                 bool want_pos) {
+  PosInfo p = parse_position(pos, k, N, H, W, want_pos);
+  const auto u = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+  const auto uf = [&](float v) { return __builtin_bit_cast(float, u(__builtin_bit_cast(int, v))); };
+  p.y0 = u(p.y0);
+  p.x0 = u(p.x0);
+  p.ey = u(p.ey);
+  p.ex = u(p.ex);
+  p.fy = uf(p.fy);
+  p.fx = uf(p.fx);
+  p.ok = u(p.ok) != 0;
+  p.finite = u(p.finite) != 0;
+  return p;
+}
+
 // Bilinear sample of a slice at window pixel (y, x). A tap whose weight is zero (an
 // integer coordinate) re-reads the base pixel instead of the next one, so the reads
 // stay inside the N x N window and the code has no per-pixel branches.

@@ -119,7 +119,6 @@ ptyhip_status plan_init(Plan* p, const ptyhip_desc& d, int maxK, const ptyhip_tu
   const size_t kk = size_t(std::max(maxK, 1));
   if ((st = dalloc(p, &p->loss_part, kk)) != PTYHIP_OK) return st;
   if ((st = dalloc(p, &p->pos_part, kk * 2 * G)) != PTYHIP_OK) return st;
-  if ((st = dalloc(p, &p->w_part, kk * E * G)) != PTYHIP_OK) return st;
   // per-position partials of dL/d(lambda z): the detector distance of the near field or
   // the slice spacing of a multislice model
   if ((d.propagation == PTYHIP_PROP_NEAR || S > 1) && (st = dalloc(p, &p->lz_part, kk)) != PTYHIP_OK) return st;
@@ -186,6 +185,13 @@ ptyhip_status plan_init(Plan* p, const ptyhip_desc& d, int maxK, const ptyhip_tu
     if ((st = dalloc(p, &p->eig_part, size_t(p->eig_splits) * E * M * NN)) != PTYHIP_OK) return st;
   }
   p->window_bytes = size_t(p->fchunk) * S * (N + 1) * (N + 1) * sizeof(float2) * G;
+  // weight-gradient partials: one per mode group, or the splits of the staged contraction
+  // (n positions take at most 1024 / ceil(n / 32) splits, so n splits <= 32 * 1024 for a
+  // call of one chunk)
+  size_t nw = kk * G;
+  if (stage && !p->on_chip)
+    nw = std::max(nw, std::max(kk * weight_contract_splits(std::min(int(kk), p->fchunk), M, N), size_t(32) * 1024));
+  if ((st = dalloc(p, &p->w_part, nw * E)) != PTYHIP_OK) return st;
 
   // per-step path buffers, chunked to a bounded footprint
   const size_t per_pos = NN * sizeof(float2) * (size_t(S) * 2 + size_t(M) * 2 + (S > 1 ? size_t(S) * M : 0)) +
@@ -313,6 +319,14 @@ static CallArgs chunk_args(const CallArgs& a, int k0, int n, int N, int E, int M
   return c;
 }
 
+// Staged probe-wave gradients of the four-step frames: the weight gradients are a contraction
+// of the staged frames, with this many partial sums per position (0: the fused kernel sums
+// them itself).
+static int staged_weight_splits(const Plan* p, int K, bool want_w) {
+  if (!want_w || p->on_chip || !p->gpstage || K == 0) return 0;
+  return weight_contract_splits(std::min(K, p->fchunk), p->d.n_modes, p->d.frame);
+}
+
 // Run one call in the chosen form, leaving per-position partials in the plan and the
 // object (and, for the fused form, probe) gradient in the caller's buffers.
 static ptyhip_status run_call(Plan* p, const CallArgs& a, bool plain, bool acc, float* g_obj, float* g_probe,
@@ -323,6 +337,7 @@ static ptyhip_status run_call(Plan* p, const CallArgs& a, bool plain, bool acc, 
   const bool adjoint = a.mode == MODE_FWD_ADJ || a.mode == MODE_APPLY_AH;
   const bool want_obj = adjoint && g_obj != nullptr;
   const bool want_probe = adjoint && g_probe != nullptr;
+  const int wsplits = fused && a.mode == MODE_FWD_ADJ ? staged_weight_splits(p, a.K, (a.want & WANT_WEIGHTS) != 0) : 0;
   if (!fused) {
     if (want_obj && !acc && launch_fill(g_obj, p->obj_elems * 2, 0.f, st) != hipSuccess) return PTYHIP_EHIP;
     if (want_probe &&
@@ -364,13 +379,16 @@ static ptyhip_status run_call(Plan* p, const CallArgs& a, bool plain, bool acc, 
       const int n = std::min(p->fchunk, a.K - k0);
       CallArgs c = chunk_args(a, k0, n, N, d.n_eig, d.n_modes);
       c.pos_part = a.pos_part ? a.pos_part + size_t(2) * G * k0 : nullptr;
-      c.w_part = a.w_part ? a.w_part + size_t(d.n_eig) * G * k0 : nullptr;
+      c.w_part = a.w_part && !wsplits ? a.w_part + size_t(d.n_eig) * G * k0 : nullptr;
       c.groups = G;
       c.group_modes = p->group_modes;
       c.ipart = p->ipart;
       c.cfr = a.mode == MODE_FWD_ADJ ? p->cfr : nullptr;
       c.kvalid = p->kvalid;
-      c.gpstage = (want_probe && a.mode == MODE_FWD_ADJ) ? p->gpstage : nullptr;
+      c.gpstage = ((want_probe || wsplits) && a.mode == MODE_FWD_ADJ) ? p->gpstage : nullptr;
+      // the four-step passes hand the far fields over in the frames that the adjoint pass
+      // then overwrites with the probe-wave gradients, mode by mode
+      c.far = (!p->on_chip && a.mode == MODE_FWD_ADJ) ? p->gpstage : nullptr;
       c.gwin = want_obj ? p->gwin : nullptr;
       c.wvalid = p->wvalid;
       timing_begin(p, st);
@@ -396,6 +414,9 @@ static ptyhip_status run_call(Plan* p, const CallArgs& a, bool plain, bool acc, 
         g.rep = G;
         if (launch_window_gather(g, st) != hipSuccess) return PTYHIP_EHIP;
       }
+      if (wsplits && launch_weight_contract(p->gpstage, a.probe, p->kvalid, n, d.n_eig, d.n_modes, N, wsplits,
+                                            a.w_part + size_t(d.n_eig) * wsplits * k0, st) != hipSuccess)
+        return PTYHIP_EHIP;
       if (want_probe &&
           launch_eig_stage_reduce(p->gpstage, c.weights, p->kvalid, n, d.n_eig, d.n_modes, N, p->eig_splits,
                                   p->eig_part, reinterpret_cast<float2*>(g_probe), add ? 1 : 0, st) != hipSuccess)
@@ -409,9 +430,10 @@ static ptyhip_status run_call(Plan* p, const CallArgs& a, bool plain, bool acc, 
   for (int k0 = 0; k0 < a.K; k0 += p->fchunk) {
     const int n = std::min(p->fchunk, a.K - k0);
     CallArgs c = chunk_args(a, k0, n, N, d.n_eig, d.n_modes);
-    const bool staged = want_probe && p->gpstage != nullptr && a.mode == MODE_FWD_ADJ &&
+    const bool staged = (want_probe || wsplits) && p->gpstage != nullptr && a.mode == MODE_FWD_ADJ &&
                         (a.weights != nullptr || p->tune.probe_stage == 1);
     c.gpstage = staged ? p->gpstage : nullptr;
+    if (wsplits) c.w_part = nullptr;
     timing_begin(p, st);
     hipError_t e = p->on_chip ? launch_fused_small(c, N, p->tune.variant, grid, st)
                               : launch_fused_big(c, N, p->tune.variant, grid, st);
@@ -431,7 +453,10 @@ static ptyhip_status run_call(Plan* p, const CallArgs& a, bool plain, bool acc, 
       g.accumulate = (acc || k0 > 0) ? 1 : 0;
       if (launch_window_gather(g, st) != hipSuccess) return PTYHIP_EHIP;
     }
-    if (c.gpstage &&
+    if (wsplits && launch_weight_contract(p->gpstage, a.probe, p->wvalid, n, d.n_eig, d.n_modes, N, wsplits,
+                                          a.w_part + size_t(d.n_eig) * wsplits * k0, st) != hipSuccess)
+      return PTYHIP_EHIP;
+    if (c.gpstage && want_probe &&
         launch_eig_stage_reduce(p->gpstage, c.weights, p->wvalid, n, d.n_eig, d.n_modes, N, p->eig_splits,
                                 p->eig_part, reinterpret_cast<float2*>(g_probe), (acc || k0 > 0) ? 1 : 0,
                                 st) != hipSuccess)
@@ -565,6 +590,8 @@ static ptyhip_status enqueue_forward_adjoint(Plan* p, hipStream_t st, int K, uin
   f.E = d.n_eig;
   f.accumulate = acc ? 1 : 0;
   f.rep = (fused && p->groups > 1) ? p->groups : 1;
+  const int wsplits = fused ? staged_weight_splits(p, K, want_w) : 0;
+  f.wrep = wsplits ? wsplits : f.rep;
   return launch_finalize(f, st) == hipSuccess ? PTYHIP_OK : PTYHIP_EHIP;
 }
 

@@ -7,8 +7,8 @@
 // transform cost); every workgroup reads its
 // dataset's call arguments from a device descriptor table (sorted by class, then by
 // first workgroup) and runs the same per-position body as the per-plan kernels (512
-// threads for 64^2; 1024 for 128^2, with the patch in registers, and for the four-step
-// frames 256^2 and 512^2). Gathers, probe reductions and final reductions follow, one
+// threads for 64^2; 1024 for 128^2, with the patch in registers; 1024 and 512 for the
+// four-step frames 256^2 and 512^2). Gathers, probe reductions and final reductions follow, one
 // launch each for all datasets of the class; they too read their pointers from the
 // table, so a captured graph stays valid when the caller rebinds buffers.
 #include <algorithm>
@@ -50,12 +50,13 @@ __global__ __launch_bounds__(BT128) void batched_128_kernel(const BatchEntry* __
 }
 
 template <int N, int T, int LOSS>
-__global__ __launch_bounds__(T) void batched_big_kernel(const BatchEntry* __restrict__ tab, int n) {
+__global__ __launch_bounds__(T, N == 256 ? 4 : 2) void batched_big_kernel(const BatchEntry* __restrict__ tab, int n) {
   __shared__ BigShared<N, T> sh;
   const int d = batch_dataset(tab, n);
   const CallArgs a = tab[d].a;
   const int wg = int(blockIdx.x) - tab[d].first_wg, nwg = tab[d].n_wg;
-  big_body<N, T, LOSS>(a, sh, wg, nwg);
+  if (a.mode == MODE_FWD_ADJ) big_body<N, T, LOSS, 0, true>(a, sh, wg, nwg);
+  else big_body<N, T, LOSS, 0, false>(a, sh, wg, nwg);
 }
 
 int batch_class(int N, int loss) { return 2 * (N <= 64 ? 0 : (N == 128 ? 1 : (N == 256 ? 2 : 3))) + (loss ? 1 : 0); }
@@ -102,7 +103,16 @@ __global__ void batch_probe_reduce_kernel(const BatchEntry* __restrict__ tab) {
     const size_t em = g / NN, r = g % NN;
     const float2* src = a.scratch + a.pacc_off + em * NN + r;
     float2 s = make_float2(0.f, 0.f);
-    for (int w = 0; w < groups; ++w) s = cadd(s, src[size_t(w) * a.scratch_stride]);
+    // eight workgroups' loads in flight, added in order
+    int w = 0;
+    for (; w + 8 <= groups; w += 8) {
+      float2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = src[size_t(w + u) * a.scratch_stride];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s = cadd(s, v[u]);
+    }
+    for (; w < groups; ++w) s = cadd(s, src[size_t(w) * a.scratch_stride]);
     size_t pix = r;
     if constexpr (N <= 128) pix = size_t(SmallCtx<N, T>::a_pix(int(r % T), int(r / T)));
     out[em * NN + pix] = s;
@@ -141,8 +151,8 @@ hipError_t launch_batched_class(const BatchEntry* dev_tab, const BatchEntry* hos
     case 3: hipLaunchKernelGGL(batched_128_kernel<1>, grid, dim3(BT128), 0, st, t, nc); break;
     case 4: hipLaunchKernelGGL((batched_big_kernel<256, 1024, 0>), grid, dim3(1024), 0, st, t, nc); break;
     case 5: hipLaunchKernelGGL((batched_big_kernel<256, 1024, 1>), grid, dim3(1024), 0, st, t, nc); break;
-    case 6: hipLaunchKernelGGL((batched_big_kernel<512, 1024, 0>), grid, dim3(1024), 0, st, t, nc); break;
-    default: hipLaunchKernelGGL((batched_big_kernel<512, 1024, 1>), grid, dim3(1024), 0, st, t, nc); break;
+    case 6: hipLaunchKernelGGL((batched_big_kernel<512, 512, 0>), grid, dim3(512), 0, st, t, nc); break;
+    default: hipLaunchKernelGGL((batched_big_kernel<512, 512, 1>), grid, dim3(512), 0, st, t, nc); break;
   }
   int tiles = 0;
   size_t nel = 0;

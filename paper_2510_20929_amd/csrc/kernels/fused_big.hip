@@ -1,8 +1,8 @@
 // Fused forward + adjoint kernels for 256^2 and 512^2 frames (thin wrappers over
-// big_body) and the probe-gradient reduction. Two layouts: variant 0 runs one
-// workgroup of 1024 threads per CU whose line blocks fill most of the LDS (512-point
-// lines use the wide line transform, 32 lanes per line); variant 1 runs two workgroups
-// per CU with fewer threads and smaller blocks (512 threads for 256^2, 256 for 512^2).
+// big_body), the probe-gradient reductions and the weight gradients of staged
+// probe-wave gradients. Two layouts: variant 0 runs one workgroup per CU (1024 threads for
+// 256^2; 512 for 512^2, whose lines take 32 elements per thread and twice the registers);
+// variant 1 runs two workgroups of half the threads per CU.
 #include <algorithm>
 
 #include "big_body.hpp"
@@ -11,10 +11,7 @@
 
 namespace ptyhip {
 
-int fused_big_threads(int N, int variant) {
-  if (variant != 1) return 1024;
-  return N == 256 ? 512 : 256;
-}
+int fused_big_threads(int N, int variant) { return (N == 256 ? 1024 : 512) / (variant == 1 ? 2 : 1); }
 
 int fused_big_wg_per_cu(int variant) { return variant == 1 ? 2 : 1; }
 
@@ -23,10 +20,14 @@ size_t fused_big_scratch_elems(int N, int S, int M, int E, size_t* pacc_off) {
   return big_scratch_elems(N, M, E, pacc_off);
 }
 
-template <int N, int T, int LOSS>
-__global__ __launch_bounds__(T) void fused_big_kernel(CallArgs a) {
+// waves per SIMD of every layout: 16 waves per CU at 256^2, 8 at 512^2
+template <int N>
+constexpr int big_waves() { return N == 256 ? 4 : 2; }
+
+template <int N, int T, int LOSS, bool FA>
+__global__ __launch_bounds__(T, big_waves<N>()) void fused_big_kernel(CallArgs a) {
   __shared__ BigShared<N, T> sh;
-  big_body<N, T, LOSS>(a, sh, blockIdx.x, gridDim.x);
+  big_body<N, T, LOSS, 0, FA>(a, sh, blockIdx.x, gridDim.x);
 }
 
 __global__ __launch_bounds__(256) void probe_reduce_big_kernel(const float2* __restrict__ scratch, size_t stride,
@@ -154,20 +155,101 @@ hipError_t launch_eig_stage_reduce(const float2* gp, const float* w, const int* 
   return hipGetLastError();
 }
 
+// Weight gradients from staged probe-wave gradients: for position k and eigenprobe e
+//   part[k][s][e] = sum over split s of the 2 M N^2 floats of gP[k] . U[e],
+// i.e. Re sum conj(gP) U, a contraction of [n][L] with [E][L] on the matrix cores (FP32
+// inputs and accumulation, 16 x 16 x 4). A wave takes 32 positions (two row blocks that
+// share the eigenprobe loads) and every fourth run of 64 floats of the split; the lanes of
+// a row load 16 bytes each, and which four floats meet in one product is the same for both
+// operands, so their order does not matter. The FP32 accumulators hold 64 terms before
+// they are added in FP64; the four waves and (in the final reduction) the splits are
+// added in order. Bound by reading the staged frames once.
+typedef float f4_t __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(256) void weight_contract_kernel(const float* __restrict__ gp, const float* __restrict__ U,
+                                                              const int* __restrict__ valid, int n, int E,
+                                                              size_t L, int splits, double* __restrict__ part) {
+  __shared__ double red[4][32][16];
+  const int lane = threadIdx.x & (WAVE - 1), wave = threadIdx.x / WAVE;
+  const int row = lane & 15, sub = lane >> 4;
+  const int k0 = blockIdx.x * 32, s = blockIdx.y;
+  const size_t runs = L / 64;  // N >= 256: a multiple of 64 floats
+  const size_t c0 = runs * s / splits, c1 = runs * (s + 1) / splits;
+  const int ka = k0 + row, kb = k0 + 16 + row;
+  const bool oa = ka < n && valid[ka], ob = kb < n && valid[kb], oe = row < E;
+  const float* pa = gp + (oa ? size_t(ka) * L : 0) + sub * 4;
+  const float* pb = gp + (ob ? size_t(kb) * L : 0) + sub * 4;
+  const float* pu = U + (oe ? size_t(row) * L : 0) + sub * 4;
+  const f4_t z = {0.f, 0.f, 0.f, 0.f};
+  double da[4] = {0, 0, 0, 0}, db[4] = {0, 0, 0, 0};
+  for (size_t c = c0 + wave; c < c1; c += 4) {
+    f4_t A[4], Bm[4], Uv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      A[i] = oa ? *reinterpret_cast<const f4_t*>(pa + c * 64 + i * 16) : z;
+      Bm[i] = ob ? *reinterpret_cast<const f4_t*>(pb + c * 64 + i * 16) : z;
+      Uv[i] = oe ? *reinterpret_cast<const f4_t*>(pu + c * 64 + i * 16) : z;
+    }
+    f4_t xa = z, xb = z;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        xa = __builtin_amdgcn_mfma_f32_16x16x4f32(A[i][j], Uv[i][j], xa, 0, 0, 0);
+        xb = __builtin_amdgcn_mfma_f32_16x16x4f32(Bm[i][j], Uv[i][j], xb, 0, 0, 0);
+      }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      da[i] += double(xa[i]);
+      db[i] += double(xb[i]);
+    }
+  }
+  // accumulator i of a lane: position row 4 sub + i, eigenprobe `row`
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    red[wave][4 * sub + i][row] = da[i];
+    red[wave][16 + 4 * sub + i][row] = db[i];
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 32 * 16; i += 256) {
+    const int kk = k0 + i / 16, e = i % 16;
+    if (kk >= n || e >= E) continue;
+    const double t = red[0][i / 16][e] + red[1][i / 16][e] + red[2][i / 16][e] + red[3][i / 16][e];
+    part[(size_t(kk) * splits + s) * E + e] = valid[kk] ? t : 0.0;
+  }
+}
+
+// enough splits for about eight waves per CU, none below 16 K floats
+int weight_contract_splits(int n, int M, int N) {
+  const size_t L = size_t(2) * M * N * N;
+  const size_t want = std::max<size_t>(1, 1024 / size_t((n + 31) / 32));
+  return int(std::max<size_t>(1, std::min<size_t>(want, L / 16384)));
+}
+
+hipError_t launch_weight_contract(const float2* gp, const float2* U, const int* valid, int n, int E, int M,
+                                  int N, int splits, double* part, hipStream_t st) {
+  const size_t L = size_t(2) * M * N * N;
+  hipLaunchKernelGGL(weight_contract_kernel, dim3(unsigned((n + 31) / 32), unsigned(splits)), dim3(256), 0, st,
+                     reinterpret_cast<const float*>(gp), reinterpret_cast<const float*>(U), valid, n, E, L,
+                     splits, part);
+  return hipGetLastError();
+}
+
 // Mode-split form (a.groups > 1) of the four-step body: forward pass (PH 1) and adjoint
 // pass (PH 2) over (position, mode group) items; the loss pass between them is
 // split_loss_nat_kernel + split_loss_total_kernel.
 template <int N, int T, int PH>
-__global__ __launch_bounds__(T) void split_big_kernel(CallArgs a) {
+__global__ __launch_bounds__(T, big_waves<N>()) void split_big_kernel(CallArgs a) {
   __shared__ BigShared<N, T> sh;
-  big_body<N, T, 0, PH>(a, sh, blockIdx.x, gridDim.x);
+  big_body<N, T, 0, PH, true>(a, sh, blockIdx.x, gridDim.x);
 }
 
-// Loss pass of the mode-split form for frames in natural pixel order. Block (c, k) takes
-// pixels [c SPLIT_LOSS_PIX, (c + 1) SPLIT_LOSS_PIX) of position k: I = the sum of the
-// position's partial intensities in group order, the loss against the DC-centred
-// measurement, I_pred, and cfr = 2 dl/dI / (K_norm N^2) (already scaled by gscale); its
-// loss sum goes to lpart[k][c].
+// Loss pass of the mode-split form for frames in the column order of the four-step body
+// (element (cg, kk, lane) at cg 4 N + kk 64 + lane is frequency (lane / 4 + 16 kk,
+// 4 cg + lane mod 4)). Block (c, k) takes elements [c SPLIT_LOSS_PIX, (c + 1)
+// SPLIT_LOSS_PIX) of position k: I = the sum of the position's partial intensities in group
+// order, the loss against the DC-centred measurement, I_pred, and cfr = 2 dl/dI / (K_norm
+// N^2) (already scaled by gscale); its loss sum goes to lpart[k][c].
 constexpr int SPLIT_LOSS_PIX = SPLIT_LOSS_PIX_BIG;
 
 template <int LOSS>
@@ -175,7 +257,7 @@ __global__ __launch_bounds__(1024) void split_loss_nat_kernel(CallArgs a, int N,
   __shared__ double red[2 * (1024 / WAVE)];
   const int c = blockIdx.x, nch = gridDim.x;
   const size_t NN = size_t(N) * N;
-  const int p0 = c * SPLIT_LOSS_PIX, p1 = min(int(NN), p0 + SPLIT_LOSS_PIX);
+  const int p0 = c * SPLIT_LOSS_PIX;  // N^2 is a multiple of SPLIT_LOSS_PIX
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   for (int k = blockIdx.y; k < a.K; k += gridDim.y) {
     const PosInfo p = parse_position(a.pos, k, N, a.H, a.W, want_pos);
@@ -183,35 +265,34 @@ __global__ __launch_bounds__(1024) void split_loss_nat_kernel(CallArgs a, int N,
     if (p.ok) {
       // PP pixels per thread, their loads in flight together
       constexpr int PP = SPLIT_LOSS_PIX / 1024;
-      const float* ip = a.ipart + size_t(k) * a.groups * NN;
-      int px[PP];
-      bool on[PP];
-      float I[PP];
+      const float* ip = a.ipart + size_t(k) * a.groups * NN + p0 + threadIdx.x;
+      float I[PP], im[PP];
+      int ci[PP];
 #pragma unroll
       for (int j = 0; j < PP; ++j) {
-        px[j] = p0 + int(threadIdx.x) + 1024 * j;
-        on[j] = px[j] < p1;
+        const int px = p0 + int(threadIdx.x) + 1024 * j, in = px % (4 * N), lane = in & (WAVE - 1);
+        ci[j] = centred_index((lane >> 2) + 16 * (in / WAVE), 4 * (px / (4 * N)) + (lane & 3), N);
+        im[j] = a.imeas[size_t(k) * NN + ci[j]];
         I[j] = 0.f;
       }
       for (int g = 0; g < a.groups; ++g) {
         float v[PP];
 #pragma unroll
-        for (int j = 0; j < PP; ++j) v[j] = on[j] ? ip[size_t(g) * NN + px[j]] : 0.f;
+        for (int j = 0; j < PP; ++j) v[j] = ip[size_t(g) * NN + 1024 * j];
 #pragma unroll
         for (int j = 0; j < PP; ++j) I[j] += v[j];
       }
 #pragma unroll
       for (int j = 0; j < PP; ++j) {
-        if (!on[j]) continue;
-        const int ci = centred_index(px[j] / N, px[j] % N, N);
         float l, cc;
-        loss_terms<LOSS>(I[j], a.imeas[size_t(k) * NN + ci], a.eps, l, cc);
+        loss_terms<LOSS>(I[j], im[j], a.eps, l, cc);
         lsum += double(l);
-        if (a.ipred) a.ipred[size_t(k) * NN + ci] = I[j];
-        if (a.cfr) a.cfr[size_t(k) * NN + px[j]] = a.gscale * cc;
+        if (a.ipred) a.ipred[size_t(k) * NN + ci[j]] = I[j];
+        if (a.cfr) a.cfr[size_t(k) * NN + p0 + threadIdx.x + 1024 * j] = a.gscale * cc;
       }
     } else if (a.ipred) {
-      for (int pix = p0 + int(threadIdx.x); pix < p1; pix += 1024) a.ipred[size_t(k) * NN + pix] = 0.f;
+      for (int pix = p0 + int(threadIdx.x); pix < p0 + SPLIT_LOSS_PIX; pix += 1024)
+        a.ipred[size_t(k) * NN + pix] = 0.f;
     }
     const double tot = block_sum<1024>(lsum, red);
     if (threadIdx.x == 0) lpart[size_t(k) * nch + c] = tot;
@@ -249,16 +330,21 @@ hipError_t launch_fused_big_split(const CallArgs& a, int N, int variant, int gri
   const bool two = variant == 1;
   switch (N) {
     case 256: return two ? launch_big_split_t<256, 512>(a, gi, lpart, st) : launch_big_split_t<256, 1024>(a, gi, lpart, st);
-    case 512: return two ? launch_big_split_t<512, 256>(a, gi, lpart, st) : launch_big_split_t<512, 1024>(a, gi, lpart, st);
+    case 512: return two ? launch_big_split_t<512, 256>(a, gi, lpart, st) : launch_big_split_t<512, 512>(a, gi, lpart, st);
     default: return hipErrorInvalidValue;
   }
 }
 
+template <int N, int T, bool FA>
+static hipError_t launch_big_m(const CallArgs& a, int grid, hipStream_t st) {
+  if (a.loss == 0) hipLaunchKernelGGL((fused_big_kernel<N, T, 0, FA>), dim3(grid), dim3(T), 0, st, a);
+  else hipLaunchKernelGGL((fused_big_kernel<N, T, 1, FA>), dim3(grid), dim3(T), 0, st, a);
+  return hipGetLastError();
+}
+
 template <int N, int T>
 static hipError_t launch_big_t(const CallArgs& a, int grid, hipStream_t st) {
-  if (a.loss == 0) hipLaunchKernelGGL((fused_big_kernel<N, T, 0>), dim3(grid), dim3(T), 0, st, a);
-  else hipLaunchKernelGGL((fused_big_kernel<N, T, 1>), dim3(grid), dim3(T), 0, st, a);
-  return hipGetLastError();
+  return a.mode == MODE_FWD_ADJ ? launch_big_m<N, T, true>(a, grid, st) : launch_big_m<N, T, false>(a, grid, st);
 }
 
 hipError_t launch_fused_big(const CallArgs& a, int N, int variant, int grid, hipStream_t st) {
@@ -266,7 +352,7 @@ hipError_t launch_fused_big(const CallArgs& a, int N, int variant, int grid, hip
   const bool two = variant == 1;
   switch (N) {
     case 256: return two ? launch_big_t<256, 512>(a, grid, st) : launch_big_t<256, 1024>(a, grid, st);
-    case 512: return two ? launch_big_t<512, 256>(a, grid, st) : launch_big_t<512, 1024>(a, grid, st);
+    case 512: return two ? launch_big_t<512, 256>(a, grid, st) : launch_big_t<512, 512>(a, grid, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -36,7 +36,8 @@ struct FinalArgs {
   size_t probe_elems;
   int K, E;
   int accumulate;
-  int rep;                  // partial position / weight sums per position (0 or 1: one)
+  int rep;                  // partial position sums per position (0 or 1: one)
+  int wrep;                 // partial weight sums per position (0 or 1: one)
 };
 
 // Gather of the per-position window gradients into the object gradient.
@@ -100,6 +101,11 @@ int split_loss_chunks(int N);
 hipError_t launch_fused_big_split(const CallArgs& a, int N, int variant, int grid, double* lpart, hipStream_t st);
 hipError_t launch_eig_stage_reduce(const float2* gp, const float* w, const int* valid, int n, int E, int M, int N,
                                    int splits, float2* part, float2* g_probe, int accumulate, hipStream_t st);
+// weight gradients of a chunk from its staged probe-wave gradients: `splits` partial sums
+// per position (part [n][splits][E])
+int weight_contract_splits(int n, int M, int N);
+hipError_t launch_weight_contract(const float2* gp, const float2* U, const int* valid, int n, int E, int M,
+                                  int N, int splits, double* part, hipStream_t st);
 hipError_t launch_probe_reduce_big(const CallArgs& a, int N, int grid, float2* g_probe, int accumulate,
                                    hipStream_t st);
 
