@@ -99,8 +99,12 @@ ptyhip_status ptyhip_batch_create(const ptyhip_desc* descs, const int32_t* K, in
     const double N = descs[i].frame;
     cost[i] = double(std::max(K[i], 1)) * descs[i].n_modes * N * N * std::log2(N * N);
   }
-  // per frame-size class: one workgroup per CU (a tuned total if given), one workgroup per
-  // dataset at least, the rest by largest remainder in proportion to the work; inside a
+  // per frame-size class: at most one workgroup per CU (a tuned total if given), one
+  // workgroup per dataset at least. A workgroup takes whole positions one after the other,
+  // so a class ends with the dataset whose rounds of positions last longest: the split is the
+  // one with the shortest such time. In proportion to the work instead, a
+  // dataset with a few more positions than workgroups takes a second round for them (200
+  // positions of 3 modes on 187 workgroups: 6 mode times where 4 are possible). Inside a
   // class the most expensive datasets take the first workgroups. Concurrent classes
   // (tune variant 1) split that total among the classes in proportion to their work.
   b->concurrent = tune && tune->variant == 1;
@@ -122,21 +126,45 @@ ptyhip_status ptyhip_batch_create(const ptyhip_desc* descs, const int32_t* K, in
     const int share = b->concurrent ? int(std::lround(double(grid_total) * cls_cost[c] / all_cost)) : grid_total;
     const int total = std::max(nc, share);
     b->cls_wg[c] = total;
-    double tot = 0.0;
-    for (int i : members) tot += cost[i];
-    const int left = total - nc;
-    std::vector<double> rem(n, 0.0);
-    int given = 0;
+    // a position's time, in half mode times: its modes and half a mode for patch, loss and window
+    const auto unit = [&](int i) { return int64_t(2 * descs[i].n_modes + 1); };
+    const auto need = [&](int64_t t, int i) {  // workgroups of dataset i within time t
+      const int64_t rounds = std::max<int64_t>(1, t / unit(i));
+      return std::max<int64_t>(1, (K[i] + rounds - 1) / rounds);
+    };
+    const auto fits = [&](int64_t t) {
+      int64_t w = 0;
+      for (int i : members) w += need(t, i);
+      return w <= total;
+    };
+    int64_t lo = 1, hi = 1;
     for (int i : members) {
-      const double share = cost[i] / tot * left;
-      const int w = int(std::floor(share));
-      b->n_wg[i] += w;
-      given += w;
-      rem[i] = share - w;
+      lo = std::max(lo, unit(i));
+      hi = std::max(hi, std::max(K[i], 1) * unit(i));
+    }
+    while (lo < hi) {
+      const int64_t mid = lo + (hi - lo) / 2;
+      if (fits(mid)) hi = mid;
+      else lo = mid + 1;
+    }
+    int used = 0;
+    for (int i : members) {
+      b->n_wg[i] = int(need(lo, i));
+      used += b->n_wg[i];
     }
     std::vector<int> order = members;
-    std::sort(order.begin(), order.end(), [&](int x, int y) { return rem[x] > rem[y]; });
-    for (int j = 0; j < left - given; ++j) b->n_wg[order[j % nc]] += 1;
+    // what is left goes where a workgroup's rounds last longest
+    for (; used < total; ++used) {
+      int at = -1;
+      int64_t worst = 0;
+      for (int i : members) {
+        const int64_t t = (K[i] + b->n_wg[i] - 1) / b->n_wg[i] * unit(i);
+        if (b->n_wg[i] < K[i] && t > worst) worst = t, at = i;
+      }
+      if (at < 0) break;
+      b->n_wg[at] += 1;
+    }
+    b->cls_wg[c] = used;
     std::sort(order.begin(), order.end(), [&](int x, int y) { return cost[x] > cost[y]; });
     int w0 = 0;
     for (int i : order) {
