@@ -478,6 +478,10 @@ struct WaveLines {
 // x[n1 + N1 n2], the twiddle W_N^{n1 k2}, then for each k2 a DFT of size N1 giving
 // X[k2 + N2 k1]; the inverse is the same split with W_N^-1 (unnormalised). Stage-1
 // results are stored at N1 k2 + (n1 XOR (k2 mod N1)), as in LineTile.
+// Transforms are unnormalised; the twiddle table is held in LDS as W_N^{n1 k2} at k2 N1 + n1
+// (load_twiddles), so that reads are at constant offsets from the lane's n1. Cells are
+// addressed by byte offsets: a row and a column pitch of 2^a + 2^b bytes make the XOR of
+// the swizzle an XOR of offsets, one instruction per cell and none for its position.
 template <int N, int T>
 struct FrameLds {
   static constexpr int N1 = Split<N>::N1;
@@ -486,161 +490,127 @@ struct FrameLds {
   static_assert(WAVE % N1 == 0, "the N1 threads of a line must share a wavefront");
   static constexpr int LW = WAVE / N1;  // lines per wave in the column pass
   static constexpr int P = N + N1;
+  static constexpr int PB = P * 8;      // row pitch in bytes
   static constexpr int LDS_ELEMS = N * P;
   static constexpr int EL = N * N / T;  // pixels per thread in the element passes
-  __device__ __forceinline__ static int sw(int n1, int k2) { return N1 * k2 + (n1 ^ (k2 & (N1 - 1))); }
+  static_assert((N & (N - 1)) == 0 && N1 == 8 && N >= 64, "offsets of rows 0..7 and cells 0..7 XOR like their numbers");
   __device__ __forceinline__ static void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
-
-  // every line (element i of line ln at lds[ln LS + i ES]) transformed in place, times
-  // `scale`. Rows (ES = 1): line t / N1, lane q = t mod N1 (a half-wave reads four rows'
-  // consecutive cells); columns (ES = P): the lines of a wave are WAVE / N1 adjacent
-  // columns and lane q = (t mod WAVE) / N1, so a half-wave reads WAVE / N1 consecutive
-  // cells in each of four rows (with P = N + N1 both fall in distinct LDS banks).
-  template <bool INV, bool COLS>
-  __device__ __forceinline__ static void lines(float2* lds, int LS, int ES, const float2* __restrict__ tw,
-                                               float scale) {
-    const int t = opaque_tid();
-    const int q = COLS ? (t % WAVE) / LW : t % N1;
-    const int ln = COLS ? (t / WAVE) * LW + t % LW : t / N1;
-    float2* base = lds + ln * LS;
-    float2 u[N2];
-#pragma unroll
-    for (int n2 = 0; n2 < N2; ++n2) u[n2] = base[(q + N1 * n2) * ES];
-    lines_from<INV, COLS>(lds, LS, ES, tw, scale, u);
+  __device__ __forceinline__ static float2& at(float2* lds, int off) {
+    return *reinterpret_cast<float2*>(reinterpret_cast<char*>(lds) + off);
   }
-  // as lines, with the thread's stage-1 input x[q + N1 n2] already in u[n2]
+  __device__ __forceinline__ static void load_twiddles(float2* tws, const float2* __restrict__ tw) {
+    for (int i = threadIdx.x; i < N; i += T) tws[i] = tw[(i % N1) * (i / N1)];
+  }
+
+  // Rows: line t / N1, lane q = t mod N1 (a half-wave reads four rows' consecutive cells);
+  // columns: the lines of a wave are WAVE / N1 adjacent columns and lane
+  // q = (t mod WAVE) / N1, so a half-wave reads WAVE / N1 consecutive cells in each of four
+  // rows (with P = N + N1 both fall in distinct LDS banks).
+  template <bool COLS>
+  struct Line {
+    int t, q, org;  // org: byte offset of the line's first cell
+    __device__ __forceinline__ Line() {
+      t = opaque_tid();
+      q = COLS ? (t % WAVE) / LW : t % N1;
+      org = COLS ? ((t / WAVE) * LW + t % LW) * 8 : (t / N1) * PB;
+    }
+    static constexpr int ES = COLS ? PB : 8;  // bytes from cell to cell of a line
+    // cell q + N1 n2
+    __device__ __forceinline__ int cell(int n2) const { return org + q * ES + n2 * N1 * ES; }
+    // cell N1 k2 + (n1 XOR (k2 mod N1)) of the intermediate, for the lane's n1 = q ...
+    __device__ __forceinline__ int mid1(int k2) const { return ((q * ES) ^ ((k2 % N1) * ES)) + org + k2 * N1 * ES; }
+    // ... and for its k2 = q + N1 jj
+    __device__ __forceinline__ int mid2(int n1, int jj) const {
+      return ((q * ES) ^ (n1 * ES)) + (org + q * N1 * ES) + jj * N1 * N1 * ES;
+    }
+  };
+
+  // Stage 1 and the exchange: u holds x[q + N1 n2] on entry and, as jj N1 + n1, the stage-2
+  // inputs of k2 = q + N1 jj transformed to X[k2 + N2 k1] at jj N1 + k1 on return.
   template <bool INV, bool COLS>
-  __device__ __forceinline__ static void lines_from(float2* lds, int LS, int ES, const float2* __restrict__ tw,
-                                                    float scale, float2 (&u)[N2]) {
-    const int t = opaque_tid();
-    const int q = COLS ? (t % WAVE) / LW : t % N1;
-    const int ln = COLS ? (t / WAVE) * LW + t % LW : t / N1;
-    float2* base = lds + ln * LS;
+  __device__ __forceinline__ static void line(const Line<COLS>& L, float2* lds, const float2* tws, float2 (&u)[N2]) {
     Dft<N2, INV>::run(u);
     // twiddle and store four at a time (the caller's per-pixel state shares the registers)
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) {
-      if (k2 > 0) u[k2] = INV ? cmul_conjb(u[k2], tw[q * k2]) : cmul(u[k2], tw[q * k2]);
-      base[sw(q, k2) * ES] = u[k2];
+      if (k2 > 0) u[k2] = INV ? cmul_conjb(u[k2], tws[k2 * N1 + L.q]) : cmul(u[k2], tws[k2 * N1 + L.q]);
+      at(lds, L.mid1(k2)) = u[k2];
       if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
     wave_fence();
 #pragma unroll
     for (int jj = 0; jj < N2 / N1; ++jj) {
-      const int k2 = q + N1 * jj;
 #pragma unroll
-      for (int n1 = 0; n1 < N1; ++n1) u[jj * N1 + n1] = base[sw(n1, k2) * ES];
+      for (int n1 = 0; n1 < N1; ++n1) u[jj * N1 + n1] = at(lds, L.mid2(n1, jj));
       Dft<N1, INV>::run(&u[jj * N1]);
     }
+  }
+  // every line of the frame transformed in place, its stage-1 input in u (`from`) or read
+  // from the thread's cells
+  template <bool INV, bool COLS>
+  __device__ __forceinline__ static void lines_from(float2* lds, const float2* tws, float2 (&u)[N2]) {
+    const Line<COLS> L;
+    line<INV, COLS>(L, lds, tws, u);
     wave_fence();
+    // X[q + N1 (jj + (N2 / N1) k1)] is cell jj + (N2 / N1) k1 of the thread
 #pragma unroll
-    for (int jj = 0; jj < N2 / N1; ++jj)
+    for (int i = 0; i < N2; ++i) at(lds, L.cell(i)) = u[reg_of(i)];
+  }
+  template <bool COLS>
+  __device__ __forceinline__ static void read_cells(float2* lds, float2 (&u)[N2]) {
+    const Line<COLS> L;
 #pragma unroll
-      for (int k1 = 0; k1 < N1; ++k1) base[(q + N1 * jj + N2 * k1) * ES] = cscale(u[jj * N1 + k1], scale);
+    for (int n2 = 0; n2 < N2; ++n2) u[n2] = at(lds, L.cell(n2));
   }
 
   // Column and row of element e (0 <= e < N2) that cols_to_regs leaves in thread t:
   // column col(t), row row(t, e); these are the cells the thread's column pass reads and
-  // writes, so a caller that writes exactly them needs no barrier before cols().
+  // writes, so a caller that writes exactly them needs no barrier before cols_from().
   __device__ __forceinline__ static int col(int t) { return (t / WAVE) * LW + t % LW; }
   __device__ __forceinline__ static int row(int t, int e) { return (t % WAVE) / LW + N1 * (e / N1) + N2 * (e % N1); }
 
-  // The two passes on their own; the caller places the block barriers. A row pass reads
-  // and writes only the rows of its wave, and thread t only the cells (t / N1, t mod N1 +
-  // N1 j), which it may therefore fill or read itself without a barrier; a column pass
-  // touches only the columns of its wave. Rows and columns need a barrier between them.
+  // The passes; the caller places the block barriers. A row pass reads and writes only the
+  // rows of its wave, and thread t only the cells (t / N1, t mod N1 + N1 j), which it may
+  // therefore fill or read itself without a barrier; a column pass touches only the
+  // columns of its wave. Rows and columns need a barrier between them.
   template <bool INV>
-  __device__ __forceinline__ static void rows(float2* lds, const float2* __restrict__ tw, float scale) {
-    lines<INV, false>(lds, P, 1, tw, scale);
-  }
-  template <bool INV>
-  __device__ __forceinline__ static void cols(float2* lds, const float2* __restrict__ tw, float scale) {
-    lines<INV, true>(lds, 1, P, tw, scale);
+  __device__ __forceinline__ static void rows(float2* lds, const float2* tws) {
+    float2 u[N2];
+    read_cells<false>(lds, u);
+    lines_from<INV, false>(lds, tws, u);
   }
   // Row (column) pass whose stage-1 input is already in registers: u[n2] is the cell the
   // pass would read, (t / N1, t mod N1 + N1 n2) for rows, (row(t, e), col(t)) with
   // e = reg_of(n2) for columns (so that a caller holding the cols_to_regs layout passes
   // v[reg_of(n2)] as u[n2]).
   template <bool INV>
-  __device__ __forceinline__ static void rows_from(float2* lds, const float2* __restrict__ tw, float scale,
-                                                   float2 (&u)[N2]) {
-    lines_from<INV, false>(lds, P, 1, tw, scale, u);
+  __device__ __forceinline__ static void rows_from(float2* lds, const float2* tws, float2 (&u)[N2]) {
+    lines_from<INV, false>(lds, tws, u);
   }
   template <bool INV>
-  __device__ __forceinline__ static void cols_from(float2* lds, const float2* __restrict__ tw, float scale,
-                                                   float2 (&u)[N2]) {
-    lines_from<INV, true>(lds, 1, P, tw, scale, u);
+  __device__ __forceinline__ static void cols_from(float2* lds, const float2* tws, float2 (&u)[N2]) {
+    lines_from<INV, true>(lds, tws, u);
   }
   // Row pass that ends in registers: h[i] is cell (t / N1, t mod N1 + N1 i) of the
-  // transformed rows, times `scale`; the LDS cells keep the stage-1 intermediate.
+  // transformed rows; the LDS cells keep the stage-1 intermediate.
   template <bool INV>
-  __device__ __forceinline__ static void rows_to_regs(float2* lds, const float2* __restrict__ tw, float scale,
-                                                      float2 (&h)[N2]) {
-    const int t = opaque_tid();
-    const int q = t % N1;
-    float2* base = lds + (t / N1) * P;
+  __device__ __forceinline__ static void rows_to_regs(float2* lds, const float2* tws, float2 (&h)[N2]) {
+    const Line<false> L;
     float2 u[N2];
+    read_cells<false>(lds, u);
+    line<INV, false>(L, lds, tws, u);
 #pragma unroll
-    for (int n2 = 0; n2 < N2; ++n2) u[n2] = base[q + N1 * n2];
-    Dft<N2, INV>::run(u);
-#pragma unroll
-    for (int k2 = 0; k2 < N2; ++k2) {
-      if (k2 > 0) u[k2] = INV ? cmul_conjb(u[k2], tw[q * k2]) : cmul(u[k2], tw[q * k2]);
-      base[sw(q, k2)] = u[k2];
-      if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-    }
-    wave_fence();
-#pragma unroll
-    for (int jj = 0; jj < N2 / N1; ++jj) {
-      const int k2 = q + N1 * jj;
-#pragma unroll
-      for (int n1 = 0; n1 < N1; ++n1) u[jj * N1 + n1] = base[sw(n1, k2)];
-      Dft<N1, INV>::run(&u[jj * N1]);
-    }
-    // output k2 + N2 k1 = q + N1 (jj + 2 k1) is the thread's cell i = jj + 2 k1
-#pragma unroll
-    for (int i = 0; i < N2; ++i) h[i] = cscale(u[reg_of(i)], scale);
+    for (int i = 0; i < N2; ++i) h[i] = u[reg_of(i)];
   }
   // row(t, reg_of(n2)) = (t mod WAVE) / LW + N1 n2
   __host__ __device__ static constexpr int reg_of(int n2) { return (n2 % (N2 / N1)) * N1 + n2 / (N2 / N1); }
 
-  // Forward column pass that ends in registers: v[e] is frequency (row(t, e), col(t)),
-  // times `scale`; the LDS cells keep the stage-1 intermediate.
-  __device__ __forceinline__ static void cols_to_regs(float2* lds, const float2* __restrict__ tw, float scale,
-                                                      float2 (&v)[N2]) {
-    const int t = opaque_tid();
-    const int q = (t % WAVE) / LW;
-    float2* base = lds + col(t);
-#pragma unroll
-    for (int n2 = 0; n2 < N2; ++n2) v[n2] = base[(q + N1 * n2) * P];
-    Dft<N2, false>::run(v);
-#pragma unroll
-    for (int k2 = 0; k2 < N2; ++k2) {
-      if (k2 > 0) v[k2] = cmul(v[k2], tw[q * k2]);
-      base[sw(q, k2) * P] = v[k2];
-      if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-    }
-    wave_fence();
-#pragma unroll
-    for (int jj = 0; jj < N2 / N1; ++jj) {
-      const int k2 = q + N1 * jj;
-#pragma unroll
-      for (int n1 = 0; n1 < N1; ++n1) v[jj * N1 + n1] = base[sw(n1, k2) * P];
-      Dft<N1, false>::run(&v[jj * N1]);
-#pragma unroll
-      for (int k1 = 0; k1 < N1; ++k1) v[jj * N1 + k1] = cscale(v[jj * N1 + k1], scale);
-    }
-  }
-
-  // 2D transform of the frame in LDS (forward: exp(-2 pi i k.n / N); INV: the conjugate
-  // kernel), times `scale`; block barriers before, between the passes and after
-  template <bool INV>
-  __device__ __forceinline__ static void transform(float2* lds, const float2* __restrict__ tw, float scale) {
-    __syncthreads();
-    rows<INV>(lds, tw, 1.f);
-    __syncthreads();
-    cols<INV>(lds, tw, scale);
-    __syncthreads();
+  // Forward column pass that ends in registers: v[e] is frequency (row(t, e), col(t));
+  // the LDS cells keep the stage-1 intermediate.
+  __device__ __forceinline__ static void cols_to_regs(float2* lds, const float2* tws, float2 (&v)[N2]) {
+    const Line<true> L;
+    read_cells<true>(lds, v);
+    line<false, true>(L, lds, tws, v);
   }
 };
 

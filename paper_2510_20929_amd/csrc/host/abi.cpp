@@ -386,9 +386,9 @@ static ptyhip_status run_call(Plan* p, const CallArgs& a, bool plain, bool acc, 
       c.cfr = a.mode == MODE_FWD_ADJ ? p->cfr : nullptr;
       c.kvalid = p->kvalid;
       c.gpstage = ((want_probe || wsplits) && a.mode == MODE_FWD_ADJ) ? p->gpstage : nullptr;
-      // the four-step passes hand the far fields over in the frames that the adjoint pass
-      // then overwrites with the probe-wave gradients, mode by mode
-      c.far = (!p->on_chip && a.mode == MODE_FWD_ADJ) ? p->gpstage : nullptr;
+      // the passes hand the far fields over in the frames that the adjoint pass then
+      // overwrites with the probe-wave gradients, mode by mode
+      c.far = a.mode == MODE_FWD_ADJ ? p->gpstage : nullptr;
       c.gwin = want_obj ? p->gwin : nullptr;
       c.wvalid = p->wvalid;
       timing_begin(p, st);

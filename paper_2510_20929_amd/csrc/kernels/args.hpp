@@ -65,8 +65,8 @@ struct CallArgs {
   float* ipart;           // [K][groups][NN] partial intensities (frame layout: element i of thread t at i*T + t)
   float* cfr;             // [K][NN] 2 dl/dI / (K_norm N^2) (same layout)
   int* kvalid;            // [K] 1 where the position's window and loss are valid
-  float2* far;            // four-step mode-split form: far fields [K][M][NN] of the forward pass, in the
-                          // order its column pass holds them, or nullptr (no adjoint)
+  float2* far;            // mode-split form: far fields [K][M][NN] of the forward pass, in the order its
+                          // threads hold them, or nullptr (no adjoint)
 };
 
 }  // namespace ptyhip

@@ -91,9 +91,6 @@ __device__ __forceinline__ void swap_pair(float2& x0, float2& x1) {
   x1 = row_dpp<0x128, 0x3>(x1, x0);
   x0 = a;
 }
-__device__ __forceinline__ float2 lo2(float4 v) { return make_float2(v.x, v.y); }
-__device__ __forceinline__ float2 hi2(float4 v) { return make_float2(v.z, v.w); }
-__device__ __forceinline__ float4 cat2(float2 a, float2 b) { return make_float4(a.x, a.y, b.x, b.y); }
 
 // Workgroup `wg` of `nwg` processes every nwg-th work item of the call `a`, starting at its
 // place in the order of XCDs.

@@ -1,8 +1,6 @@
 // Fused forward + adjoint kernels for frames that stay on chip (N <= 128): the
 // single-slice kernel (a thin wrapper over small_body) and the multislice kernel.
 #include "launch.hpp"
-#include "lds_body.hpp"
-#include "lds_ms.hpp"
 #include "small_body.hpp"
 
 namespace ptyhip {
@@ -11,20 +9,6 @@ template <int N, int T, int LOSS, bool RV, bool GOREG = RV>
 __global__ __launch_bounds__(T) void fused_small_kernel(CallArgs a) {
   __shared__ SmallShared<N, T> sh;
   small_body<N, T, LOSS, RV, GOREG>(a, sh, blockIdx.x, gridDim.x);
-}
-
-// the working frame resident in LDS, per-position state in registers (variants 5, 6)
-template <int N, int T, int LOSS, bool CFREG>
-__global__ __launch_bounds__(T) void fused_small_lds_kernel(CallArgs a) {
-  __shared__ LdsShared<N, T> sh;
-  lds_body<N, T, LOSS, CFREG>(a, sh, blockIdx.x, gridDim.x);
-}
-
-// multislice with the working frame resident in LDS (variants 5, 6 with several slices)
-template <int N, int T, int LOSS, bool LZ>
-__global__ __launch_bounds__(T) void fused_small_lds_ms_kernel(CallArgs a) {
-  __shared__ LdsShared<N, T> sh;
-  lds_ms_body<N, T, LOSS, LZ>(a, sh, blockIdx.x, gridDim.x);
 }
 
 template <int N, int T, int LOSS>
@@ -343,12 +327,12 @@ size_t fused_small_scratch_elems(int N, int S, int M, int E, int recompute, size
                                  bool near, bool fshift) {
   const size_t fr = size_t(N) * N;
   size_t base;
-  if (S > 1) base = fr * (size_t(2) * S + (recompute ? 0 : size_t(M) * S)) + (variant >= 5 && N == 128 ? fr / 2 : 0);
+  if (variant >= 5 && N == 128) base = lds_scratch_base(S, M, recompute, variant);
+  else if (S > 1) base = fr * (size_t(2) * S + (recompute ? 0 : size_t(M) * S));
   else if (near) base = fr * (2 + size_t(M));
   else if (fshift) base = fr * (M > 1 ? (recompute ? 2 : size_t(M) + 1) : 1) + fr;  // + shifted window spectrum
   else if ((variant == 2 || variant == 3) && N >= 64) base = fr / 2 + (recompute ? 0 : fr * size_t(M - 1));
   else if (variant == 4 && N >= 64) base = fr / 2 + fr + (recompute ? 0 : fr * size_t(M - 1));
-  else if (variant >= 5 && N == 128) base = variant == 5 ? fr / 2 : 0;  // far fields always recomputed
   else base = fr * (M > 1 ? (recompute ? 2 : size_t(M) + 1) : 1);
   *pacc_off = base;
   return base + fr * size_t(E) * M;
@@ -367,27 +351,8 @@ hipError_t launch_fused_small(const CallArgs& a, int N, int variant, int grid, h
       return launch_small_t<64, 512>(a, grid, st);
     case 128:
       if (variant >= 5) {
-        // far field, bilinear patch (the plan checks)
         if (a.near) return hipErrorInvalidValue;
-        if (a.S > 1) {
-          const bool lz = (a.want & WANT_LZ) && a.mode == MODE_FWD_ADJ && a.lz_part != nullptr;
-          if (a.loss == 0) {
-            if (lz) hipLaunchKernelGGL((fused_small_lds_ms_kernel<128, 1024, 0, true>), dim3(grid), dim3(1024), 0, st, a);
-            else hipLaunchKernelGGL((fused_small_lds_ms_kernel<128, 1024, 0, false>), dim3(grid), dim3(1024), 0, st, a);
-          } else {
-            if (lz) hipLaunchKernelGGL((fused_small_lds_ms_kernel<128, 1024, 1, true>), dim3(grid), dim3(1024), 0, st, a);
-            else hipLaunchKernelGGL((fused_small_lds_ms_kernel<128, 1024, 1, false>), dim3(grid), dim3(1024), 0, st, a);
-          }
-          return hipGetLastError();
-        }
-        if (variant == 5) {
-          if (a.loss == 0) hipLaunchKernelGGL((fused_small_lds_kernel<128, 1024, 0, false>), dim3(grid), dim3(1024), 0, st, a);
-          else hipLaunchKernelGGL((fused_small_lds_kernel<128, 1024, 1, false>), dim3(grid), dim3(1024), 0, st, a);
-        } else {
-          if (a.loss == 0) hipLaunchKernelGGL((fused_small_lds_kernel<128, 1024, 0, true>), dim3(grid), dim3(1024), 0, st, a);
-          else hipLaunchKernelGGL((fused_small_lds_kernel<128, 1024, 1, true>), dim3(grid), dim3(1024), 0, st, a);
-        }
-        return hipGetLastError();
+        return launch_fused_lds(a, variant, grid, st);
       }
       if (variant == 1) return launch_small_t<128, 1024>(a, grid, st);
       if (variant == 3) return launch_small_t<128, 1024, true>(a, grid, st);

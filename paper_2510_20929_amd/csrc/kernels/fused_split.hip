@@ -10,7 +10,7 @@
 //   loss     position k, in pixel chunks: I_k = sum_g ipart[k][g] (in group order),
 //            loss, dl/dI -> cfr[k] = 2 dl/dI / (K_norm N^2); then the chunk sums of a
 //            position in order and its validity kvalid[k];
-//   adjoint  item (k, g): far fields recomputed, scaled by cfr[k], transformed back;
+//   adjoint  item (k, g): the stored far fields scaled by cfr[k], transformed back;
 //            the group's patch gradient sum_{m in g} conj(P_m) g_m becomes window k G + g
 //            (the gather adds the G windows of a position), the probe-wave gradients
 //            conj(o) g_m are staged per position and mode for the eigenprobe reduction,
@@ -27,6 +27,34 @@
 
 namespace ptyhip {
 
+// Far field of one (position, mode), handed from the forward to the adjoint pass in the
+// frame that the adjoint then overwrites with the mode's probe-wave gradient: elements 2 j
+// and 2 j + 1 of thread t at (j T + t) 16 bytes.
+template <int E, int T>
+__device__ __forceinline__ void store_pairs(float2* frame, const float2 (&v)[E]) {
+  const BufFrame f(frame, E * T * 8);
+  const int t16 = opaque_tid() * 16;
+#pragma unroll
+  for (int j = 0; j < E / 2; ++j) f.st2(cat2(v[2 * j], v[2 * j + 1]), t16, j * T * 16);
+}
+template <int E, int T>
+__device__ __forceinline__ void load_pairs(const float2* frame, float2 (&v)[E]) {
+  const BufFrame f(frame, E * T * 8);
+  const int t16 = opaque_tid() * 16;
+#pragma unroll
+  for (int j = 0; j < E / 2; ++j) {
+    const float4 x = f.ld2(t16, j * T * 16);
+    v[2 * j] = lo2(x);
+    v[2 * j + 1] = hi2(x);
+  }
+}
+
+// Work item of workgroup-order place j: items go out in the order of the mode groups, so that
+// the workgroups of an XCD share their modes' eigenprobes; item k G + g is (position, group).
+__device__ __forceinline__ int split_item(const CallArgs& a, int j) {
+  return __builtin_amdgcn_readfirstlane((j % a.K) * a.groups + j / a.K);
+}
+
 template <int N, int T>
 __global__ __launch_bounds__(T) void split_forward_kernel(CallArgs a) {
   using F = Frame2D<N, T>;
@@ -37,10 +65,10 @@ __global__ __launch_bounds__(T) void split_forward_kernel(CallArgs a) {
   const float inv_n = 1.f / float(N);
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   const int items = a.K * a.groups;
-  for (int it = blockIdx.x; it < items; it += gridDim.x) {
-    const int k = it / a.groups, g = it - k * a.groups;
+  for (int j = xcd_rank(blockIdx.x, gridDim.x); j < items; j += gridDim.x) {
+    const int it = split_item(a, j), k = it / a.groups, g = it - k * a.groups;
     const int m0 = g * a.group_modes, m1 = min(a.M, m0 + a.group_modes);
-    const PosInfo p = parse_position(a.pos, k, N, a.H, a.W, want_pos);
+    const PosInfo p = wave_position(a.pos, k, N, a.H, a.W, want_pos);
     if (!p.ok) continue;  // the loss launch drops the position
     __syncthreads();      // the previous item is done with the weights
     if (a.weights && int(threadIdx.x) < a.E) sh.wsh[threadIdx.x] = a.weights[size_t(k) * a.E + threadIdx.x];
@@ -67,6 +95,7 @@ __global__ __launch_bounds__(T) void split_forward_kernel(CallArgs a) {
       F::forward(v, sh.lds, sh.tws, inv_n);
 #pragma unroll
       for (int i = 0; i < E; ++i) cf[i] += cabs2(v[i]);
+      if (a.far) store_pairs<E, T>(a.far + (size_t(k) * a.M + m) * C::NN, v);
     }
     float* dst = a.ipart + size_t(it) * C::NN;
     const int t = opaque_tid();
@@ -162,8 +191,8 @@ __global__ __launch_bounds__(T) void split_adjoint_kernel(CallArgs a) {
   float2* scr = a.scratch + size_t(blockIdx.x) * a.scratch_stride;
   const BufFrame sb(scr, uint32_t(a.scratch_stride * sizeof(float2)));
   const int items = a.K * a.groups;
-  for (int it = blockIdx.x; it < items; it += gridDim.x) {
-    const int k = it / a.groups, g = it - k * a.groups;
+  for (int j = xcd_rank(blockIdx.x, gridDim.x); j < items; j += gridDim.x) {
+    const int it = split_item(a, j), k = it / a.groups, g = it - k * a.groups;
     const int m0 = g * a.group_modes, m1 = min(a.M, m0 + a.group_modes);
     if (!a.kvalid[k]) {
       const int tid = threadIdx.x;
@@ -177,7 +206,7 @@ __global__ __launch_bounds__(T) void split_adjoint_kernel(CallArgs a) {
       if (a.w_part && tid < a.E) a.w_part[size_t(it) * a.E + tid] = 0.0;
       continue;
     }
-    const PosInfo p = parse_position(a.pos, k, N, a.H, a.W, want_pos);
+    const PosInfo p = wave_position(a.pos, k, N, a.H, a.W, want_pos);
     __syncthreads();  // the previous item is done with LDS, weights and sums
     if (a.weights && int(threadIdx.x) < a.E) sh.wsh[threadIdx.x] = a.weights[size_t(k) * a.E + threadIdx.x];
     for (int i = threadIdx.x; i < MAX_EIG * (T / WAVE); i += T) sh.wacc[i] = 0.0;
@@ -195,11 +224,7 @@ __global__ __launch_bounds__(T) void split_adjoint_kernel(CallArgs a) {
     const float* cfr = a.cfr + size_t(k) * C::NN;
     float2 v[E];
     for (int m = m0; m < m1; ++m) {
-      {
-        const int t = opaque_tid();
-        for_probe<N, T>(a, wk, m, t, [&](int i, float2 P) { v[i] = cmul(P, o[i]); });
-      }
-      F::forward(v, lds, sh.tws, inv_n);
+      load_pairs<E, T>(a.far + (size_t(k) * a.M + m) * C::NN, v);
       {
         const int t = opaque_tid();
 #pragma unroll
@@ -253,56 +278,59 @@ __global__ __launch_bounds__(T) void split_forward_lds_kernel(CallArgs a) {
   using F = FrameLds<N, T>;
   constexpr int EL = F::EL, NN = N * N, N1 = F::N1;
   __shared__ LdsShared<N, T> sh;
-  for (int i = threadIdx.x; i < N; i += T) sh.tws[i] = a.tw[i];
-  const float inv_n = 1.f / float(N);
+  F::load_twiddles(sh.tws, a.tw);
+  const float inv_nn = 1.f / float(N * N);
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   const BufFrame pb(a.probe, uint32_t(size_t(a.E) * a.M * NN * sizeof(float2)));
   const int items = a.K * a.groups;
-  for (int it = blockIdx.x; it < items; it += gridDim.x) {
-    const int k = it / a.groups, g = it - k * a.groups;
+  for (int j = xcd_rank(blockIdx.x, gridDim.x); j < items; j += gridDim.x) {
+    const int it = split_item(a, j), k = it / a.groups, g = it - k * a.groups;
     const int m0 = g * a.group_modes, m1 = min(a.M, m0 + a.group_modes);
-    const PosInfo p = parse_position(a.pos, k, N, a.H, a.W, want_pos);
+    const PosInfo p = wave_position(a.pos, k, N, a.H, a.W, want_pos);
     if (!p.ok) continue;  // the loss launch drops the position
-    __syncthreads();      // the previous item is done with the weights and the LDS
-    if (a.weights && int(threadIdx.x) < a.E) sh.wsh[threadIdx.x] = a.weights[size_t(k) * a.E + threadIdx.x];
+    __syncthreads();      // the previous item is done with LDS and the weights
+    if (int(threadIdx.x) < a.E) sh.wsh[threadIdx.x] = a.weights ? a.weights[size_t(k) * a.E + threadIdx.x] : 1.f;
     __syncthreads();
-    const float* wk = a.weights ? sh.wsh : nullptr;
+    const PatchWindow pw(a.obj, a.W, N, p);
     const int t = opaque_tid();
-    const int vp = ((t / N1) * N + t % N1) * 8;
+    const int vo = ((t / N1) * a.W + t % N1) * 8;
     float2 o[EL];
 #pragma unroll
-    for (int i = 0; i < EL; ++i) o[i] = bilinear(a.obj, a.W, p, t / N1, t % N1 + N1 * i);
+    for (int i = 0; i < EL; ++i) {
+      o[i] = pw.at(vo + 8 * N1 * i);
+      pin(o[i]);
+      if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
     float cf[EL];
 #pragma unroll
     for (int e = 0; e < EL; ++e) cf[e] = 0.f;
     for (int m = m0; m < m1; ++m) {
       float2 u[EL];
 #pragma unroll
-      for (int i = 0; i < EL; ++i) {
-        float2 P;
-        if (wk == nullptr) {
-          P = pb.ld(vp, (m * NN + N1 * i) * 8);
-        } else {
-          P = make_float2(0.f, 0.f);
-          for (int e = 0; e < a.E; ++e) {
-            const float2 q = pb.ld(vp, ((e * a.M + m) * NN + N1 * i) * 8);
-            P.x = fmaf(wk[e], q.x, P.x);
-            P.y = fmaf(wk[e], q.y, P.y);
-          }
-        }
-        u[i] = cmul(P, o[i]);
-      }
-      F::template rows_from<false>(sh.lds, sh.tws, 1.f, u);
-      __syncthreads();
-      float2 v[EL];
-      F::cols_to_regs(sh.lds, sh.tws, inv_n, v);
+      for (int i = 0; i < EL; ++i) u[i] = make_float2(0.f, 0.f);
+      for (int e = 0; e < a.E; ++e) {
+        const int vp = ((opaque_tid() / N1) * N + t % N1) * 8;
+        const float w = sh.wsh[e];
 #pragma unroll
-      for (int e = 0; e < EL; ++e) cf[e] += cabs2(v[e]);
+        for (int i = 0; i < EL; ++i) {
+          const float2 q = pb.ld(vp + 8 * N1 * i, (e * a.M + m) * NN * 8);
+          u[i].x = fmaf(w, q.x, u[i].x);
+          u[i].y = fmaf(w, q.y, u[i].y);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < EL; ++i) u[i] = cmul(u[i], o[i]);
+      F::template rows_from<false>(sh.lds, sh.tws, u);
+      __syncthreads();
+      F::cols_to_regs(sh.lds, sh.tws, u);
+#pragma unroll
+      for (int e = 0; e < EL; ++e) cf[e] = fmaf(u[e].x, u[e].x, fmaf(u[e].y, u[e].y, cf[e]));
+      if (a.far) store_pairs<EL, T>(a.far + (size_t(k) * a.M + m) * NN, u);
       __syncthreads();  // column phase done before the next exit wave
     }
     float* dst = a.ipart + size_t(it) * NN;
 #pragma unroll
-    for (int e = 0; e < EL; ++e) dst[size_t(e) * T + t] = cf[e];
+    for (int e = 0; e < EL; ++e) dst[size_t(e) * T + t] = cf[e] * inv_nn;
   }
 }
 
@@ -312,14 +340,14 @@ __global__ __launch_bounds__(T) void split_adjoint_lds_kernel(CallArgs a) {
   constexpr int EL = F::EL, NN = N * N, N1 = F::N1, P = F::P;
   __shared__ LdsShared<N, T> sh;
   float2* lds = sh.lds;
-  for (int i = threadIdx.x; i < N; i += T) sh.tws[i] = a.tw[i];
-  const float inv_n = 1.f / float(N);
+  F::load_twiddles(sh.tws, a.tw);
+  const float inv_nn = 1.f / float(N * N);
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
-  const bool want_probe = (a.want & WANT_PROBE) != 0;
+  const bool want_w = (a.want & WANT_WEIGHTS) && a.weights;
   const BufFrame pb(a.probe, uint32_t(size_t(a.E) * a.M * NN * sizeof(float2)));
   const int items = a.K * a.groups;
-  for (int it = blockIdx.x; it < items; it += gridDim.x) {
-    const int k = it / a.groups, g = it - k * a.groups;
+  for (int j = xcd_rank(blockIdx.x, gridDim.x); j < items; j += gridDim.x) {
+    const int it = split_item(a, j), k = it / a.groups, g = it - k * a.groups;
     const int m0 = g * a.group_modes, m1 = min(a.M, m0 + a.group_modes);
     if (!a.kvalid[k]) {
       const int tid = threadIdx.x;
@@ -333,108 +361,91 @@ __global__ __launch_bounds__(T) void split_adjoint_lds_kernel(CallArgs a) {
       if (a.w_part && tid < a.E) a.w_part[size_t(it) * a.E + tid] = 0.0;
       continue;
     }
-    const PosInfo p = parse_position(a.pos, k, N, a.H, a.W, want_pos);
+    const PosInfo p = wave_position(a.pos, k, N, a.H, a.W, want_pos);
     __syncthreads();  // the previous item is done with LDS, weights and sums
-    if (a.weights && int(threadIdx.x) < a.E) sh.wsh[threadIdx.x] = a.weights[size_t(k) * a.E + threadIdx.x];
+    if (int(threadIdx.x) < a.E) sh.wsh[threadIdx.x] = a.weights ? a.weights[size_t(k) * a.E + threadIdx.x] : 1.f;
     for (int i = threadIdx.x; i < MAX_EIG * (T / WAVE); i += T) sh.wacc[i] = 0.0;
     __syncthreads();
-    // the item's modes, with the weighted (OPR) and unweighted probe loops as separate
-    // instantiations
-    auto item = [&](auto wc) {
-      constexpr bool WT = decltype(wc)::value;
-      const float* wk = WT ? sh.wsh : nullptr;
-      const int t = opaque_tid();
-      const int vp = ((t / N1) * N + t % N1) * 8;
-      auto probe_r = [&](int m, int i) -> float2 {
-        if constexpr (!WT) return pb.ld(vp, (m * NN + N1 * i) * 8);
-        float2 P = make_float2(0.f, 0.f);
+    const PatchWindow pw(a.obj, a.W, N, p);
+    const BufFrame cb(a.cfr + size_t(k) * NN, uint32_t(NN * sizeof(float)));  // cfr of position k
+    const int t = opaque_tid();
+    const int vo = ((t / N1) * a.W + t % N1) * 8;
+    float2 o[EL], go[EL];
+#pragma unroll
+    for (int i = 0; i < EL; ++i) {
+      o[i] = pw.at(vo + 8 * N1 * i);
+      pin(o[i]);
+      go[i] = make_float2(0.f, 0.f);
+      if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    for (int m = m0; m < m1; ++m) {
+      {
+        float2 v[EL], u[EL];
+        load_pairs<EL, T>(a.far + (size_t(k) * a.M + m) * NN, v);
+        const int t4 = opaque_tid() * 4;
+#pragma unroll
+        for (int n2 = 0; n2 < EL; ++n2) {
+          const int e = F::reg_of(n2);
+          u[n2] = cscale(v[e], inv_nn * cb.ldf(t4, e * T * 4));
+        }
+        if (m > m0) __syncthreads();  // the previous mode's rows are done
+        F::template cols_from<true>(lds, sh.tws, u);
+      }
+      __syncthreads();
+      F::template rows<true>(lds, sh.tws);
+      // element pass, four pixels at a time: the staged probe-wave gradient conj(o) g_m (natural
+      // pixel order), the running patch gradient conj(P_m) g_m; then the OPR weight terms
+      const int t2 = opaque_tid();
+      const int vp = ((t2 / N1) * N + t2 % N1) * 8;
+      const float2* c0 = lds + (t2 / N1) * P + t2 % N1;
+      const BufFrame st(a.gpstage ? a.gpstage + (size_t(k) * a.M + m) * NN : a.far, a.gpstage ? NN * 8 : 0);
+#pragma unroll
+      for (int i0 = 0; i0 < EL; i0 += 4) {
+        float2 gm[4], Pm[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          gm[u] = c0[N1 * (i0 + u)];
+          Pm[u] = make_float2(0.f, 0.f);
+        }
         for (int e = 0; e < a.E; ++e) {
-          const float2 q = pb.ld(vp, ((e * a.M + m) * NN + N1 * i) * 8);
-          P.x = fmaf(wk[e], q.x, P.x);
-          P.y = fmaf(wk[e], q.y, P.y);
-        }
-        return P;
-      };
-      float2 o[EL];
+          const float w = sh.wsh[e];
 #pragma unroll
-      for (int i = 0; i < EL; ++i) o[i] = bilinear(a.obj, a.W, p, t / N1, t % N1 + N1 * i);
-      const BufFrame cb(a.cfr + size_t(k) * NN, uint32_t(NN * sizeof(float)));  // cfr of position k
-      float2 go[EL];
-      for (int m = m0; m < m1; ++m) {
-        {
-          float2 u[EL];
+          for (int u = 0; u < 4; ++u) {
+            const float2 q = pb.ld(vp + 8 * N1 * (i0 + u), (e * a.M + m) * NN * 8);
+            Pm[u].x = fmaf(w, q.x, Pm[u].x);
+            Pm[u].y = fmaf(w, q.y, Pm[u].y);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          go[i0 + u] = cmulc_add(Pm[u], gm[u], go[i0 + u]);
+          pin(go[i0 + u]);
+          st.st(cmulc(o[i0 + u], gm[u]), vp + 8 * N1 * (i0 + u), 0);  // (no room without staging: dropped)
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (want_w) {
+        for (int e = 0; e < a.E; ++e) {
+          float sf = 0.f;
 #pragma unroll
           for (int i = 0; i < EL; ++i) {
-            u[i] = cmul(probe_r(m, i), o[i]);
+            sf += cdotre(cmulc(o[i], c0[N1 * i]), pb.ld(vp + 8 * N1 * i, (e * a.M + m) * NN * 8));
             if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
           }
-          F::template rows_from<false>(lds, sh.tws, 1.f, u);
-        }
-        __syncthreads();
-        {
-          float2 v[EL], u[EL];
-          F::cols_to_regs(lds, sh.tws, inv_n, v);
-#pragma unroll
-          for (int n2 = 0; n2 < EL; ++n2) {
-            const int e = F::reg_of(n2);
-            u[n2] = cscale(v[e], cb.ldf(t * 4, e * T * 4));
-          }
-          F::template cols_from<true>(lds, sh.tws, 1.f, u);
-        }
-        __syncthreads();
-        F::template rows<true>(lds, sh.tws, inv_n);
-        // probe side: the staged probe-wave gradient conj(o) g_m (natural pixel order) and
-        // the OPR weight terms
-        if (want_probe && a.gpstage) {
-          float2* st = a.gpstage + (size_t(k) * a.M + m) * NN;
-#pragma unroll
-          for (int i = 0; i < EL; ++i) {
-            st[(t / N1) * N + t % N1 + N1 * i] = cmulc(o[i], lds[(t / N1) * P + t % N1 + N1 * i]);
-            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-        if (WT && (a.want & WANT_WEIGHTS)) {
-          for (int e = 0; e < a.E; ++e) {
-            float sf = 0.f;
-#pragma unroll
-            for (int i = 0; i < EL; ++i) {
-              sf += cdotre(cmulc(o[i], lds[(t / N1) * P + t % N1 + N1 * i]), pb.ld(vp, ((e * a.M + m) * NN + N1 * i) * 8));
-              if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-            }
-            const double sw = wave_sum(double(sf));
-            if ((threadIdx.x & (WAVE - 1)) == 0) sh.wacc[e * (T / WAVE) + threadIdx.x / WAVE] += sw;
-          }
-        }
-        // object side: the group's running patch gradient; the last mode's lands in the frame
-        auto pass = [&](auto first_c, auto last_c) {
-          constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
-#pragma unroll
-          for (int i = 0; i < EL; ++i) {
-            const int c = (t / N1) * P + t % N1 + N1 * i;
-            float2 gg = cmulc(probe_r(m, i), lds[c]);
-            if constexpr (!FIRST) gg = cadd(gg, go[i]);
-            if constexpr (LAST) lds[c] = gg;
-            else go[i] = gg;
-            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-          }
-        };
-        using T0 = std::false_type;
-        using T1 = std::true_type;
-        const bool first = m == m0, last = m == m1 - 1;
-        if (first) {
-          if (last) pass(T1{}, T1{});
-          else pass(T1{}, T0{});
-        } else {
-          if (last) pass(T0{}, T1{});
-          else pass(T0{}, T0{});
+          const double s = wave_sum(double(sf));
+          if ((threadIdx.x & (WAVE - 1)) == 0) sh.wacc[e * (T / WAVE) + threadIdx.x / WAVE] += s;
         }
       }
-    };
-    if (a.weights) item(std::true_type{});
-    else item(std::false_type{});
+    }
+    {
+      const int t2 = opaque_tid();
+      float2* c0 = lds + (t2 / N1) * P + t2 % N1;
+#pragma unroll
+      for (int i = 0; i < EL; ++i) c0[N1 * i] = go[i];
+    }
     __syncthreads();
     double gy = 0.0, gx = 0.0;
-    window_pass<N, T>(a, p, lds, a.obj, a.gwin ? a.gwin + size_t(it) * (N + 1) * (N + 1) : nullptr, gy, gx);
+    window_rows<N, T, P>(a, p, lds, pw.win, a.gwin ? a.gwin + size_t(it) * (N + 1) * (N + 1) : nullptr, gy, gx);
     finish_position<N, T>(a, it, gy, gx, sh.red, sh.wacc);
   }
 }

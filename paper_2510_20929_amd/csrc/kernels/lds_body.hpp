@@ -13,14 +13,24 @@
 // state is held in the layout the column pass leaves in registers, whose cells the
 // thread's inverse column pass reads; so element passes and transforms meet without
 // block barriers, and a forward + inverse pair costs two barriers (between rows and
-// columns) instead of six.
+// columns) instead of six. The transforms are unnormalised; every 1/N is a power of two and
+// is folded into dl/dI (and into the intensity once).
 //
-// Per position: gather the patch; per mode form P_m o in LDS, transform, add |Psi_m|^2;
-// loss and dl/dI; per mode from the last (whose far field is still in LDS): recompute
-// the far field, scale it by 2 dl/dI / (K_norm N^2), transform back, accumulate the
-// probe gradient conj(o) g_m (and the OPR weight terms), then the patch gradient
-// conj(P_m) g_m; the last mode's patch gradient is written into the frame, from which
-// the window pass forms the window gradient and the position gradient.
+// Per position: gather the patch; per mode form P_m o, transform, add |Psi_m|^2;
+// loss and dl/dI; per mode from the last (whose far field is still in registers): the
+// recomputed far field, scaled by 2 dl/dI / (K_norm N^2), transformed back; one
+// element pass accumulates the probe gradient conj(o) g_m and the patch gradient
+// conj(P_m) g_m (the OPR forms: the probe side and its weight terms first); the patch
+// gradient is written into the frame, from which the window pass forms the window
+// gradient and the position gradient.
+//
+// Bound by the transforms' arithmetic (VALU busy 59% at 30 modes) and the accumulator's
+// traffic. Measured at 2000 positions of 4 modes, Poisson: 0.97 ms (1.16 with scaled transforms,
+// separate probe and object passes, per-pixel window indices and 119 spilled registers); at 6732
+// positions of 30 modes 25.3 ms (28.2). Keeping the far fields of 4 modes in scratch instead of
+// recomputing them took 1.17-1.21 ms: 128 KB a mode more each way through the same memory. Eight
+// pixels at a time in the element passes took 1.03 ms (registers spilled), sixteen probe
+// loads at a time changed nothing.
 #pragma once
 #include "small_body.hpp"
 
@@ -35,26 +45,125 @@ struct LdsShared {
   double wacc[MAX_EIG * (T / WAVE)];
 };
 
+// The object window of a position: buffer over its (N + 1)^2 pixels and the tap weights (a
+// tap of zero weight re-reads the base pixel).
+struct PatchWindow {
+  BufFrame win;
+  int wdx, wdy;
+  float w00, w01, w10, w11;
+  __device__ __forceinline__ PatchWindow(const float2* slice, int W, int N, const PosInfo& p)
+      : win(slice + size_t(p.y0) * W + p.x0, uint32_t((size_t(N) * W + N + 1) * 8)),
+        wdx(p.fx > 0.f ? 8 : 0), wdy(p.fy > 0.f ? W * 8 : 0),
+        w00((1.f - p.fy) * (1.f - p.fx)), w01((1.f - p.fy) * p.fx), w10(p.fy * (1.f - p.fx)), w11(p.fy * p.fx) {}
+  // bilinear sample at byte offset `voff` of the window
+  __device__ __forceinline__ float2 at(int voff) const {
+    const float2 t00 = win.ld(voff, 0), t01 = win.ld(voff, wdx), t10 = win.ld(voff, wdy), t11 = win.ld(voff, wdy + wdx);
+    return make_float2(fmaf(w11, t11.x, fmaf(w10, t10.x, fmaf(w01, t01.x, w00 * t00.x))),
+                       fmaf(w11, t11.y, fmaf(w10, t10.y, fmaf(w01, t01.y, w00 * t00.y))));
+  }
+};
+
+// Object-window pass for one slice with whole rows per wave: LDS holds the patch gradient in
+// natural order (pitch P). A wave takes N / waves consecutive rows, a lane columns lane + 64 j;
+// the row above stays in registers, so a window pixel costs two LDS reads and no index
+// arithmetic. h = (1 - fx) g[x] + fx g[x - 1]; the window is (1 - fy) h[y] + fy h[y - 1], and
+// the position terms are its derivatives against the object (requested only with a full
+// window). Call between block barriers.
+template <int N, int T, int P>
+__device__ __forceinline__ void window_rows(const CallArgs& a, const PosInfo& p, const float2* lds,
+                                            const BufFrame& win, float2* gwin, double& gy, double& gx) {
+  constexpr int WN = N + 1, NW = T / WAVE, R = N / NW, J = N / WAVE;
+  static_assert(R * NW == N && J * WAVE == N && R < WAVE, "whole rows per wave");
+  const bool want_obj = (a.want & WANT_OBJ) && gwin != nullptr;
+  const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
+  if (!want_obj && !want_pos) return;
+  const int tid = opaque_tid();
+  const int lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+  const int y0 = wave * R;
+  const float ay = 1.f - p.fy, ax = 1.f - p.fx;
+  const float2 z = make_float2(0.f, 0.f);
+  float fy = 0.f, fx = 0.f;  // the thread's few terms in FP32, then FP64
+  float2 hp[J], dp[J];       // the row above: interpolated along x, difference along x
+  const auto row = [&](int y, float2 (&h)[J], float2 (&d)[J]) {
+    const float2* r = lds + y * P + lane;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const float2 c = r[WAVE * j];
+      float2 l = j > 0 || lane > 0 ? r[WAVE * j - (j > 0 || lane > 0 ? 1 : 0)] : z;
+      h[j].x = fmaf(p.fx, l.x, ax * c.x);
+      h[j].y = fmaf(p.fx, l.y, ax * c.y);
+      d[j] = csub(l, c);
+    }
+  };
+  const auto emit = [&](float2 h, float2 d, float2 hup, float2 dup, int y, int x) {
+    if (want_obj) {
+      const f2v_t o = {fmaf(p.fy, hup.x, ay * h.x), fmaf(p.fy, hup.y, ay * h.y)};
+      __builtin_nontemporal_store(o, reinterpret_cast<f2v_t*>(gwin + y * WN + x));
+    }
+    if (want_pos) {
+      const float2 A = win.ld(x * 8, y * a.W * 8);
+      fy += cdotre(csub(hup, h), A);
+      fx += cdotre(make_float2(fmaf(p.fy, dup.x, ay * d.x), fmaf(p.fy, dup.y, ay * d.y)), A);
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < J; ++j) hp[j] = dp[j] = z;
+  if (wave > 0) row(y0 - 1, hp, dp);
+#pragma unroll 2
+  for (int r = 0; r < R; ++r) {
+    float2 h[J], d[J];
+    row(y0 + r, h, d);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      emit(h[j], d[j], hp[j], dp[j], y0 + r, lane + WAVE * j);
+      hp[j] = h[j];
+      dp[j] = d[j];
+    }
+  }
+  if (wave == NW - 1) {  // row N
+#pragma unroll
+    for (int j = 0; j < J; ++j) emit(z, z, hp[j], dp[j], N, lane + WAVE * j);
+  }
+  // column N of the wave's rows (and of row N), one row a lane
+  if (lane < R + (wave == NW - 1 ? 1 : 0)) {
+    const int y = y0 + lane;
+    const float2 c = y < N ? lds[y * P + N - 1] : z, u = y > 0 ? lds[(y - 1) * P + N - 1] : z;
+    const float2 h = cscale(c, p.fx), hu = cscale(u, p.fx);
+    if (want_obj) {
+      const f2v_t o = {fmaf(p.fy, hu.x, ay * h.x), fmaf(p.fy, hu.y, ay * h.y)};
+      __builtin_nontemporal_store(o, reinterpret_cast<f2v_t*>(gwin + y * WN + N));
+    }
+    if (want_pos) {
+      const float2 A = win.ld((y * a.W + N) * 8, 0);
+      fy += cdotre(csub(hu, h), A);
+      fx += cdotre(make_float2(fmaf(p.fy, u.x, ay * c.x), fmaf(p.fy, u.y, ay * c.y)), A);
+    }
+  }
+  gy += double(fy);
+  gx += double(fx);
+}
+
 // CFREG: dl/dI stays in registers (variant 6); otherwise it is parked in the first half
-// frame of the workgroup's scratch between its uses (variant 5).
-template <int N, int T, int LOSS, bool CFREG>
+// frame of the workgroup's scratch between its uses (variant 5). FA: a forward + adjoint
+// call (a.mode).
+template <int N, int T, int LOSS, bool CFREG, bool FA>
 __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh, int wg, int nwg) {
   using F = FrameLds<N, T>;
   constexpr int EL = F::EL;
   constexpr int NN = N * N;
   constexpr int P = F::P;
-  static_assert(P == Frame2D<N, T>::P, "the window pass reads the frame with the on-chip pitch");
   float2* lds = sh.lds;
   float2* tws = sh.tws;
   double* red = sh.red;
   float* wsh = sh.wsh;
   double* wacc = sh.wacc;
-  const float inv_n = 1.f / float(N);
-  const bool fwd = a.mode != MODE_APPLY_AH;
-  const bool adj = a.mode == MODE_FWD_ADJ || a.mode == MODE_APPLY_AH;
-  const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
+  const float inv_n = 1.f / float(N), inv_nn = inv_n * inv_n;
+  const bool fwd = FA || a.mode != MODE_APPLY_AH;
+  const bool apply_a = !FA && a.mode == MODE_APPLY_A;
+  const bool adj = FA || !fwd;
+  const bool want_pos = FA && (a.want & WANT_POS);
   const bool want_probe = (a.want & WANT_PROBE) != 0;
-  for (int i = threadIdx.x; i < N; i += T) tws[i] = a.tw[i];
+  F::load_twiddles(tws, a.tw);
   float2* scr = a.scratch + size_t(wg) * a.scratch_stride;
   const BufFrame sb(scr, uint32_t(a.scratch_stride * sizeof(float2)));
   const int pacc_b = int(a.pacc_off * sizeof(float2));
@@ -65,33 +174,33 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
   const bool acc_lazy = adj && a.zero_acc && want_probe && !a.gpstage && (a.weights || a.E == 1);
   if (adj && a.zero_acc && want_probe && !a.gpstage && !acc_lazy) zero_probe_acc<N, T>(a, scr + a.pacc_off);
   bool acc_fresh = acc_lazy;
-  // pixel (y, x) = (t / N1, t mod N1 + N1 i) of element i of thread t: its index, its
-  // LDS cell, and the thread part of its byte offset; element loops issue four
+  // pixel (y, x) = (t / N1, t mod N1 + N1 i) of element i of thread t: the thread part of its
+  // byte offset (8 N1 i further per element), its LDS cell; element loops issue four
   // elements' loads at a time (a scheduling barrier after every fourth)
   constexpr int N1 = F::N1;
-  auto pix = [](int t, int i) { return (t / N1) * N + t % N1 + N1 * i; };
   auto cell = [](int t, int i) { return (t / N1) * P + t % N1 + N1 * i; };
   auto vpix = [](int t) { return ((t / N1) * N + t % N1) * 8; };
   auto chunk = [](int i) {
     if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
   };
   // probe reads through a buffer resource: the thread part is the vector offset and the
-  // element, mode and eigenprobe parts a scalar offset, so the unrolled loops keep no
-  // per-element address registers live across the transforms
+  // element, mode and eigenprobe parts constant and scalar offsets, so the unrolled loops
+  // keep no per-element address registers live across the transforms
   const BufFrame pb(a.probe, uint32_t(size_t(a.E) * a.M * NN * sizeof(float2)));
-  auto probe_px = [&](auto wc, const float* wk, int m, int t, int i) -> float2 {
-    if constexpr (!decltype(wc)::value) return pb.ld(vpix(t), (m * NN + N1 * i) * 8);
+  auto probe_px = [&](auto wc, const float* wk, int m, int vp, int i) -> float2 {
+    if constexpr (!decltype(wc)::value) return pb.ld(vp + 8 * N1 * i, m * NN * 8);
     float2 acc = make_float2(0.f, 0.f);
     for (int e = 0; e < a.E; ++e) {
-      const float2 u = pb.ld(vpix(t), ((e * a.M + m) * NN + N1 * i) * 8);
+      const float2 u = pb.ld(vp + 8 * N1 * i, (e * a.M + m) * NN * 8);
       acc.x = fmaf(wk[e], u.x, acc.x);
       acc.y = fmaf(wk[e], u.y, acc.y);
     }
     return acc;
   };
 
-  for (int k = wg; k < a.K; k += nwg) {
-    const PosInfo p = parse_position(a.pos, k, N, a.H, a.W, want_pos);
+  for (int it = xcd_rank(wg, nwg); it < a.K; it += nwg) {
+    const int k = opaque_scalar(it);
+    const PosInfo p = wave_position(a.pos, k, N, a.H, a.W, want_pos);
     if (!p.ok) {
       skip_position<N, T>(a, k, p);
       continue;
@@ -100,6 +209,7 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
     if (a.weights && int(threadIdx.x) < a.E) wsh[threadIdx.x] = a.weights[size_t(k) * a.E + threadIdx.x];
     for (int i = threadIdx.x; i < MAX_EIG * (T / WAVE); i += T) wacc[i] = 0.0;
     __syncthreads();
+    const PatchWindow pw(a.obj, a.W, N, p);
     // the rest of the position, with the weighted (OPR) and unweighted probe loops as
     // separate instantiations
     auto position = [&](auto wc) {
@@ -109,40 +219,41 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
     float2 o[EL];
     {
       const int t = opaque_tid();
+      const int vo = ((t / N1) * a.W + t % N1) * 8;
 #pragma unroll
       for (int i = 0; i < EL; ++i) {
-        o[i] = bilinear(a.obj, a.W, p, t / N1, t % N1 + N1 * i);
+        o[i] = pw.at(vo + 8 * N1 * i);
+        pin(o[i]);
         chunk(i);
       }
     }
     // forward row pass of the exit wave P_m o of mode m, fed from registers (element i
     // is the row pass's input n2 = i)
     auto exit_rows = [&](int m) {
-      const int t = opaque_tid();
+      const int vp = vpix(opaque_tid());
       float2 u[EL];
 #pragma unroll
       for (int i = 0; i < EL; ++i) {
-        u[i] = cmul(probe_px(wc, wk, m, t, i), o[i]);
+        u[i] = cmul(probe_px(wc, wk, m, vp, i), o[i]);
         chunk(i);
       }
-      F::template rows_from<false>(lds, tws, 1.f, u);
+      F::template rows_from<false>(lds, tws, u);
     };
 
     // frequency-domain state (intensity, dl/dI, far fields) in the layout the forward
     // transform leaves in registers: element e of thread t is frequency (row(t, e), col(t))
     auto fpix = [](int t, int e) { return F::row(t, e) * N + F::col(t); };
     float cf[EL];
-    // inverse column pass of the far field v (registers), scaled by 2 dl/dI / (K_norm N^2)
+    // inverse column pass of the far field v (registers), scaled by dl/dI and its constants
     auto scaled_cols = [&](const float2 (&v)[EL]) {
-      const int t = opaque_tid();
+      const int t4 = opaque_tid() * 4;
       float2 u[EL];
 #pragma unroll
       for (int n2 = 0; n2 < EL; ++n2) {
         const int e = F::reg_of(n2);
-        const float c = CFREG ? cf[e] : sb.ldf(t * 4, e * T * 4);
-        u[n2] = cscale(v[e], a.gscale * c);
+        u[n2] = cscale(v[e], CFREG ? cf[e] : sb.ldf(t4, e * T * 4));
       }
-      F::template cols_from<true>(lds, tws, 1.f, u);
+      F::template cols_from<true>(lds, tws, u);
     };
     if (fwd) {
       float2 v[EL];
@@ -151,16 +262,17 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
       for (int m = 0; m < a.M; ++m) {
         exit_rows(m);
         __syncthreads();
-        F::cols_to_regs(lds, tws, inv_n, v);
-        const int t = opaque_tid();
+        F::cols_to_regs(lds, tws, v);
 #pragma unroll
-        for (int e = 0; e < EL; ++e) {
-          cf[e] += cabs2(v[e]);
-          if (a.mode == MODE_APPLY_A) a.psi_out[(size_t(k) * a.M + m) * NN + fpix(t, e)] = v[e];
+        for (int e = 0; e < EL; ++e) cf[e] = fmaf(v[e].x, v[e].x, fmaf(v[e].y, v[e].y, cf[e]));
+        if (apply_a) {
+          const int t = opaque_tid();
+#pragma unroll
+          for (int e = 0; e < EL; ++e) a.psi_out[(size_t(k) * a.M + m) * NN + fpix(t, e)] = cscale(v[e], inv_n);
         }
         if (m < a.M - 1) __syncthreads();  // column phase done before the next exit wave
       }
-      if (a.mode == MODE_APPLY_A) return;
+      if (apply_a) return;
       // loss and dl/dI (detector DC-centred)
       {
         const int t = opaque_tid();
@@ -168,6 +280,8 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
         float imv[EL];
 #pragma unroll
         for (int e = 0; e < EL; ++e) imv[e] = __builtin_nontemporal_load(im + centred_index(F::row(t, e), F::col(t), N));
+#pragma unroll
+        for (int e = 0; e < EL; ++e) cf[e] *= inv_nn;
         if (a.ipred) {
           float* ip = a.ipred + size_t(k) * NN;
 #pragma unroll
@@ -179,7 +293,8 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
           float l, c;
           loss_terms<LOSS>(cf[e], imv[e], a.eps, l, c);
           lsum += double(l);
-          cf[e] = c;
+          cf[e] = a.gscale * inv_nn * c;
+          chunk(e);
         }
         const double tot = block_sum<T>(lsum, red);
         const bool fin = isfinite(tot);
@@ -199,20 +314,22 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
           return;
         }
       }
-      if (a.mode == MODE_FORWARD) return;
+      if (!FA) return;
       if constexpr (!CFREG) {
-        const int t = opaque_tid();
+        const int t4 = opaque_tid() * 4;
 #pragma unroll
-        for (int e = 0; e < EL; ++e) sb.stf(cf[e], t * 4, e * T * 4);
+        for (int e = 0; e < EL; ++e) sb.stf(cf[e], t4, e * T * 4);
       }
       scaled_cols(v);  // the first adjoint step's inverse column pass (the last mode)
     }
 
     // adjoint, last mode first (its inverse column pass is done)
     float2 go[EL];
+#pragma unroll
+    for (int i = 0; i < EL; ++i) go[i] = make_float2(0.f, 0.f);
     for (int mm = 0; mm < a.M; ++mm) {
       const int m = a.M - 1 - mm;
-      const bool first = mm == 0, last = mm == a.M - 1;
+      const bool first = mm == 0;
       // inverse transform: columns (from registers), rows
       if (!fwd) {
         // the given far field, read in the order of the thread's inverse column pass
@@ -221,95 +338,114 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
         const float2* y = a.Y + (size_t(k) * a.M + m) * NN;
         float2 u[EL];
 #pragma unroll
-        for (int n2 = 0; n2 < EL; ++n2) u[n2] = y[fpix(t, F::reg_of(n2))];
-        F::template cols_from<true>(lds, tws, 1.f, u);
+        for (int n2 = 0; n2 < EL; ++n2) u[n2] = cscale(y[fpix(t, F::reg_of(n2))], inv_n);
+        F::template cols_from<true>(lds, tws, u);
       } else if (!first) {
         float2 v[EL];
         exit_rows(m);
         __syncthreads();
-        F::cols_to_regs(lds, tws, inv_n, v);
+        F::cols_to_regs(lds, tws, v);
         scaled_cols(v);
       }
       __syncthreads();
-      F::template rows<true>(lds, tws, inv_n);
+      F::template rows<true>(lds, tws);
       const int t = opaque_tid();
-      using T0 = std::false_type;
-      using T1 = std::true_type;
-      {
+      const int vp = vpix(t);
+      const float2* c0 = lds + cell(t, 0);
+      if constexpr (WT) {
         // probe side: conj(o) g_m into each eigenprobe's accumulator (or the staging
-        // frame), and the OPR weight terms (separate passes from the object side: one
-        // fused pass needs more registers than the transforms leave)
+        // frame), and the OPR weight terms
         if (want_probe && a.gpstage) {
-          float2* st = a.gpstage + (size_t(k) * a.M + m) * NN;
+          const BufFrame st(a.gpstage + (size_t(k) * a.M + m) * NN, NN * 8);
 #pragma unroll
           for (int i = 0; i < EL; ++i) {
-            st[pix(t, i)] = cmulc(o[i], lds[cell(t, i)]);
+            st.st(cmulc(o[i], c0[N1 * i]), vp + 8 * N1 * i, 0);
             chunk(i);
           }
         } else if (want_probe) {
-          for (int e = 0; e < (WT ? a.E : 1); ++e) {
+          for (int e = 0; e < a.E; ++e) {
             const int fb = pacc_b + (e * a.M + m) * NN * 8;
-            const float w = WT ? wk[e] : 1.f;
+            const float w = wk[e];
 #pragma unroll
             for (int i0 = 0; i0 < EL; i0 += 4) {
               float2 g[4];
-              if (acc_fresh) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) g[u] = make_float2(0.f, 0.f);
-              } else {
+              for (int u = 0; u < 4; ++u) g[u] = make_float2(0.f, 0.f);
+              if (!acc_fresh) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) g[u] = sb.ld(vpix(t), fb + N1 * (i0 + u) * 8);
+                for (int u = 0; u < 4; ++u) g[u] = sb.ld(vp + 8 * N1 * (i0 + u), fb);
               }
 #pragma unroll
               for (int u = 0; u < 4; ++u) {
-                const float2 gp = cmulc(o[i0 + u], lds[cell(t, i0 + u)]);
+                const float2 gp = cmulc(o[i0 + u], c0[N1 * (i0 + u)]);
                 g[u].x = fmaf(w, gp.x, g[u].x);
                 g[u].y = fmaf(w, gp.y, g[u].y);
-                sb.st(g[u], vpix(t), fb + N1 * (i0 + u) * 8);
+                sb.st(g[u], vp + 8 * N1 * (i0 + u), fb);
               }
               __builtin_amdgcn_sched_barrier(0);
             }
           }
         }
-        if (WT && (a.want & WANT_WEIGHTS)) {
+        if (a.want & WANT_WEIGHTS) {
           for (int e = 0; e < a.E; ++e) {
             float sf = 0.f;
 #pragma unroll
             for (int i = 0; i < EL; ++i) {
-              sf += cdotre(cmulc(o[i], lds[cell(t, i)]), pb.ld(vpix(t), ((e * a.M + m) * NN + N1 * i) * 8));
+              sf += cdotre(cmulc(o[i], c0[N1 * i]), pb.ld(vp + 8 * N1 * i, (e * a.M + m) * NN * 8));
               chunk(i);
             }
             const double s = wave_sum(double(sf));
             if ((threadIdx.x & (WAVE - 1)) == 0) wacc[e * (T / WAVE) + threadIdx.x / WAVE] += s;
           }
         }
-        // object side: the running patch gradient; the last mode's lands in the frame
-        auto pass = [&](auto first_c, auto last_c) {
-          constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
+        // object side: the running patch gradient
 #pragma unroll
-          for (int i = 0; i < EL; ++i) {
-            const float2 P = probe_px(wc, wk, m, t, i);
-            float2 g = cmulc(P, lds[cell(t, i)]);
-            if constexpr (!FIRST) g = cadd(g, go[i]);
-            if constexpr (LAST) lds[cell(t, i)] = g;
-            else go[i] = g;
-            chunk(i);
+        for (int i = 0; i < EL; ++i) {
+          go[i] = cmulc_add(probe_px(wc, wk, m, vp, i), c0[N1 * i], go[i]);
+          pin(go[i]);
+          chunk(i);
+        }
+      } else {
+        // both sides, four pixels at a time: conj(o) g_m into the accumulator (or the
+        // staging frame), conj(P_m) g_m into the running patch gradient
+        const BufFrame st(a.gpstage ? a.gpstage + (size_t(k) * a.M + m) * NN : scr + a.pacc_off + size_t(m) * NN,
+                          NN * 8);
+        const bool read = !a.gpstage && !acc_fresh;
+#pragma unroll
+        for (int i0 = 0; i0 < EL; i0 += 4) {
+          float2 g[4], Pm[4], acc[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            Pm[u] = pb.ld(vp + 8 * N1 * (i0 + u), m * NN * 8);
+            acc[u] = make_float2(0.f, 0.f);
+            g[u] = c0[N1 * (i0 + u)];
           }
-        };
-        if (first) {
-          if (last) pass(T1{}, T1{});
-          else pass(T1{}, T0{});
-        } else {
-          if (last) pass(T0{}, T1{});
-          else pass(T0{}, T0{});
+          if (want_probe && read) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc[u] = st.ld(vp + 8 * N1 * (i0 + u), 0);
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            go[i0 + u] = cmulc_add(Pm[u], g[u], go[i0 + u]);
+            pin(go[i0 + u]);
+          }
+          if (want_probe) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) st.st(cmulc_add(o[i0 + u], g[u], acc[u]), vp + 8 * N1 * (i0 + u), 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
-
+    {
+      float2* c0 = lds + cell(opaque_tid(), 0);
+#pragma unroll
+      for (int i = 0; i < EL; ++i) c0[N1 * i] = go[i];
+    }
     acc_fresh = false;  // every accumulator frame holds this position's terms now
     __syncthreads();
     double gy = 0.0, gx = 0.0;
-    window_pass<N, T>(a, p, lds, a.obj, a.gwin ? a.gwin + size_t(k) * (N + 1) * (N + 1) : nullptr, gy, gx);
+    window_rows<N, T, P>(a, p, lds, pw.win, a.gwin ? a.gwin + size_t(k) * (N + 1) * (N + 1) : nullptr, gy, gx);
     finish_position<N, T>(a, k, gy, gx, red, wacc);
     };
     if (a.weights) position(std::true_type{});
