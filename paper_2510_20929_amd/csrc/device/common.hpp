@@ -146,23 +146,6 @@ struct Twiddle {
   static constexpr float im = INV ? float(ct_sin(ang)) : float(-ct_sin(ang));
 };
 
-// multiply by the constant twiddle W_R^J, with the trivial angles special-cased
-template <int R, int J, bool INV>
-__device__ __forceinline__ float2 twiddle_const(float2 a) {
-  constexpr int j = J % R;
-  if constexpr (j == 0) {
-    return a;
-  } else if constexpr (4 * j == R) {
-    return mul_mi<INV>(a);
-  } else if constexpr (2 * j == R) {
-    return make_float2(-a.x, -a.y);
-  } else if constexpr (4 * j == 3 * R) {
-    return mul_mi<!INV>(a);
-  } else {
-    return cmul(a, make_float2(Twiddle<R, J, INV>::re, Twiddle<R, J, INV>::im));
-  }
-}
-
 // ----------------------------------------------------------------------------- atomics
 // Hardware float add at device scope (the buffers are ordinary device allocations).
 __device__ __forceinline__ void atomic_add_f32(float* p, float v) {

@@ -3,9 +3,9 @@
 // A length-N transform is split as N = N1 * N2 (N1 <= N2): with input index
 // n = n1 + N1 n2 and output index k = k2 + N2 k1,
 //   X[k2 + N2 k1] = sum_n1 W_N^{n1 k2} W_N1^{n1 k1} sum_n2 x[n1 + N1 n2] W_N2^{n2 k2},
-// i.e. N1 register DFTs of size N2, a twiddle W_N^{n1 k2}, then N2 register DFTs of
-// size N1. The two register stages exchange data through LDS. A 2D N x N transform
-// runs that over the rows and then over the columns (4 register stages, 3 LDS
+// i.e. N1 register DFTs of size N2, then N2 register DFTs of size N1 whose butterflies
+// carry the twiddles W_N^{n1 k2}. The two register stages exchange data through LDS. A 2D
+// N x N transform runs that over the rows and then over the columns (4 register stages, 3 LDS
 // exchanges). The inverse runs the adjoint stages in reverse order, so a forward
 // transform leaves each thread holding exactly the frequencies its inverse needs,
 // and the inverse returns every pixel to the thread that supplied it.
@@ -18,73 +18,95 @@
 namespace ptyhip {
 
 // ----------------------------------------------------------------------------- register DFTs
-template <int R, bool INV>
-struct Dft;
-
+// Radix-2 decimation in time, unrolled, in natural order. A butterfly a +- w b costs six
+// fused operations: s = a + w b (four), a - w b = 2 a - s (two); w = 1 and -i cost four
+// additions.
 template <bool INV>
-struct Dft<1, INV> {
-  __device__ __forceinline__ static void run(float2*) {}
-};
-
-template <bool INV>
-struct Dft<2, INV> {
-  __device__ __forceinline__ static void run(float2* v) {
-    float2 a = v[0], b = v[1];
-    v[0] = cadd(a, b);
-    v[1] = csub(a, b);
+__device__ __forceinline__ void butterfly(float2 a, float2 b, float2 w, float2& s, float2& d) {
+  if constexpr (INV) {  // a +- conj(w) b
+    s.x = fmaf(b.x, w.x, fmaf(b.y, w.y, a.x));
+    s.y = fmaf(b.y, w.x, fmaf(-b.x, w.y, a.y));
+  } else {
+    s.x = fmaf(b.x, w.x, fmaf(-b.y, w.y, a.x));
+    s.y = fmaf(b.y, w.x, fmaf(b.x, w.y, a.y));
   }
-};
-
-template <bool INV>
-struct Dft<4, INV> {
-  __device__ __forceinline__ static void run(float2* v) {
-    float2 s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
-    float2 s13 = cadd(v[1], v[3]), d13 = mul_mi<INV>(csub(v[1], v[3]));
-    v[0] = cadd(s02, s13);
-    v[2] = csub(s02, s13);
-    v[1] = cadd(d02, d13);
-    v[3] = csub(d02, d13);
-  }
-};
-
-// Cooley-Tukey split R = A * B with constant twiddles (register renaming only).
-template <int A, int B, bool INV>
-__device__ __forceinline__ void dft_split(float2* v) {
-  constexpr int R = A * B;
-  float2 t[R];
-  static_for<0, A>([&](auto n1c) {
-    constexpr int n1 = decltype(n1c)::value;
-    float2 u[B];
-#pragma unroll
-    for (int n2 = 0; n2 < B; ++n2) u[n2] = v[n1 + A * n2];
-    Dft<B, INV>::run(u);
-    static_for<0, B>([&](auto k2c) {
-      constexpr int k2 = decltype(k2c)::value;
-      t[n1 * B + k2] = twiddle_const<R, n1 * k2, INV>(u[k2]);
-    });
-  });
-#pragma unroll
-  for (int k2 = 0; k2 < B; ++k2) {
-    float2 u[A];
-#pragma unroll
-    for (int n1 = 0; n1 < A; ++n1) u[n1] = t[n1 * B + k2];
-    Dft<A, INV>::run(u);
-#pragma unroll
-    for (int k1 = 0; k1 < A; ++k1) v[k2 + B * k1] = u[k1];
-  }
+  d.x = fmaf(2.f, a.x, -s.x);
+  d.y = fmaf(2.f, a.y, -s.y);
 }
 
-template <bool INV>
-struct Dft<8, INV> {
-  __device__ __forceinline__ static void run(float2* v) { dft_split<2, 4, INV>(v); }
+// DFT of size R of v (exp(-2 pi i k n / R), or its conjugate)
+template <int R, bool INV>
+struct Dft {
+  __device__ __forceinline__ static void run(float2* v) {
+    if constexpr (R > 1) {
+      constexpr int H = R / 2;
+      float2 e[H], o[H];
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        e[i] = v[2 * i];
+        o[i] = v[2 * i + 1];
+      }
+      Dft<H, INV>::run(e);
+      Dft<H, INV>::run(o);
+      static_for<0, H>([&](auto kc) {
+        constexpr int k = decltype(kc)::value;
+        if constexpr (k == 0) {
+          v[0] = cadd(e[0], o[0]);
+          v[H] = csub(e[0], o[0]);
+        } else if constexpr (4 * k == R) {
+          const float2 t = mul_mi<INV>(o[k]);
+          v[k] = cadd(e[k], t);
+          v[k + H] = csub(e[k], t);
+        } else {
+          butterfly<false>(e[k], o[k], make_float2(Twiddle<R, k, INV>::re, Twiddle<R, k, INV>::im), v[k], v[k + H]);
+        }
+      });
+    }
+  }
 };
-template <bool INV>
-struct Dft<16, INV> {
-  __device__ __forceinline__ static void run(float2* v) { dft_split<4, 4, INV>(v); }
-};
-template <bool INV>
-struct Dft<32, INV> {
-  __device__ __forceinline__ static void run(float2* v) { dft_split<4, 8, INV>(v); }
+
+// DFT of size R of v[n] w^n with w = W_N^p (p < N / R), the second factor of a transform of
+// size N: the twiddles go into the butterflies, whose factors at size L are w^(R / L) W_L^k,
+// k < L / 4 (the other quarter has -i times the same). That is R / 2 table entries and no
+// multiplication of its own instead of R - 1 of each (128^2, 6732 positions x 30 modes:
+// 25.75 -> 24.09 ms together with the fused radix-2 butterflies; 8 slices x 1500 positions:
+// 6.52 -> 5.95 ms). Table (load_twiddles): factor j of
+// every p consecutive, so that a lane's entries are at constant distances.
+template <int R, int N, bool INV>
+struct TwiddledDft {
+  static constexpr int PITCH = N / R;
+  float2 c[R / 2];  // size 2: c[0]; size L: c[L / 4 + k]
+  __device__ __forceinline__ TwiddledDft(const float2* tab, int p) {
+#pragma unroll
+    for (int j = 0; j < R / 2; ++j) c[j] = tab[j * PITCH + p];
+  }
+  // W_N's exponent of factor j
+  __device__ __forceinline__ static int exponent(int j, int p) {
+    if (j == 0) return (R / 2) * p;
+    const int lg = 31 - __builtin_clz(j);  // j = L / 4 + k
+    return ((R / 4) >> lg) * p + (j - (1 << lg)) * ((N / 4) >> lg);
+  }
+  template <int L = R>
+  __device__ __forceinline__ void run(float2* v) const {
+    if constexpr (L == 2) {
+      butterfly<INV>(v[0], v[1], c[0], v[0], v[1]);
+    } else {
+      constexpr int H = L / 2, Q = L / 4;
+      float2 e[H], o[H];
+#pragma unroll
+      for (int i = 0; i < H; ++i) {
+        e[i] = v[2 * i];
+        o[i] = v[2 * i + 1];
+      }
+      run<H>(e);
+      run<H>(o);
+#pragma unroll
+      for (int k = 0; k < Q; ++k) {
+        butterfly<INV>(e[k], o[k], c[Q + k], v[k], v[k + H]);
+        butterfly<INV>(e[k + Q], mul_mi<INV>(o[k + Q]), c[Q + k], v[k + Q], v[k + Q + H]);
+      }
+    }
+  }
 };
 
 // ----------------------------------------------------------------------------- factorisations
@@ -96,6 +118,17 @@ template <> struct Split<64>  { static constexpr int N1 = 8,  N2 = 8;  };
 template <> struct Split<128> { static constexpr int N1 = 8,  N2 = 16; };
 template <> struct Split<256> { static constexpr int N1 = 16, N2 = 16; };
 template <> struct Split<512> { static constexpr int N1 = 16, N2 = 32; };
+
+// The LDS table of a transform of N points, N entries from tw (W_N^j): the factors of its
+// forward second stage (size N1), then from N / 2 those of its inverse (size N2).
+template <int N>
+__device__ __forceinline__ void load_twiddles(float2* tws, const float2* __restrict__ tw) {
+  constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2;
+  for (int i = threadIdx.x; i < N; i += blockDim.x) {
+    const int h = i % (N / 2);
+    tws[i] = tw[i < N / 2 ? TwiddledDft<N1, N, false>::exponent(h / N2, h % N2) : TwiddledDft<N2, N, true>::exponent(h / N1, h % N1)];
+  }
+}
 
 // ----------------------------------------------------------------------------- on-chip 2D frame
 // A whole N x N frame spread over T threads (N <= 128). Each thread owns E elements.
@@ -143,14 +176,12 @@ struct Frame2D {
                                                  float scale) {
     const int t = opaque_tid();
     __syncthreads();
-    // row stage 1: DFT over n2, twiddle, exchange within the wave
+    // row stage 1: DFT over n2, exchange within the wave
 #pragma unroll
     for (int l = 0; l < L; ++l) {
       const int s = t + T * l, y = s / N1, n1 = s % N1;
       float2* u = &v[l * N2];
       Dft<N2, false>::run(u);
-#pragma unroll
-      for (int k2 = 1; k2 < N2; ++k2) u[k2] = cmul(u[k2], tw[n1 * k2]);
 #pragma unroll
       for (int k2 = 0; k2 < N2; ++k2) lds[y * P + sw(n1, k2)] = u[k2];
     }
@@ -165,7 +196,7 @@ struct Frame2D {
         float2* u = &v[l * N2 + jj * N1];
 #pragma unroll
         for (int n1 = 0; n1 < N1; ++n1) u[n1] = lds[y * P + sw(n1, k2)];
-        Dft<N1, false>::run(u);
+        TwiddledDft<N1, N, false>(tw, k2).run(u);
       }
     }
     wave_fence();
@@ -178,7 +209,7 @@ struct Frame2D {
         for (int k1 = 0; k1 < N1; ++k1) lds[y * P + q + N1 * jj + N2 * k1] = v[l * N2 + jj * N1 + k1];
     }
     __syncthreads();
-    // column stage 1 (in place): thread owns column kx, residue m1; DFT over m2, twiddle
+    // column stage 1 (in place): thread owns column kx, residue m1; DFT over m2
 #pragma unroll
     for (int l = 0; l < L; ++l) {
       const int s = t + T * l, kx = s % N, m1 = s / N;
@@ -186,8 +217,6 @@ struct Frame2D {
 #pragma unroll
       for (int m2 = 0; m2 < N2; ++m2) u[m2] = lds[(m1 + N1 * m2) * P + kx];
       Dft<N2, false>::run(u);
-#pragma unroll
-      for (int l2 = 1; l2 < N2; ++l2) u[l2] = cmul(u[l2], tw[m1 * l2]);
 #pragma unroll
       for (int l2 = 0; l2 < N2; ++l2) lds[(m1 + N1 * l2) * P + kx] = u[l2];
     }
@@ -202,7 +231,7 @@ struct Frame2D {
         float2* u = &v[l * N2 + jj * N1];
 #pragma unroll
         for (int n1 = 0; n1 < N1; ++n1) u[n1] = lds[(n1 + N1 * l2) * P + kx];
-        Dft<N1, false>::run(u);
+        TwiddledDft<N1, N, false>(tw, l2).run(u);
 #pragma unroll
         for (int l1 = 0; l1 < N1; ++l1) u[l1] = cscale(u[l1], scale);
       }
@@ -236,9 +265,7 @@ struct Frame2D {
       float2 u[N2];
 #pragma unroll
       for (int l2 = 0; l2 < N2; ++l2) u[l2] = lds[(m1 + N1 * l2) * P + kx];
-#pragma unroll
-      for (int l2 = 1; l2 < N2; ++l2) u[l2] = cmul_conjb(u[l2], tw[m1 * l2]);
-      Dft<N2, true>::run(u);
+      TwiddledDft<N2, N, true>(tw + N / 2, m1).run(u);
 #pragma unroll
       for (int m2 = 0; m2 < N2; ++m2) lds[(m1 + N1 * m2) * P + kx] = u[m2];
     }
@@ -274,9 +301,7 @@ struct Frame2D {
       float2* u = &v[l * N2];
 #pragma unroll
       for (int k2 = 0; k2 < N2; ++k2) u[k2] = lds[y * P + sw(n1, k2)];
-#pragma unroll
-      for (int k2 = 1; k2 < N2; ++k2) u[k2] = cmul_conjb(u[k2], tw[n1 * k2]);
-      Dft<N2, true>::run(u);
+      TwiddledDft<N2, N, true>(tw + N / 2, n1).run(u);
 #pragma unroll
       for (int n2 = 0; n2 < N2; ++n2) u[n2] = cscale(u[n2], scale);
     }
@@ -328,8 +353,6 @@ struct LineTile {
         for (int n2 = 0; n2 < N2; ++n2) u[n2] = base[(q + N1 * n2) * ES];
         Dft<N2, false>::run(u);
 #pragma unroll
-        for (int k2 = 1; k2 < N2; ++k2) u[k2] = cmul(u[k2], tw[q * k2]);
-#pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) base[sw(q, k2) * ES] = u[k2];
       }
       __syncthreads();
@@ -343,7 +366,7 @@ struct LineTile {
           float2* u = &w[r][jj * N1];
 #pragma unroll
           for (int n1 = 0; n1 < N1; ++n1) u[n1] = base[sw(n1, k2) * ES];
-          Dft<N1, false>::run(u);
+          TwiddledDft<N1, N, false>(tw, k2).run(u);
         }
       }
       __syncthreads();
@@ -386,9 +409,7 @@ struct LineTile {
         float2 u[N2];
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) u[k2] = base[sw(q, k2) * ES];
-#pragma unroll
-        for (int k2 = 1; k2 < N2; ++k2) u[k2] = cmul_conjb(u[k2], tw[q * k2]);
-        Dft<N2, true>::run(u);
+        TwiddledDft<N2, N, true>(tw + N / 2, q).run(u);
 #pragma unroll
         for (int n2 = 0; n2 < N2; ++n2) base[(q + N1 * n2) * ES] = u[n2];
       }
@@ -399,9 +420,9 @@ struct LineTile {
 // ----------------------------------------------------------------------------- wave lines
 // 1D transforms of four lines of N = 16 N2 points by one wavefront (256 and 512 points),
 // input and output in registers. Stage 1: thread (line, n1) holds x[n1 + 16 n2] in
-// u[n2], runs a register DFT of size N2 and multiplies by W_N^{n1 k2}; the wave exchanges
-// through its own 4 N cells of LDS (no block barrier: a wave's LDS operations execute in
-// order); stage 2: thread (line, kq) runs N2 / 16 DFTs of size 16 and holds frequency
+// u[n2] and runs a register DFT of size N2; the wave exchanges through its own 4 N cells of
+// LDS (no block barrier: a wave's LDS operations execute in order); stage 2: thread
+// (line, kq) runs N2 / 16 twiddled DFTs of size 16 and holds frequency
 // kq + 16 kk in v[kk]. The inverse runs the adjoint stages in reverse order.
 // Cell of the intermediate (line, n1, k2): the XORs put the 32 lanes of a half-wave into
 // distinct 8-byte banks in both stages, for lanes that are 16 consecutive n1 (or k2) of two
@@ -410,12 +431,26 @@ template <int N>
 struct WaveLines {
   static constexpr int N1 = 16, N2 = N / 16;
   static_assert(N2 == 16 || N2 == 32, "256- and 512-point lines");
+  // Where the twiddles W_N^{n1 k2} are applied. Inside the butterflies of the second stage
+  // (8 or 16 factors of a lane live through it) at 512 threads; one by one at the exchange
+  // where a thread has 128 registers and 32 pixels (256^2: the eight factors make the loss of
+  // the forward kernel spill, 533 against 509 us over 331 positions x 3 modes).
+  static constexpr bool STAGE1 = N == 256;
+
+  // table in LDS: W_N^{n1 k2} at k2 16 + n1, or load_twiddles' table
+  __device__ __forceinline__ static void table(float2* tws, const float2* __restrict__ tw) {
+    if constexpr (STAGE1) {
+      for (int i = threadIdx.x; i < N; i += blockDim.x) tws[i] = tw[(i & 15) * (i >> 4)];
+    } else {
+      load_twiddles<N>(tws, tw);
+    }
+  }
   __device__ __forceinline__ static int cell0(int line, int i) {  // XORed with (k2, n1 ^ k2) parts
     return line * N + 16 * (line & 1) + (i ^ ((line >> 1) << 3));
   }
   __device__ __forceinline__ static void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
 
-  // `ex`: the wave's cells; `tw`: W_N^{n1 k2} at k2 16 + n1 (LDS)
+  // `ex`: the wave's cells; `tw`: the table
   __device__ __forceinline__ static void forward(float2* ex, const float2* tw, int line1, int n1, int line2, int kq,
                                                  float2 (&u)[N2], float2 (&v)[N2]) {
     Dft<N2, false>::run(u);
@@ -423,9 +458,9 @@ struct WaveLines {
     wave_fence();
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) {
-      if (k2 > 0) u[k2] = cmul(u[k2], tw[k2 * 16 + n1]);
+      if (STAGE1 && k2 > 0) u[k2] = cmul(u[k2], tw[k2 * 16 + n1]);
       ex[c1 ^ (16 * k2 + (k2 & 15))] = u[k2];
-      if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      if (STAGE1 && k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
     wave_fence();
 #pragma unroll
@@ -434,7 +469,8 @@ struct WaveLines {
       float2 w[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) w[i] = ex[c2 ^ i];
-      Dft<16, false>::run(w);
+      if constexpr (STAGE1) Dft<16, false>::run(w);
+      else TwiddledDft<16, N, false>(tw, kq + 16 * jj).run(w);
 #pragma unroll
       for (int k1 = 0; k1 < 16; ++k1) v[jj + (N2 / 16) * k1] = w[k1];
     }
@@ -458,11 +494,12 @@ struct WaveLines {
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) {
       u[k2] = ex[c1 ^ (16 * k2 + (k2 & 15))];
-      if (k2 > 0) u[k2] = cmul_conjb(u[k2], tw[k2 * 16 + n1]);
-      if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      if (STAGE1 && k2 > 0) u[k2] = cmul_conjb(u[k2], tw[k2 * 16 + n1]);
+      if (STAGE1 && k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
     wave_fence();
-    Dft<N2, true>::run(u);
+    if constexpr (STAGE1) Dft<N2, true>::run(u);
+    else TwiddledDft<N2, N, true>(tw + N / 2, n1).run(u);
   }
 };
 
@@ -478,10 +515,9 @@ struct WaveLines {
 // x[n1 + N1 n2], the twiddle W_N^{n1 k2}, then for each k2 a DFT of size N1 giving
 // X[k2 + N2 k1]; the inverse is the same split with W_N^-1 (unnormalised). Stage-1
 // results are stored at N1 k2 + (n1 XOR (k2 mod N1)), as in LineTile.
-// Transforms are unnormalised; the twiddle table is held in LDS as W_N^{n1 k2} at k2 N1 + n1
-// (load_twiddles), so that reads are at constant offsets from the lane's n1. Cells are
-// addressed by byte offsets: a row and a column pitch of 2^a + 2^b bytes make the XOR of
-// the swizzle an XOR of offsets, one instruction per cell and none for its position.
+// Transforms are unnormalised (tws: load_twiddles' table). Cells are addressed by byte
+// offsets: a row and a column pitch of 2^a + 2^b bytes make the XOR of the swizzle an XOR
+// of offsets, one instruction per cell and none for its position.
 template <int N, int T>
 struct FrameLds {
   static constexpr int N1 = Split<N>::N1;
@@ -497,9 +533,6 @@ struct FrameLds {
   __device__ __forceinline__ static void wave_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
   __device__ __forceinline__ static float2& at(float2* lds, int off) {
     return *reinterpret_cast<float2*>(reinterpret_cast<char*>(lds) + off);
-  }
-  __device__ __forceinline__ static void load_twiddles(float2* tws, const float2* __restrict__ tw) {
-    for (int i = threadIdx.x; i < N; i += T) tws[i] = tw[(i % N1) * (i / N1)];
   }
 
   // Rows: line t / N1, lane q = t mod N1 (a half-wave reads four rows' consecutive cells);
@@ -530,19 +563,14 @@ struct FrameLds {
   template <bool INV, bool COLS>
   __device__ __forceinline__ static void line(const Line<COLS>& L, float2* lds, const float2* tws, float2 (&u)[N2]) {
     Dft<N2, INV>::run(u);
-    // twiddle and store four at a time (the caller's per-pixel state shares the registers)
 #pragma unroll
-    for (int k2 = 0; k2 < N2; ++k2) {
-      if (k2 > 0) u[k2] = INV ? cmul_conjb(u[k2], tws[k2 * N1 + L.q]) : cmul(u[k2], tws[k2 * N1 + L.q]);
-      at(lds, L.mid1(k2)) = u[k2];
-      if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-    }
+    for (int k2 = 0; k2 < N2; ++k2) at(lds, L.mid1(k2)) = u[k2];
     wave_fence();
 #pragma unroll
     for (int jj = 0; jj < N2 / N1; ++jj) {
 #pragma unroll
       for (int n1 = 0; n1 < N1; ++n1) u[jj * N1 + n1] = at(lds, L.mid2(n1, jj));
-      Dft<N1, INV>::run(&u[jj * N1]);
+      TwiddledDft<N1, N, INV>(tws, L.q + N1 * jj).run(&u[jj * N1]);
     }
   }
   // every line of the frame transformed in place, its stage-1 input in u (`from`) or read

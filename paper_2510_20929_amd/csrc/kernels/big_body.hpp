@@ -56,7 +56,7 @@ struct Big {
 template <int N, int TT>
 struct BigShared {
   float2 ex[Big<N, TT>::NW][4 * N];
-  float2 tw[N];  // W_N^{n1 k2} at k2 16 + n1
+  float2 tw[N];
   double red[2 * Big<N, TT>::NW];
   double wred[BIG_MAX_EIG * Big<N, TT>::NW];
   float wsh[BIG_MAX_EIG];
@@ -158,7 +158,7 @@ __device__ __forceinline__ void big_body(const CallArgs& a, BigShared<N, TT>& sh
   };
   if (PH == 0 && (fa || !fwd) && a.zero_acc && want_probe && !a.gpstage && !acc_lazy) clear_acc();
   bool acc_fresh = acc_lazy;
-  for (int i = tid; i < N; i += T) sh.tw[i] = a.tw[(i & 15) * (i >> 4)];
+  WL::table(sh.tw, a.tw);
   __syncthreads();
 
   // columns of group cg between the work frame and registers (row cq + 16 n2 of column cc)

@@ -39,7 +39,7 @@ __global__ __launch_bounds__(T) void fused_small_ms_kernel(CallArgs a) {
   __shared__ double wacc[MAX_EIG * (T / WAVE)];
   const int tid = threadIdx.x;
   const int S = a.S;
-  for (int i = threadIdx.x; i < N; i += T) tws[i] = a.tw[i];
+  load_twiddles<N>(tws, a.tw);
   const float inv_n = 1.f / float(N);
   const bool fwd = a.mode != MODE_APPLY_AH;
   const bool adj = a.mode == MODE_FWD_ADJ || a.mode == MODE_APPLY_AH;

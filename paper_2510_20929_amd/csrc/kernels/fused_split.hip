@@ -61,7 +61,7 @@ __global__ __launch_bounds__(T) void split_forward_kernel(CallArgs a) {
   using C = SmallCtx<N, T>;
   constexpr int E = C::E;
   __shared__ SmallShared<N, T> sh;
-  for (int i = threadIdx.x; i < N; i += T) sh.tws[i] = a.tw[i];
+  load_twiddles<N>(sh.tws, a.tw);
   const float inv_n = 1.f / float(N);
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   const int items = a.K * a.groups;
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(T) void split_adjoint_kernel(CallArgs a) {
   constexpr int E = C::E;
   __shared__ SmallShared<N, T> sh;
   float2* lds = sh.lds;
-  for (int i = threadIdx.x; i < N; i += T) sh.tws[i] = a.tw[i];
+  load_twiddles<N>(sh.tws, a.tw);
   const float inv_n = 1.f / float(N);
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   float2* scr = a.scratch + size_t(blockIdx.x) * a.scratch_stride;
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(T) void split_forward_lds_kernel(CallArgs a) {
   using F = FrameLds<N, T>;
   constexpr int EL = F::EL, NN = N * N, N1 = F::N1;
   __shared__ LdsShared<N, T> sh;
-  F::load_twiddles(sh.tws, a.tw);
+  load_twiddles<N>(sh.tws, a.tw);
   const float inv_nn = 1.f / float(N * N);
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   const BufFrame pb(a.probe, uint32_t(size_t(a.E) * a.M * NN * sizeof(float2)));
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(T) void split_adjoint_lds_kernel(CallArgs a) {
   constexpr int EL = F::EL, NN = N * N, N1 = F::N1, P = F::P;
   __shared__ LdsShared<N, T> sh;
   float2* lds = sh.lds;
-  F::load_twiddles(sh.tws, a.tw);
+  load_twiddles<N>(sh.tws, a.tw);
   const float inv_nn = 1.f / float(N * N);
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   const bool want_w = (a.want & WANT_WEIGHTS) && a.weights;

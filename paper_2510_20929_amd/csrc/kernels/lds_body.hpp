@@ -163,7 +163,7 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
   const bool adj = FA || !fwd;
   const bool want_pos = FA && (a.want & WANT_POS);
   const bool want_probe = (a.want & WANT_PROBE) != 0;
-  F::load_twiddles(tws, a.tw);
+  load_twiddles<N>(tws, a.tw);
   float2* scr = a.scratch + size_t(wg) * a.scratch_stride;
   const BufFrame sb(scr, uint32_t(a.scratch_stride * sizeof(float2)));
   const int pacc_b = int(a.pacc_off * sizeof(float2));

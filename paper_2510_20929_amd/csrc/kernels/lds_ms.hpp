@@ -46,7 +46,7 @@ __device__ __forceinline__ void lds_ms_body(const CallArgs& a, LdsShared<N, T>& 
   const bool recompute = a.recompute || !fwd;
   const bool want_pos = (a.want & WANT_POS) && fa;
   const bool want_probe = (a.want & WANT_PROBE) != 0;
-  F::load_twiddles(tws, a.tw);
+  load_twiddles<N>(tws, a.tw);
   float2* scr = a.scratch + size_t(wg) * a.scratch_stride;
   constexpr int FB = int(FR * sizeof(float2));  // bytes of a frame: S patches, S patch gradients, M S waves
   const auto op_b = [&](int s) { return s * FB; };

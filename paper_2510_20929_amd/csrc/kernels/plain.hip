@@ -30,6 +30,9 @@ __global__ __launch_bounds__(T) void fft_frames_kernel(float2* X, int nframes, c
   using F = Frame2D<N, T>;
   constexpr int E = F::E, N2 = F::N2;
   __shared__ float2 lds[F::LDS_ELEMS];
+  __shared__ float2 tws[N];
+  load_twiddles<N>(tws, tw);
+  __syncthreads();
   for (int f = blockIdx.x; f < nframes; f += gridDim.x) {
     float2* x = X + size_t(f) * N * N;
     float2 v[E];
@@ -37,14 +40,14 @@ __global__ __launch_bounds__(T) void fft_frames_kernel(float2* X, int nframes, c
     if constexpr (!INV) {
 #pragma unroll
       for (int i = 0; i < E; ++i) v[i] = x[F::a_y(t, i / N2) * N + F::a_x(t, i / N2, i % N2)];
-      F::forward(v, lds, tw, scale);
+      F::forward(v, lds, tws, scale);
       const int t2 = opaque_tid();
 #pragma unroll
       for (int i = 0; i < E; ++i) x[F::d_ky(t2, i / N2, i % N2) * N + F::d_kx(t2, i / N2)] = v[i];
     } else {
 #pragma unroll
       for (int i = 0; i < E; ++i) v[i] = x[F::d_ky(t, i / N2, i % N2) * N + F::d_kx(t, i / N2)];
-      F::inverse(v, lds, tw, scale);
+      F::inverse(v, lds, tws, scale);
       const int t2 = opaque_tid();
 #pragma unroll
       for (int i = 0; i < E; ++i) x[F::a_y(t2, i / N2) * N + F::a_x(t2, i / N2, i % N2)] = v[i];
@@ -57,10 +60,12 @@ template <int N, int RB, int T, bool INV>
 __global__ __launch_bounds__(T) void fft_rows_kernel(float2* X, const float2* __restrict__ tw, float scale) {
   constexpr int LP = N + 1;
   __shared__ float2 tile[RB * LP];
+  __shared__ float2 tws[N];
+  load_twiddles<N>(tws, tw);
   float2* x = X + size_t(blockIdx.y) * N * N + size_t(blockIdx.x) * RB * N;
   for (int i = threadIdx.x; i < RB * N; i += T) tile[(i / N) * LP + (i % N)] = x[i];
   __syncthreads();
-  LineTile<N, RB, T>::template run<INV>(tile, LP, 1, tw);
+  LineTile<N, RB, T>::template run<INV>(tile, LP, 1, tws);
   __syncthreads();
   for (int i = threadIdx.x; i < RB * N; i += T) x[i] = cscale(tile[(i / N) * LP + (i % N)], scale);
 }
@@ -70,10 +75,12 @@ template <int N, int CB, int T, bool INV>
 __global__ __launch_bounds__(T) void fft_cols_kernel(float2* X, const float2* __restrict__ tw, float scale) {
   constexpr int CP = CB + 1;
   __shared__ float2 tile[N * CP];
+  __shared__ float2 tws[N];
+  load_twiddles<N>(tws, tw);
   float2* x = X + size_t(blockIdx.y) * N * N + size_t(blockIdx.x) * CB;
   for (int i = threadIdx.x; i < N * CB; i += T) tile[(i / CB) * CP + (i % CB)] = x[size_t(i / CB) * N + (i % CB)];
   __syncthreads();
-  LineTile<N, CB, T>::template run<INV>(tile, 1, CP, tw);
+  LineTile<N, CB, T>::template run<INV>(tile, 1, CP, tws);
   __syncthreads();
   for (int i = threadIdx.x; i < N * CB; i += T)
     x[size_t(i / CB) * N + (i % CB)] = cscale(tile[(i / CB) * CP + (i % CB)], scale);

@@ -342,7 +342,7 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
   const bool fwd = a.mode != MODE_APPLY_AH;
   const bool adj = a.mode == MODE_FWD_ADJ || a.mode == MODE_APPLY_AH;
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
-  for (int i = threadIdx.x; i < N; i += T) tws[i] = a.tw[i];
+  load_twiddles<N>(tws, a.tw);
   // scratch (RV = false): patch [NN], patch-gradient accumulator [NN], far fields of
   //   modes 0..M-2 [M-1][NN] (unless recomputed), probe accumulator [E][M][NN]
   // scratch (RV = true): dl/dI [NN floats], far fields [M-1][NN], probe accumulator
@@ -606,7 +606,7 @@ __device__ __forceinline__ void small_body_near(const CallArgs& a, SmallShared<N
   const bool adj = a.mode == MODE_FWD_ADJ;
   const bool want_pos = (a.want & WANT_POS) && adj;
   const bool want_lz = (a.want & WANT_LZ) && adj && a.lz_part != nullptr;
-  for (int i = threadIdx.x; i < N; i += T) tws[i] = a.tw[i];
+  load_twiddles<N>(tws, a.tw);
   float2* scr = a.scratch + size_t(wg) * a.scratch_stride;
   const BufFrame sb(scr, uint32_t(a.scratch_stride * sizeof(float2)));
   constexpr int GACC_B = C::NN * 8;
