@@ -330,7 +330,7 @@ ptyhip_status ptyhip_batch_launch(ptyhip_batch bh, void* stream, uint32_t flags)
       e.gts = gather_tile_side(e.g.H, e.g.W, e.g.S);
       e.tiles_x = (e.g.W + e.gts - 1) / e.gts;
       e.tiles_y = (e.g.H + e.gts - 1) / e.gts;
-      tile += e.tiles_x * e.tiles_y * e.g.S;
+      tile += gather_tiles(e.g.H, e.g.W, e.g.S, e.gts);
     }
   }
   if (!b->uploaded || std::memcmp(sorted.data(), b->staging, sizeof(BatchEntry) * b->n) != 0) {

@@ -3,9 +3,9 @@
 
 namespace ptyhip {
 
-template <int TS>
-__global__ __launch_bounds__(256) void window_gather_kernel(GatherArgs g) {
-  gather_tile_t<float2, TS>(g.gwin, g.wvalid, g.pos, g.gobj, g.K, g.S, g.N, g.H, g.W, g.accumulate, g.rep);
+template <int TS, int GP>
+__global__ __launch_bounds__(256 * GP) void window_gather_kernel(GatherArgs g) {
+  gather_tile_t<float2, TS, GP>(g.gwin, g.wvalid, g.pos, g.gobj, g.K, g.S, g.N, g.H, g.W, g.accumulate, g.rep);
 }
 
 // Mode-split form: the G windows of a position (one per mode group) added in group
@@ -38,15 +38,19 @@ hipError_t launch_window_group_sum(float2* gwin, int* wvalid, int npos, int G, i
   return hipGetLastError();
 }
 
-hipError_t launch_window_gather(const GatherArgs& g, hipStream_t st) {
-  if (gather_tile_side(g.H, g.W, g.S) < GT) {
-    constexpr int TS = GT / 2;
-    dim3 grid(unsigned((g.W + TS - 1) / TS), unsigned((g.H + TS - 1) / TS), unsigned(g.S));
-    hipLaunchKernelGGL(window_gather_kernel<TS>, grid, dim3(256), 0, st, g);
-  } else {
-    dim3 grid(unsigned((g.W + GT - 1) / GT), unsigned((g.H + GT - 1) / GT), unsigned(g.S));
-    hipLaunchKernelGGL(window_gather_kernel<GT>, grid, dim3(256), 0, st, g);
+template <int TS>
+static void window_gather_t(const GatherArgs& g, hipStream_t st) {
+  const dim3 grid(unsigned(gather_tiles(g.H, g.W, g.S, TS)));
+  switch (gather_groups(g.K / (g.rep > 1 ? g.rep : 1), g.S, g.N, g.H, g.W, TS)) {
+    case 4: hipLaunchKernelGGL((window_gather_kernel<TS, 4>), grid, dim3(1024), 0, st, g); break;
+    case 2: hipLaunchKernelGGL((window_gather_kernel<TS, 2>), grid, dim3(512), 0, st, g); break;
+    default: hipLaunchKernelGGL((window_gather_kernel<TS, 1>), grid, dim3(256), 0, st, g); break;
   }
+}
+
+hipError_t launch_window_gather(const GatherArgs& g, hipStream_t st) {
+  if (gather_tile_side(g.H, g.W, g.S) < GT) window_gather_t<GT / 2>(g, st);
+  else window_gather_t<GT>(g, st);
   return hipGetLastError();
 }
 

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void illum_windows_kernel(IllumArgs a) {
 }
 
 __global__ __launch_bounds__(256) void illum_gather_kernel(IllumArgs a) {
-  gather_tile_t<float>(a.win, a.wvalid, a.pos + 2 * size_t(a.k0), a.illum, a.n, 1, a.N, a.H, a.W, a.accumulate);
+  gather_tile_t<float, GT, 1>(a.win, a.wvalid, a.pos + 2 * size_t(a.k0), a.illum, a.n, 1, a.N, a.H, a.W, a.accumulate);
 }
 
 // ---------------------------------------------------------------------------- maxima
@@ -166,8 +166,7 @@ hipError_t launch_illum_chunk(const IllumArgs& a, int grid, hipStream_t st) {
                        a.E, a.N * a.N, a.n, a.Ak);
   }
   hipLaunchKernelGGL(illum_windows_kernel, dim3(unsigned(std::max(1, std::min(a.n, grid)))), dim3(256), 0, st, a);
-  dim3 g2(unsigned((a.W + GT - 1) / GT), unsigned((a.H + GT - 1) / GT), 1);
-  hipLaunchKernelGGL(illum_gather_kernel, g2, dim3(256), 0, st, a);
+  hipLaunchKernelGGL(illum_gather_kernel, dim3(unsigned(gather_tiles(a.H, a.W, 1, GT))), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

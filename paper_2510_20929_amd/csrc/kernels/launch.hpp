@@ -76,6 +76,24 @@ inline int gather_tile_side(int H, int W, int S) {
   return tiles < 8192 ? GT / 2 : GT;
 }
 
+// groups of 256 threads per tile of the window gather, from the windows that a tile meets
+// on average. Few: the second group only costs a launch of more waves (16 windows of 513^2,
+// 2 per tile: 24 us with one group, 37 with two). Otherwise two (2000 of 129^2, 40 per tile,
+// 4096 tiles: 83 -> 78 us, 119 with four; 2500 of 257^2: 371 -> 353, 390 with four), and four
+// where the tiles leave CUs short of waves (625 of 65^2, 256 tiles: 28 -> 17 -> 13 us; 6732 of
+// 129^2, 884 tiles: 338 -> 276 -> 271).
+inline int gather_groups(int npos, int S, int N, int H, int W, int ts) {
+  const size_t tiles = size_t((W + ts - 1) / ts) * size_t((H + ts - 1) / ts) * size_t(S);
+  const double hits = double(npos) * (N + ts) * (N + ts) / (double(H) * W);
+  if (hits < 16 || tiles > (size_t(1) << 22)) return 1;
+  return tiles <= 1024 ? 4 : 2;
+}
+
+// workgroups of a gather launch: the tile rows of all slices, a multiple of the eight XCDs
+inline int gather_tiles(int H, int W, int S, int ts) {
+  return (W + ts - 1) / ts * (((H + ts - 1) / ts * S + 7) / 8 * 8);
+}
+
 hipError_t launch_fill(float* p, size_t n, float v, hipStream_t st);
 hipError_t launch_window_gather(const GatherArgs& g, hipStream_t st);
 // mode-split form: add the G group windows of each of npos positions into its first
