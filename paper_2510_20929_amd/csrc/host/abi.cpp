@@ -131,9 +131,9 @@ ptyhip_status plan_init(Plan* p, const ptyhip_desc& d, int maxK, const ptyhip_tu
   p->on_chip = N <= 128;
   const int recompute = p->tune.recompute ? 1 : 0;
   if (p->on_chip) {
-    p->threads = fused_small_threads(N, p->tune.variant);
-    p->scratch_stride = fused_small_scratch_elems(N, S, M, E, recompute, &p->pacc_off, p->tune.variant,
-                                                  d.propagation == PTYHIP_PROP_NEAR,
+    const bool near = d.propagation == PTYHIP_PROP_NEAR;
+    p->threads = fused_small_threads(N, p->tune.variant, near);
+    p->scratch_stride = fused_small_scratch_elems(N, S, M, E, recompute, &p->pacc_off, p->tune.variant, near,
                                                   d.subpixel == PTYHIP_SUBPIXEL_FOURIER);
   } else {
     p->threads = fused_big_threads(N, p->tune.variant);

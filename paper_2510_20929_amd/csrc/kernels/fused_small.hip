@@ -273,10 +273,12 @@ __global__ __launch_bounds__(256) void probe_reduce_kernel(const float2* __restr
 template <int N, int T, bool RV = false, bool GOREG = RV>
 static hipError_t launch_small_t(const CallArgs& a, int grid, hipStream_t st) {
   const bool ms = a.S > 1;
-  if (a.near) {
-    if (a.loss == 0) hipLaunchKernelGGL((fused_small_near_kernel<N, T, 0>), dim3(grid), dim3(T), 0, st, a);
-    else hipLaunchKernelGGL((fused_small_near_kernel<N, T, 1>), dim3(grid), dim3(T), 0, st, a);
-    return hipGetLastError();
+  if constexpr (N < 128) {
+    if (a.near) {
+      if (a.loss == 0) hipLaunchKernelGGL((fused_small_near_kernel<N, T, 0>), dim3(grid), dim3(T), 0, st, a);
+      else hipLaunchKernelGGL((fused_small_near_kernel<N, T, 1>), dim3(grid), dim3(T), 0, st, a);
+      return hipGetLastError();
+    }
   }
   if (ms) {
     // the slice-spacing gradient needs the adjoint and its per-position partials
@@ -310,9 +312,10 @@ static hipError_t probe_reduce_t(const CallArgs& a, int grid, float2* g_probe, i
 // 4 = as 3 with the patch gradient in scratch; 5, 6 (128^2 only) = 1024 threads, the
 // working frame resident in LDS, patch and running patch gradient in registers, dl/dI
 // in scratch (5) or in registers (6); with several slices both run the LDS-resident
-// multislice kernel (dl/dI in scratch)
-int fused_small_threads(int N, int variant) {
-  const bool wide = variant == 1 || variant == 3 || variant == 4 || (N == 128 && variant >= 5);
+// multislice kernel (dl/dI in scratch). The near field of 128^2 frames has one layout, the
+// LDS-resident one, whatever the variant.
+int fused_small_threads(int N, int variant, bool near) {
+  const bool wide = variant == 1 || variant == 3 || variant == 4 || (N == 128 && (variant >= 5 || near));
   switch (N) {
     case 16: return 64;
     case 32: return 128;
@@ -327,7 +330,7 @@ size_t fused_small_scratch_elems(int N, int S, int M, int E, int recompute, size
                                  bool near, bool fshift) {
   const size_t fr = size_t(N) * N;
   size_t base;
-  if (variant >= 5 && N == 128) base = lds_scratch_base(S, M, recompute, variant);
+  if (N == 128 && (variant >= 5 || near)) base = lds_scratch_base(S, M, recompute, variant, near);
   else if (S > 1) base = fr * (size_t(2) * S + (recompute ? 0 : size_t(M) * S));
   else if (near) base = fr * (2 + size_t(M));
   else if (fshift) base = fr * (M > 1 ? (recompute ? 2 : size_t(M) + 1) : 1) + fr;  // + shifted window spectrum
@@ -350,10 +353,7 @@ hipError_t launch_fused_small(const CallArgs& a, int N, int variant, int grid, h
       if (variant == 2) return launch_small_t<64, 512, true>(a, grid, st);
       return launch_small_t<64, 512>(a, grid, st);
     case 128:
-      if (variant >= 5) {
-        if (a.near) return hipErrorInvalidValue;
-        return launch_fused_lds(a, variant, grid, st);
-      }
+      if (variant >= 5 || a.near) return launch_fused_lds(a, variant, grid, st);
       if (variant == 1) return launch_small_t<128, 1024>(a, grid, st);
       if (variant == 3) return launch_small_t<128, 1024, true>(a, grid, st);
       if (variant == 4) return launch_small_t<128, 1024, true, false>(a, grid, st);
@@ -372,7 +372,7 @@ hipError_t launch_probe_reduce_small(const CallArgs& a, int N, int variant, int 
       return fused_small_threads(64, variant) == 256 ? probe_reduce_t<64, 256>(a, grid, g_probe, accumulate, st)
                                                      : probe_reduce_t<64, 512>(a, grid, g_probe, accumulate, st);
     case 128:
-      if (variant >= 5) return probe_reduce_t<128, 1024, true>(a, grid, g_probe, accumulate, st);
+      if (variant >= 5 || a.near) return probe_reduce_t<128, 1024, true>(a, grid, g_probe, accumulate, st);
       return fused_small_threads(128, variant) == 1024
                  ? probe_reduce_t<128, 1024>(a, grid, g_probe, accumulate, st)
                  : probe_reduce_t<128, 512>(a, grid, g_probe, accumulate, st);

@@ -101,13 +101,13 @@ hipError_t launch_window_group_sum(float2* gwin, int* wvalid, int npos, int G, i
 hipError_t launch_fft2(float2* X, int nframes, int N, const float2* tw, bool inverse, hipStream_t st);
 hipError_t run_plain_chunk(PlainArgs b, hipStream_t st);
 
-int fused_small_threads(int N, int variant);
+int fused_small_threads(int N, int variant, bool near = false);
 size_t fused_small_scratch_elems(int N, int S, int M, int E, int recompute, size_t* pacc_off, int variant,
                                  bool near = false, bool fshift = false);
 hipError_t launch_fused_small(const CallArgs& a, int N, int variant, int grid, hipStream_t st);
 // LDS-resident kernels (128^2, variants 5 and 6)
 hipError_t launch_fused_lds(const CallArgs& a, int variant, int grid, hipStream_t st);
-size_t lds_scratch_base(int S, int M, int recompute, int variant);
+size_t lds_scratch_base(int S, int M, int recompute, int variant, bool near);
 hipError_t launch_fused_small_fs(const CallArgs& a, int N, int threads, int grid, hipStream_t st);
 hipError_t launch_fused_split(const CallArgs& a, int N, int variant, int grid, double* lpart, hipStream_t st);
 hipError_t launch_probe_reduce_small(const CallArgs& a, int N, int variant, int grid, float2* g_probe,

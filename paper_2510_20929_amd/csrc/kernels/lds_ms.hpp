@@ -24,6 +24,55 @@
 
 namespace ptyhip {
 
+// Probe side of one mode: the gradient v (R) of its incident probe wave into the staging
+// frame or the accumulator frames ([E][M] from byte pacc_b of `sb`; `fresh`: written, not
+// read), and the weight terms Re<v, U_e,m> (`pb`: the probe).
+template <int N, int T>
+__device__ __forceinline__ void lds_probe_side(const CallArgs& a, int k, int m, const float* wk,
+                                               const float2 (&v)[FrameLds<N, T>::EL], const BufFrame& pb,
+                                               const BufFrame& sb, int pacc_b, bool fresh, double* wacc) {
+  constexpr int EL = FrameLds<N, T>::EL, N1 = FrameLds<N, T>::N1, NN = N * N;
+  const int t = opaque_tid();
+  const int vp = ((t / N1) * N + t % N1) * 8;
+  if ((a.want & WANT_PROBE) && a.gpstage) {
+    const BufFrame st(a.gpstage + (size_t(k) * a.M + m) * NN, NN * 8);
+#pragma unroll
+    for (int i = 0; i < EL; ++i) st.st(v[i], vp + 8 * N1 * i, 0);
+  } else if (a.want & WANT_PROBE) {
+    const int ne = wk ? a.E : 1;
+    for (int e = 0; e < ne; ++e) {
+      const int fb = pacc_b + (e * a.M + m) * NN * 8;
+      const float w = wk ? wk[e] : 1.f;
+#pragma unroll
+      for (int i0 = 0; i0 < EL; i0 += 4) {
+        float2 acc[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[u] = make_float2(0.f, 0.f);
+        if (!fresh) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc[u] = sb.ld(vp + 8 * N1 * (i0 + u), fb);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          acc[u].x = fmaf(w, v[i0 + u].x, acc[u].x);
+          acc[u].y = fmaf(w, v[i0 + u].y, acc[u].y);
+          sb.st(acc[u], vp + 8 * N1 * (i0 + u), fb);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  if ((a.want & WANT_WEIGHTS) && wk != nullptr) {
+    for (int e = 0; e < a.E; ++e) {
+      float sf = 0.f;
+#pragma unroll
+      for (int i = 0; i < EL; ++i) sf += cdotre(v[i], pb.ld(vp + 8 * N1 * i, (e * a.M + m) * NN * 8));
+      const double sw = wave_sum(double(sf));
+      if ((threadIdx.x & (WAVE - 1)) == 0) wacc[e * (T / WAVE) + threadIdx.x / WAVE] += sw;
+    }
+  }
+}
+
 template <int N, int T, int LOSS, bool LZ, bool FA>
 __device__ __forceinline__ void lds_ms_body(const CallArgs& a, LdsShared<N, T>& sh, int wg, int nwg) {
   using F = FrameLds<N, T>;
@@ -342,47 +391,7 @@ __device__ __forceinline__ void lds_ms_body(const CallArgs& a, LdsShared<N, T>& 
           inv_t(X, v);
         }
       }
-      // probe side: the gradient of mode m's incident probe wave, v (R)
-      {
-        const int vp = vpix(opaque_tid());
-        if (want_probe && a.gpstage) {
-          const BufFrame st(a.gpstage + (size_t(k) * a.M + m) * NN, NN * 8);
-#pragma unroll
-          for (int i = 0; i < EL; ++i) st.st(v[i], vp + 8 * N1 * i, 0);
-        } else if (want_probe) {
-          const int ne = wk ? a.E : 1;
-          for (int e = 0; e < ne; ++e) {
-            const int fb = pacc_b + (e * a.M + m) * NN * 8;
-            const float w = wk ? wk[e] : 1.f;
-#pragma unroll
-            for (int i0 = 0; i0 < EL; i0 += 4) {
-              float2 acc[4];
-#pragma unroll
-              for (int u = 0; u < 4; ++u) acc[u] = make_float2(0.f, 0.f);
-              if (!acc_fresh) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) acc[u] = sb.ld(vp + 8 * N1 * (i0 + u), fb);
-              }
-#pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                acc[u].x = fmaf(w, v[i0 + u].x, acc[u].x);
-                acc[u].y = fmaf(w, v[i0 + u].y, acc[u].y);
-                sb.st(acc[u], vp + 8 * N1 * (i0 + u), fb);
-              }
-              __builtin_amdgcn_sched_barrier(0);
-            }
-          }
-        }
-        if ((a.want & WANT_WEIGHTS) && wk != nullptr) {
-          for (int e = 0; e < a.E; ++e) {
-            float sf = 0.f;
-#pragma unroll
-            for (int i = 0; i < EL; ++i) sf += cdotre(v[i], pb.ld(vp + 8 * N1 * i, (e * a.M + m) * NN * 8));
-            const double sw = wave_sum(double(sf));
-            if ((tid & (WAVE - 1)) == 0) wacc[e * (T / WAVE) + tid / WAVE] += sw;
-          }
-        }
-      }
+      lds_probe_side<N, T>(a, k, m, wk, v, pb, sb, pacc_b, acc_fresh, wacc);
     }
     if constexpr (LZ) {
       const double tot = block_sum<T>(lz, red);
