@@ -32,6 +32,8 @@ FP32_VECTOR_PEAK_TFLOPS = 157.3  # MI355X FP32 vector (published)
 
 KERNEL_SOURCES = [
     "paper_2510_20929_amd/csrc/kernels/fused_small.hip",
+    "paper_2510_20929_amd/csrc/kernels/fused_small.hpp",
+    "paper_2510_20929_amd/csrc/kernels/fused_small64.hip",
     "paper_2510_20929_amd/csrc/kernels/fused_lds.hip",
     "paper_2510_20929_amd/csrc/kernels/small_body.hpp",
     "paper_2510_20929_amd/csrc/kernels/lds_body.hpp",
@@ -221,8 +223,11 @@ def kernel_name(plan, prob, tune):
         # working frame resident in LDS; dl/dI in registers (6) or scratch (5)
         return "fused_small_lds_kernel<%d, %d, %d, %s>" % (prob.N, info["threads"], loss,
                                                             "true" if v == 6 else "false")
-    rv = "true" if v in (2, 3, 4) else "false"      # patch in registers
-    goreg = "true" if v in (2, 3) else "false"      # patch gradient in registers
+    inreg = prob.N == 64 and v == 0                  # the default of 64^2 frames is layout 2
+    rv = "true" if inreg or v in (2, 3, 4) else "false"      # patch in registers
+    goreg = "true" if inreg or v in (2, 3) else "false"      # patch gradient in registers
+    if getattr(prob, "det_lambda_z", None) is not None and prob.N == 128:
+        return "fused_small_lds_near_kernel<%d, %d, %d>" % (prob.N, info["threads"], loss)
     if getattr(prob, "det_lambda_z", None) is not None:
         return "fused_small_near_kernel<%d, %d, %d>" % (prob.N, info["threads"], loss)
     return "fused_small_kernel<%d, %d, %d, %s, %s>" % (prob.N, info["threads"], loss, rv, goreg)

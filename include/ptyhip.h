@@ -125,7 +125,8 @@ typedef struct {
 
 /* Optional implementation choices (the autotuner's search space). Zero = default. */
 typedef struct {
-  int32_t variant;      /* on-chip fused kernel (64^2, 128^2): 0 = 512 threads, patch in scratch;
+  int32_t variant;      /* on-chip fused kernel (64^2, 128^2): 0 = 512 threads, patch in scratch
+                           (64^2: in registers, as 2);
                            1 = 1024 (128^2) / 256 (64^2) threads; 2 = 512 threads, patch and
                            patch gradient in registers; 3 = as 2 with 1024 / 256 threads;
                            4 = as 3 with the patch gradient in scratch; 128^2 only, one slice,
@@ -134,9 +135,11 @@ typedef struct {
                            LDS, patch and running patch gradient in registers, dl/dI in
                            scratch, far fields always recomputed; 6 = as 5 with dl/dI in
                            registers.
-                           Four-step fused kernel (256^2, 512^2): 0 = one workgroup of 1024
-                           threads per CU; 1 = two per CU (512 / 256 threads, smaller line
-                           blocks); other values are PTYHIP_EINVAL */
+                           Near-field plans of 128^2 frames run one layout, the frame resident
+                           in LDS, whatever the variant (0-4).
+                           Four-step fused kernel (256^2, 512^2): 0 = one workgroup per CU
+                           (1024 / 512 threads); 1 = two per CU (512 / 256 threads); other
+                           values are PTYHIP_EINVAL */
   int32_t grid;         /* persistent workgroups; 0 = occupancy x compute units */
   int32_t recompute;    /* 1 = recompute (multislice: incident waves; several modes: far fields)
                            instead of keeping them in workgroup scratch */
@@ -349,7 +352,7 @@ ptyhip_status ptyhip_batch_bind(ptyhip_batch b, int32_t i, const float* obj, con
 /* Run every dataset (gradient flags as in ptyhip_forward_adjoint; outputs are
  * overwritten). By default the datasets of each frame-size class run in one persistent
  * launch (one workgroup per CU, or the tuned grid) whose workgroups are split among
- * them in proportion to their work, followed by per-dataset
+ * them so that the last to finish is earliest, followed by per-dataset
  * reductions; the first launch with given flags captures this into a hipGraph on
  * `stream` and later launches replay it. PTYHIP_BATCH_PER_CALL runs one non-captured
  * fused call per dataset instead, PTYHIP_PLAIN one per-step call per dataset. Frame

@@ -3,8 +3,8 @@
 // Datasets are grouped by frame size (64^2, 128^2, 256^2, 512^2) and loss form, and each
 // class runs as one persistent launch with that frame size's thread layout (the loss form
 // a compile-time choice, as in the per-plan kernels). A launch's workgroups are
-// partitioned among its datasets in proportion to their work (positions x modes x
-// transform cost); every workgroup reads its
+// partitioned among its datasets so that the longest of them is shortest in whole rounds of
+// positions; every workgroup reads its
 // dataset's call arguments from a device descriptor table (sorted by class, then by
 // first workgroup) and runs the same per-position body as the per-plan kernels (512
 // threads for 64^2; 1024 for 128^2, with the patch in registers; 1024 and 512 for the
@@ -20,25 +20,7 @@
 
 namespace ptyhip {
 
-constexpr int BT = 512;
-
 constexpr int BT128 = 1024;  // 128^2: the register-resident patch layout (tuning variant 4)
-
-// the dataset of this workgroup within the class's entries tab[0..n)
-__device__ __forceinline__ int batch_dataset(const BatchEntry* __restrict__ tab, int n) {
-  int d = 0;
-  while (d + 1 < n && int(blockIdx.x) >= tab[d + 1].first_wg) ++d;
-  return d;
-}
-
-template <int LOSS>
-__global__ __launch_bounds__(BT) void batched_64_kernel(const BatchEntry* __restrict__ tab, int n) {
-  __shared__ SmallShared<64, BT> sh;
-  const int d = batch_dataset(tab, n);
-  const CallArgs a = tab[d].a;
-  const int wg = int(blockIdx.x) - tab[d].first_wg, nwg = tab[d].n_wg;
-  small_body<64, BT, LOSS>(a, sh, wg, nwg);
-}
 
 template <int LOSS>
 __global__ __launch_bounds__(BT128) void batched_128_kernel(const BatchEntry* __restrict__ tab, int n) {
@@ -94,7 +76,7 @@ __global__ __launch_bounds__(256 * GP) void batch_gather_kernel(const BatchEntry
 // probe gradients of every dataset of a class (blockIdx.y: dataset): the sum of the
 // dataset's workgroup accumulators; the on-chip bodies store element i of thread t at
 // i*T + t, the four-step bodies in natural order
-template <int N, int T = BT>
+template <int N, int T = 512>
 __global__ void batch_probe_reduce_kernel(const BatchEntry* __restrict__ tab) {
   const BatchEntry& e = tab[blockIdx.y];
   if (e.g_probe == nullptr || e.a.mode != MODE_FWD_ADJ) return;
@@ -149,10 +131,10 @@ hipError_t launch_batched_class(const BatchEntry* dev_tab, const BatchEntry* hos
   const BatchEntry* h = host_tab + cls_first[c];
   const dim3 grid{unsigned(cls_wg[c])};
   switch (c) {
-    case 0: hipLaunchKernelGGL(batched_64_kernel<0>, grid, dim3(BT), 0, st, t, nc); break;
-    case 1: hipLaunchKernelGGL(batched_64_kernel<1>, grid, dim3(BT), 0, st, t, nc); break;
-    case 2: hipLaunchKernelGGL(batched_128_kernel<0>, grid, dim3(BT128), 0, st, t, nc); break;
-    case 3: hipLaunchKernelGGL(batched_128_kernel<1>, grid, dim3(BT128), 0, st, t, nc); break;
+    case 0: launch_batched64(t, nc, 0, grid, st); break;
+    case 1: launch_batched64(t, nc, 1, grid, st); break;
+    case 2: hipLaunchKernelGGL(batched_128_kernel<0>, grid, dim3(1024), 0, st, t, nc); break;
+    case 3: hipLaunchKernelGGL(batched_128_kernel<1>, grid, dim3(1024), 0, st, t, nc); break;
     case 4: hipLaunchKernelGGL((batched_big_kernel<256, 1024, 0>), grid, dim3(1024), 0, st, t, nc); break;
     case 5: hipLaunchKernelGGL((batched_big_kernel<256, 1024, 1>), grid, dim3(1024), 0, st, t, nc); break;
     case 6: hipLaunchKernelGGL((batched_big_kernel<512, 512, 0>), grid, dim3(512), 0, st, t, nc); break;
@@ -177,7 +159,7 @@ hipError_t launch_batched_class(const BatchEntry* dev_tab, const BatchEntry* hos
     const dim3 pg(unsigned(std::min<size_t>(4096, (nel + 255) / 256)), unsigned(nc));
     switch (h[0].N) {
       case 64: hipLaunchKernelGGL(batch_probe_reduce_kernel<64>, pg, dim3(256), 0, st, t); break;
-      case 128: hipLaunchKernelGGL((batch_probe_reduce_kernel<128, BT128>), pg, dim3(256), 0, st, t); break;
+      case 128: hipLaunchKernelGGL((batch_probe_reduce_kernel<128, 1024>), pg, dim3(256), 0, st, t); break;
       case 256: hipLaunchKernelGGL(batch_probe_reduce_kernel<256>, pg, dim3(256), 0, st, t); break;
       case 512: hipLaunchKernelGGL(batch_probe_reduce_kernel<512>, pg, dim3(256), 0, st, t); break;
       default: return hipErrorInvalidValue;

@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256) void split_loss_chunk_kernel(CallArgs a, doubl
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   constexpr int PP = SPLIT_LOSS_PIX_SMALL / 256;  // elements per thread, their loads in flight together
   for (int k = blockIdx.y; k < a.K; k += gridDim.y) {
-    const PosInfo p = parse_position(a.pos, k, N, a.H, a.W, want_pos);
+    const PosInfo p = wave_position(a.pos, k, N, a.H, a.W, want_pos);
     const float* ip = a.ipart + size_t(k) * a.groups * NN;
     double lsum = 0.0;
     int fj[PP], cj[PP];
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(T) void split_adjoint_kernel(CallArgs a) {
           else pass(T0{}, T0{});
         }
       }
-      probe_gradients<N, T, 4>(a, k, m, wk, v, sb, 0, sh.red, sh.wacc);
+      probe_gradients<N, T, 4>(a, k, m, wk, v, sb, 0, false, sh.wacc);
     }
     __syncthreads();
     double gy = 0.0, gx = 0.0;

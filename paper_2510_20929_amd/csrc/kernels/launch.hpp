@@ -104,6 +104,9 @@ hipError_t run_plain_chunk(PlainArgs b, hipStream_t st);
 int fused_small_threads(int N, int variant, bool near = false);
 size_t fused_small_scratch_elems(int N, int S, int M, int E, int recompute, size_t* pacc_off, int variant,
                                  bool near = false, bool fshift = false);
+hipError_t launch_fused_small64(const CallArgs& a, int variant, int grid, hipStream_t st);
+hipError_t launch_probe_reduce64(const CallArgs& a, int threads, int grid, float2* g_probe, int accumulate,
+                                 hipStream_t st);
 hipError_t launch_fused_small(const CallArgs& a, int N, int variant, int grid, hipStream_t st);
 // LDS-resident kernels (128^2, variants 5 and 6)
 hipError_t launch_fused_lds(const CallArgs& a, int variant, int grid, hipStream_t st);
@@ -158,6 +161,16 @@ struct BatchEntry {
   int pad;
 };
 
+#ifdef __HIPCC__
+// the dataset of this workgroup within the class's entries tab[0..n)
+__device__ __forceinline__ int batch_dataset(const BatchEntry* __restrict__ tab, int n) {
+  int d = 0;
+  while (d + 1 < n && int(blockIdx.x) >= tab[d + 1].first_wg) ++d;
+  return d;
+}
+#endif
+
+void launch_batched64(const BatchEntry* tab, int n, int loss, dim3 grid, hipStream_t st);
 size_t batched_scratch_elems(int N, int M, int E, int recompute, size_t* pacc_off);
 // classes of the batched launch: frame size (64^2, 128^2, 256^2, 512^2) x loss form
 // (amplitude, Poisson), class 2 * size + loss; and the tuning variant whose body (and

@@ -25,11 +25,11 @@
 // gradient and the position gradient.
 //
 // Bound by the transforms' arithmetic (VALU busy 59% at 30 modes) and the accumulator's
-// traffic. Measured at 2000 positions of 4 modes, Poisson: 0.97 ms (1.16 with scaled transforms,
+// traffic. Measured at 2000 positions of 4 modes, Poisson: 1.01 ms (1.25 with scaled transforms,
 // separate probe and object passes, per-pixel window indices and 119 spilled registers); at 6732
-// positions of 30 modes 25.3 ms (28.2). Keeping the far fields of 4 modes in scratch instead of
-// recomputing them took 1.17-1.21 ms: 128 KB a mode more each way through the same memory. Eight
-// pixels at a time in the element passes took 1.03 ms (registers spilled), sixteen probe
+// positions of 30 modes 23.5 ms (28.2). Keeping the far fields of 4 modes in scratch instead of
+// recomputing them took 1.17-1.21 ms (0.97 then): 128 KB a mode more each way through the same memory. Eight
+// pixels at a time in the element passes took 1.03 ms, also 0.97 then (registers spilled), sixteen probe
 // loads at a time changed nothing.
 #pragma once
 #include "small_body.hpp"
@@ -44,104 +44,6 @@ struct LdsShared {
   float wsh[MAX_EIG];
   double wacc[MAX_EIG * (T / WAVE)];
 };
-
-// The object window of a position: buffer over its (N + 1)^2 pixels and the tap weights (a
-// tap of zero weight re-reads the base pixel).
-struct PatchWindow {
-  BufFrame win;
-  int wdx, wdy;
-  float w00, w01, w10, w11;
-  __device__ __forceinline__ PatchWindow(const float2* slice, int W, int N, const PosInfo& p)
-      : win(slice + size_t(p.y0) * W + p.x0, uint32_t((size_t(N) * W + N + 1) * 8)),
-        wdx(p.fx > 0.f ? 8 : 0), wdy(p.fy > 0.f ? W * 8 : 0),
-        w00((1.f - p.fy) * (1.f - p.fx)), w01((1.f - p.fy) * p.fx), w10(p.fy * (1.f - p.fx)), w11(p.fy * p.fx) {}
-  // bilinear sample at byte offset `voff` of the window
-  __device__ __forceinline__ float2 at(int voff) const {
-    const float2 t00 = win.ld(voff, 0), t01 = win.ld(voff, wdx), t10 = win.ld(voff, wdy), t11 = win.ld(voff, wdy + wdx);
-    return make_float2(fmaf(w11, t11.x, fmaf(w10, t10.x, fmaf(w01, t01.x, w00 * t00.x))),
-                       fmaf(w11, t11.y, fmaf(w10, t10.y, fmaf(w01, t01.y, w00 * t00.y))));
-  }
-};
-
-// Object-window pass for one slice with whole rows per wave: LDS holds the patch gradient in
-// natural order (pitch P). A wave takes N / waves consecutive rows, a lane columns lane + 64 j;
-// the row above stays in registers, so a window pixel costs two LDS reads and no index
-// arithmetic. h = (1 - fx) g[x] + fx g[x - 1]; the window is (1 - fy) h[y] + fy h[y - 1], and
-// the position terms are its derivatives against the object (requested only with a full
-// window). Call between block barriers.
-template <int N, int T, int P>
-__device__ __forceinline__ void window_rows(const CallArgs& a, const PosInfo& p, const float2* lds,
-                                            const BufFrame& win, float2* gwin, double& gy, double& gx) {
-  constexpr int WN = N + 1, NW = T / WAVE, R = N / NW, J = N / WAVE;
-  static_assert(R * NW == N && J * WAVE == N && R < WAVE, "whole rows per wave");
-  const bool want_obj = (a.want & WANT_OBJ) && gwin != nullptr;
-  const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
-  if (!want_obj && !want_pos) return;
-  const int tid = opaque_tid();
-  const int lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
-  const int y0 = wave * R;
-  const float ay = 1.f - p.fy, ax = 1.f - p.fx;
-  const float2 z = make_float2(0.f, 0.f);
-  float fy = 0.f, fx = 0.f;  // the thread's few terms in FP32, then FP64
-  float2 hp[J], dp[J];       // the row above: interpolated along x, difference along x
-  const auto row = [&](int y, float2 (&h)[J], float2 (&d)[J]) {
-    const float2* r = lds + y * P + lane;
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const float2 c = r[WAVE * j];
-      float2 l = j > 0 || lane > 0 ? r[WAVE * j - (j > 0 || lane > 0 ? 1 : 0)] : z;
-      h[j].x = fmaf(p.fx, l.x, ax * c.x);
-      h[j].y = fmaf(p.fx, l.y, ax * c.y);
-      d[j] = csub(l, c);
-    }
-  };
-  const auto emit = [&](float2 h, float2 d, float2 hup, float2 dup, int y, int x) {
-    if (want_obj) {
-      const f2v_t o = {fmaf(p.fy, hup.x, ay * h.x), fmaf(p.fy, hup.y, ay * h.y)};
-      __builtin_nontemporal_store(o, reinterpret_cast<f2v_t*>(gwin + y * WN + x));
-    }
-    if (want_pos) {
-      const float2 A = win.ld(x * 8, y * a.W * 8);
-      fy += cdotre(csub(hup, h), A);
-      fx += cdotre(make_float2(fmaf(p.fy, dup.x, ay * d.x), fmaf(p.fy, dup.y, ay * d.y)), A);
-    }
-  };
-#pragma unroll
-  for (int j = 0; j < J; ++j) hp[j] = dp[j] = z;
-  if (wave > 0) row(y0 - 1, hp, dp);
-#pragma unroll 2
-  for (int r = 0; r < R; ++r) {
-    float2 h[J], d[J];
-    row(y0 + r, h, d);
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      emit(h[j], d[j], hp[j], dp[j], y0 + r, lane + WAVE * j);
-      hp[j] = h[j];
-      dp[j] = d[j];
-    }
-  }
-  if (wave == NW - 1) {  // row N
-#pragma unroll
-    for (int j = 0; j < J; ++j) emit(z, z, hp[j], dp[j], N, lane + WAVE * j);
-  }
-  // column N of the wave's rows (and of row N), one row a lane
-  if (lane < R + (wave == NW - 1 ? 1 : 0)) {
-    const int y = y0 + lane;
-    const float2 c = y < N ? lds[y * P + N - 1] : z, u = y > 0 ? lds[(y - 1) * P + N - 1] : z;
-    const float2 h = cscale(c, p.fx), hu = cscale(u, p.fx);
-    if (want_obj) {
-      const f2v_t o = {fmaf(p.fy, hu.x, ay * h.x), fmaf(p.fy, hu.y, ay * h.y)};
-      __builtin_nontemporal_store(o, reinterpret_cast<f2v_t*>(gwin + y * WN + N));
-    }
-    if (want_pos) {
-      const float2 A = win.ld((y * a.W + N) * 8, 0);
-      fy += cdotre(csub(hu, h), A);
-      fx += cdotre(make_float2(fmaf(p.fy, u.x, ay * c.x), fmaf(p.fy, u.y, ay * c.y)), A);
-    }
-  }
-  gy += double(fy);
-  gx += double(fx);
-}
 
 // CFREG: dl/dI stays in registers (variant 6); otherwise it is parked in the first half
 // frame of the workgroup's scratch between its uses (variant 5). FA: a forward + adjoint

@@ -16,7 +16,7 @@
 // window, and the last mode's far field is scaled in the registers that hold it after
 // the forward pass. The transforms are unnormalised; 1/N^2 (a power of two) is applied with
 // the transfer function and with dl/dI. Measured at 1500 positions of 2 modes and 8 slices:
-// 6.05 ms, 8.03 ms with every mode reading and writing every slice's gradient and 8-byte
+// 5.55 ms, 8.03 ms with every mode reading and writing every slice's gradient and 8-byte
 // accesses.
 // FA: a forward + adjoint call (a.mode). LZ: also dL/d(lambda z) of the slice spacing, from F g_psi_s and F psi_s for s > 0.
 #pragma once

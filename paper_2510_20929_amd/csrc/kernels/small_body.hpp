@@ -122,16 +122,23 @@ __device__ __forceinline__ void skip_position(const CallArgs& a, int k, const Po
 // dl/dI. Returns false if the position's loss is not finite (then it is skipped).
 // NAT: the intensity is held in layout A and the detector is in natural pixel order
 // (near field); otherwise layout D and a DC-centred detector.
-template <int N, int T, int LOSS, bool NAT = false>
-__device__ __forceinline__ bool position_loss(const CallArgs& a, int k, float (&Iacc)[Frame2D<N, T>::E],
-                                              double* red) {
+// HAVE: imv holds the measured intensities already (measured_intensities, issued early).
+template <int N, int T, bool NAT = false>
+__device__ __forceinline__ void measured_intensities(const CallArgs& a, int k, float (&imv)[Frame2D<N, T>::E]) {
   using C = SmallCtx<N, T>;
   const float* im = a.imeas + size_t(k) * C::NN;
   const int t = opaque_tid();
-  auto idx = [&](int i) { return NAT ? C::a_pix(t, i) : C::d_centred(t, i); };
-  float imv[C::E];
 #pragma unroll
-  for (int i = 0; i < C::E; ++i) imv[i] = __builtin_nontemporal_load(im + idx(i));
+  for (int i = 0; i < C::E; ++i) imv[i] = __builtin_nontemporal_load(im + (NAT ? C::a_pix(t, i) : C::d_centred(t, i)));
+}
+
+template <int N, int T, int LOSS, bool NAT = false, bool HAVE = false>
+__device__ __forceinline__ bool position_loss(const CallArgs& a, int k, float (&Iacc)[Frame2D<N, T>::E],
+                                              float (&imv)[Frame2D<N, T>::E], double* red) {
+  using C = SmallCtx<N, T>;
+  const int t = opaque_tid();
+  auto idx = [&](int i) { return NAT ? C::a_pix(t, i) : C::d_centred(t, i); };
+  if constexpr (!HAVE) measured_intensities<N, T, NAT>(a, k, imv);
   if (a.ipred) {
     float* ip = a.ipred + size_t(k) * C::NN;
 #pragma unroll
@@ -175,11 +182,12 @@ __device__ __forceinline__ void zero_probe_acc(const CallArgs& a, float2* acc) {
 // several eigenprobes (a.gpstage set), write gP once to the position's staging frame
 // (natural pixel order) for the separate eigenprobe reduction sum_k w_k,e gP_k; and the
 // OPR weight-gradient sums Re<gP, U_e,m>.
-// The accumulator is read CH elements at a time (all loads of a chunk in flight).
+// The accumulator is read CH elements at a time (all loads of a chunk in flight), or with
+// `fresh` only written.
 template <int N, int T, int CH = Frame2D<N, T>::E>
 __device__ __forceinline__ void probe_gradients(const CallArgs& a, int k, int m, const float* wk,
                                                 const float2 (&gP)[Frame2D<N, T>::E], const BufFrame& sb, int acc_b,
-                                                double* red, double* wacc) {
+                                                bool fresh, double* wacc) {
   using C = SmallCtx<N, T>;
   static_assert(C::E % CH == 0, "chunk must divide the elements per thread");
   const int t = opaque_tid();
@@ -196,7 +204,11 @@ __device__ __forceinline__ void probe_gradients(const CallArgs& a, int k, int m,
       for (int i0 = 0; i0 < C::E; i0 += CH) {
         float2 g[CH];
 #pragma unroll
-        for (int u = 0; u < CH; ++u) g[u] = sb.ld(t * 8, fb + (i0 + u) * T * 8);
+        for (int u = 0; u < CH; ++u) g[u] = make_float2(0.f, 0.f);
+        if (!fresh) {
+#pragma unroll
+          for (int u = 0; u < CH; ++u) g[u] = sb.ld(t * 8, fb + (i0 + u) * T * 8);
+        }
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
           g[u].x = fmaf(w, gP[i0 + u].x, g[u].x);
@@ -209,7 +221,6 @@ __device__ __forceinline__ void probe_gradients(const CallArgs& a, int k, int m,
   if ((a.want & WANT_WEIGHTS) && wk != nullptr) {
     // Re <gP, U_e,m>: per-thread sums, then per wave into the wave's own slot of wacc
     // (no block barrier; the slots are added in a fixed order when the position ends)
-    (void)red;
     for (int e = 0; e < a.E; ++e) {
       const float2* U = a.probe + (size_t(e) * a.M + m) * C::NN;
       float sf = 0.f;  // the thread's few terms in FP32, the wave and position sums in FP64
@@ -221,13 +232,145 @@ __device__ __forceinline__ void probe_gradients(const CallArgs& a, int k, int m,
   }
 }
 
+// The object window of a position: buffer over its (N + 1)^2 pixels and the tap weights (a
+// tap of zero weight re-reads the base pixel).
+struct PatchWindow {
+  BufFrame win;
+  int wdx, wdy;
+  float w00, w01, w10, w11;
+  __device__ __forceinline__ PatchWindow(const float2* slice, int W, int N, const PosInfo& p)
+      : win(slice + size_t(p.y0) * W + p.x0, uint32_t((size_t(N) * W + N + 1) * 8)),
+        wdx(p.fx > 0.f ? 8 : 0), wdy(p.fy > 0.f ? W * 8 : 0),
+        w00((1.f - p.fy) * (1.f - p.fx)), w01((1.f - p.fy) * p.fx), w10(p.fy * (1.f - p.fx)), w11(p.fy * p.fx) {}
+  // bilinear sample at byte offset `voff` of the window
+  __device__ __forceinline__ float2 at(int voff) const {
+    const float2 t00 = win.ld(voff, 0), t01 = win.ld(voff, wdx), t10 = win.ld(voff, wdy), t11 = win.ld(voff, wdy + wdx);
+    return make_float2(fmaf(w11, t11.x, fmaf(w10, t10.x, fmaf(w01, t01.x, w00 * t00.x))),
+                       fmaf(w11, t11.y, fmaf(w10, t10.y, fmaf(w01, t01.y, w00 * t00.y))));
+  }
+};
+
+// The (N + 1)^2 object window of a position into LDS (natural order, pitch P), a lane a
+// column; row and column N only where their taps have weight (else zero: they may lie
+// outside the object). 64^2 frames.
+template <int N, int T>
+__device__ __forceinline__ void load_window(const PatchWindow& pw, const PosInfo& p, int W, float2* lds) {
+  constexpr int P = Frame2D<N, T>::P, NW = T / WAVE;
+  static_assert(N == WAVE && N % NW == 0 && P > N, "a row a wave");
+  const int tid = opaque_tid();
+  const int lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+  const float2 z = make_float2(0.f, 0.f);
+  float2 r[N / NW];
+#pragma unroll
+  for (int j = 0; j < N / NW; ++j) r[j] = pw.win.ld(lane * 8, (wave + NW * j) * W * 8);
+  // row N by the first wave, column N of rows `lane` by the second (and the corner)
+  float2 e = z, corner = z;
+  if (wave == 0 && p.fy > 0.f) e = pw.win.ld(lane * 8, N * W * 8);
+  if (wave == 1 && p.fx > 0.f) {
+    e = pw.win.ld((lane * W + N) * 8, 0);
+    if (p.fy > 0.f) corner = pw.win.ld((N * W + N) * 8, 0);
+  }
+#pragma unroll
+  for (int j = 0; j < N / NW; ++j) lds[(wave + NW * j) * P + lane] = r[j];
+  if (wave == 0) lds[N * P + lane] = e;
+  if (wave == 1) {
+    lds[lane * P + N] = e;
+    if (lane == 0) lds[N * P + N] = corner;
+  }
+}
+
+// Object-window pass for one slice with whole rows per wave: LDS holds the patch gradient in
+// natural order (pitch P). A wave takes N / waves consecutive rows, a lane columns lane + 64 j;
+// the row above stays in registers, so a window pixel costs two LDS reads and no index
+// arithmetic. h = (1 - fx) g[x] + fx g[x - 1]; the window is (1 - fy) h[y] + fy h[y - 1], and
+// the position terms are its derivatives against the object (requested only with a full
+// window). Call between block barriers.
+template <int N, int T, int P>
+__device__ __forceinline__ void window_rows(const CallArgs& a, const PosInfo& p, const float2* lds,
+                                            const BufFrame& win, float2* gwin, double& gy, double& gx) {
+  constexpr int WN = N + 1, NW = T / WAVE, R = N / NW, J = N / WAVE;
+  static_assert(R * NW == N && J * WAVE == N && R < WAVE, "whole rows per wave");
+  const bool want_obj = (a.want & WANT_OBJ) && gwin != nullptr;
+  const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
+  if (!want_obj && !want_pos) return;
+  const int tid = opaque_tid();
+  const int lane = tid & (WAVE - 1), wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+  const int y0 = wave * R;
+  const float ay = 1.f - p.fy, ax = 1.f - p.fx;
+  const float2 z = make_float2(0.f, 0.f);
+  float fy = 0.f, fx = 0.f;  // the thread's few terms in FP32, then FP64
+  float2 hp[J], dp[J];       // the row above: interpolated along x, difference along x
+  const auto row = [&](int y, float2 (&h)[J], float2 (&d)[J]) {
+    const float2* r = lds + y * P + lane;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const float2 c = r[WAVE * j];
+      float2 l = j > 0 || lane > 0 ? r[WAVE * j - (j > 0 || lane > 0 ? 1 : 0)] : z;
+      h[j].x = fmaf(p.fx, l.x, ax * c.x);
+      h[j].y = fmaf(p.fx, l.y, ax * c.y);
+      d[j] = csub(l, c);
+    }
+  };
+  const auto emit = [&](float2 h, float2 d, float2 hup, float2 dup, int y, int x) {
+    if (want_obj) {
+      const f2v_t o = {fmaf(p.fy, hup.x, ay * h.x), fmaf(p.fy, hup.y, ay * h.y)};
+      __builtin_nontemporal_store(o, reinterpret_cast<f2v_t*>(gwin + y * WN + x));
+    }
+    if (want_pos) {
+      const float2 A = win.ld(x * 8, y * a.W * 8);
+      fy += cdotre(csub(hup, h), A);
+      fx += cdotre(make_float2(fmaf(p.fy, dup.x, ay * d.x), fmaf(p.fy, dup.y, ay * d.y)), A);
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < J; ++j) hp[j] = dp[j] = z;
+  if (wave > 0) row(y0 - 1, hp, dp);
+#pragma unroll 2
+  for (int r = 0; r < R; ++r) {
+    float2 h[J], d[J];
+    row(y0 + r, h, d);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      emit(h[j], d[j], hp[j], dp[j], y0 + r, lane + WAVE * j);
+      hp[j] = h[j];
+      dp[j] = d[j];
+    }
+  }
+  if (wave == NW - 1) {  // row N
+#pragma unroll
+    for (int j = 0; j < J; ++j) emit(z, z, hp[j], dp[j], N, lane + WAVE * j);
+  }
+  // column N of the wave's rows (and of row N), one row a lane
+  if (lane < R + (wave == NW - 1 ? 1 : 0)) {
+    const int y = y0 + lane;
+    const float2 c = y < N ? lds[y * P + N - 1] : z, u = y > 0 ? lds[(y - 1) * P + N - 1] : z;
+    const float2 h = cscale(c, p.fx), hu = cscale(u, p.fx);
+    if (want_obj) {
+      const f2v_t o = {fmaf(p.fy, hu.x, ay * h.x), fmaf(p.fy, hu.y, ay * h.y)};
+      __builtin_nontemporal_store(o, reinterpret_cast<f2v_t*>(gwin + y * WN + N));
+    }
+    if (want_pos) {
+      const float2 A = win.ld((y * a.W + N) * 8, 0);
+      fy += cdotre(csub(hu, h), A);
+      fx += cdotre(make_float2(fmaf(p.fy, u.x, ay * c.x), fmaf(p.fy, u.y, ay * c.y)), A);
+    }
+  }
+  gy += double(fy);
+  gx += double(fx);
+}
+
 // Object-window pass for one slice: LDS holds the patch gradient in natural order.
 // Writes the bilinear-transposed (N+1)^2 window gradient and accumulates the position
 // gradient (which reads the object window; requested only with a full window).
+// 64^2 and 128^2 frames: whole rows per wave (window_rows).
 template <int N, int T>
 __device__ __forceinline__ void window_pass(const CallArgs& a, const PosInfo& p, const float2* lds,
                                            const float2* __restrict__ Os, float2* gwin, double& gy, double& gx) {
   constexpr int P = Frame2D<N, T>::P;
+  if constexpr (N >= WAVE) {
+    window_rows<N, T, P>(a, p, lds, PatchWindow(Os, a.W, N, p).win, gwin, gy, gx);
+    return;
+  }
   constexpr int WN = N + 1;
   const float w00 = (1.f - p.fy) * (1.f - p.fx), w01 = (1.f - p.fy) * p.fx;
   const float w10 = p.fy * (1.f - p.fx), w11 = p.fy * p.fx;
@@ -305,7 +448,7 @@ __device__ __forceinline__ void finish_position(const CallArgs& a, int k, double
 // LDS the body needs (the caller owns it so that one kernel can host several bodies)
 template <int N, int T>
 struct SmallShared {
-  float2 lds[Frame2D<N, T>::LDS_ELEMS];
+  float2 lds[Frame2D<N, T>::LDS_ELEMS + (N == WAVE ? Frame2D<N, T>::P : 0)];  // a window's rows at 64^2
   float2 tws[N];
   double red[2 * (T / WAVE)];
   float wsh[MAX_EIG];
@@ -352,11 +495,18 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
   float2* scr = a.scratch + size_t(wg) * a.scratch_stride;
   const BufFrame sb(scr, uint32_t(a.scratch_stride * sizeof(float2)));
   constexpr bool GO_IN_REGS = RV && GOREG;
+  // few elements per thread: dl/dI stays in registers, the measured intensities are loaded
+  // ahead of the last mode's transform
+  constexpr bool SMALL = E <= 8;
+  constexpr bool CF_IN_REGS = !RV || SMALL;
   constexpr int GACC_B = (RV ? C::NN / 2 : C::NN) * 8;
   constexpr int PSIS_B = (RV ? (GO_IN_REGS ? C::NN / 2 : C::NN / 2 + C::NN) : 2 * C::NN) * 8;
   const int pacc_b = int(a.pacc_off * sizeof(float2));
   const int fsx_b = pacc_b - C::NN * 8;  // FS: shifted window spectrum
-  if (adj && a.zero_acc && (a.want & WANT_PROBE) && !a.gpstage) zero_probe_acc<N, T>(a, scr + a.pacc_off);
+  // (the accumulator is written, not read, by the first finished position, as in lds_body)
+  const bool acc_lazy = adj && a.zero_acc && (a.want & WANT_PROBE) && !a.gpstage && (a.weights || a.E == 1);
+  if (adj && a.zero_acc && (a.want & WANT_PROBE) && !a.gpstage && !acc_lazy) zero_probe_acc<N, T>(a, scr + a.pacc_off);
+  bool acc_fresh = acc_lazy;
   // FS: shift phase exp(2 pi i (ky fy + kx fx) / N) of element i (layout D) and the
   // signed frequencies 2 pi k / N
   auto shift_of = [&](const PosInfo& p, int t, int i, float& cy, float& cx) {
@@ -370,7 +520,7 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
   };
 
   for (int k = wg; k < a.K; k += nwg) {
-    const PosInfo p = parse_position(a.pos, k, N, a.H, a.W, want_pos && !FS);
+    const PosInfo p = wave_position(a.pos, k, N, a.H, a.W, want_pos && !FS);
     if (!p.ok) {
       skip_position<N, T>(a, k, p);
       continue;
@@ -409,13 +559,33 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
         for (int i = 0; i < E; ++i) sb.st(w[i], t * 8, i * T * 8);
       }
     } else {
-      const int t = opaque_tid();
-#pragma unroll
-      for (int i = 0; i < E; ++i) {
-        const int l = i / C::N2, j = i % C::N2;
-        const float2 val = bilinear(a.obj, a.W, p, F::a_y(t, l), F::a_x(t, l, j));
+      const PatchWindow pw(a.obj, a.W, N, p);
+      const auto put = [&](int i, int t, float2 val) {
         if constexpr (RV) o[i] = val;
         else sb.st(val, t * 8, i * T * 8);
+      };
+      if constexpr (N == WAVE) {
+        // the window's rows, one pixel a lane, go into LDS once; a pixel's taps are then
+        // four LDS reads instead of four loads
+        load_window<N, T>(pw, p, a.W, lds);
+        __syncthreads();
+        const int t = opaque_tid();
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          const int l = i / C::N2, j = i % C::N2;
+          const float2* w = lds + F::a_y(t, l) * F::P + F::a_x(t, l, j);
+          const float2 t00 = w[0], t01 = w[1], t10 = w[F::P], t11 = w[F::P + 1];
+          put(i, t, make_float2(fmaf(pw.w11, t11.x, fmaf(pw.w10, t10.x, fmaf(pw.w01, t01.x, pw.w00 * t00.x))),
+                                fmaf(pw.w11, t11.y, fmaf(pw.w10, t10.y, fmaf(pw.w01, t01.y, pw.w00 * t00.y)))));
+        }
+        __syncthreads();  // the window is read before the transform overwrites it
+      } else {
+        const int t = opaque_tid();
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          const int l = i / C::N2, j = i % C::N2;
+          put(i, t, pw.at((F::a_y(t, l) * a.W + F::a_x(t, l, j)) * 8));
+        }
       }
     }
     // patch value of element i (thread t)
@@ -425,7 +595,7 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
     };
 
     float2 v[E];
-    float cf[E];
+    float cf[E], imv[E];
     if (fwd) {
 #pragma unroll
       for (int i = 0; i < E; ++i) cf[i] = 0.f;
@@ -433,6 +603,9 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
         {
           const int t = opaque_tid();
           for_probe<N, T>(a, wk, m, t, [&](int i, float2 P) { v[i] = cmul(P, patch(i, t)); });
+        }
+        if constexpr (SMALL) {
+          if (m == a.M - 1 && a.mode != MODE_APPLY_A) measured_intensities<N, T>(a, k, imv);
         }
         F::forward(v, lds, tws, inv_n);
 #pragma unroll
@@ -452,9 +625,9 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
         }
       }
       if (a.mode == MODE_APPLY_A) continue;
-      if (!position_loss<N, T, LOSS>(a, k, cf, red)) continue;
+      if (!position_loss<N, T, LOSS, false, SMALL>(a, k, cf, imv, red)) continue;
       if (a.mode == MODE_FORWARD) continue;
-      if constexpr (RV) {
+      if constexpr (!CF_IN_REGS) {
         const int t = opaque_tid();
 #pragma unroll
         for (int i = 0; i < E; ++i) sb.stf(cf[i], t * 4, i * T * 4);
@@ -488,7 +661,7 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
         const int t = opaque_tid();
 #pragma unroll
         for (int i = 0; i < E; ++i) {
-          if constexpr (RV) v[i] = cscale(v[i], a.gscale * sb.ldf(t * 4, i * T * 4));
+          if constexpr (!CF_IN_REGS) v[i] = cscale(v[i], a.gscale * sb.ldf(t * 4, i * T * 4));
           else v[i] = cscale(v[i], a.gscale * cf[i]);
         }
       }
@@ -501,7 +674,7 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
         // loops), then v = conj(o) g_m for the probe gradient
         auto pass = [&](auto first_c, auto last_c) {
           constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
-          for_probe<N, T, (GO_IN_REGS ? 4 : 0)>(a, wk, m, t, [&](int i, float2 P) {
+          for_probe<N, T, (GO_IN_REGS && !SMALL ? 4 : 0)>(a, wk, m, t, [&](int i, float2 P) {
             float2 g = cmulc(P, v[i]);
             if constexpr (GO_IN_REGS) {
               if constexpr (!FIRST) g = cadd(g, go[i]);
@@ -527,7 +700,7 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
           else pass(T0{}, T0{});
         }
       }
-      probe_gradients<N, T, (GO_IN_REGS ? 4 : E)>(a, k, m, wk, v, sb, pacc_b, red, wacc);
+      probe_gradients<N, T, (GO_IN_REGS && !SMALL ? 4 : E)>(a, k, m, wk, v, sb, pacc_b, acc_fresh, wacc);
     }
 
     __syncthreads();
@@ -581,8 +754,10 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
     } else {
       window_pass<N, T>(a, p, lds, a.obj, a.gwin ? a.gwin + size_t(k) * C::WN * C::WN : nullptr, gy, gx);
     }
+    acc_fresh = false;
     finish_position<N, T>(a, k, gy, gx, red, wacc);
   }
+  if (acc_fresh) zero_probe_acc<N, T>(a, scr + a.pacc_off);
 }
 
 // Near-field detector: Psi = F^-1(H F chi) with the detector transfer function H, the
@@ -615,7 +790,7 @@ __device__ __forceinline__ void small_body_near(const CallArgs& a, SmallShared<N
   if (adj && a.zero_acc && (a.want & WANT_PROBE) && !a.gpstage) zero_probe_acc<N, T>(a, scr + a.pacc_off);
 
   for (int k = wg; k < a.K; k += nwg) {
-    const PosInfo p = parse_position(a.pos, k, N, a.H, a.W, want_pos);
+    const PosInfo p = wave_position(a.pos, k, N, a.H, a.W, want_pos);
     if (!p.ok) {
       skip_position<N, T>(a, k, p);
       if (threadIdx.x == 0 && a.lz_part) a.lz_part[k] = 0.0;
@@ -657,7 +832,8 @@ __device__ __forceinline__ void small_body_near(const CallArgs& a, SmallShared<N
 #pragma unroll
       for (int i = 0; i < E; ++i) cf[i] += cabs2(v[i]);
     }
-    if (!position_loss<N, T, LOSS, true>(a, k, cf, red)) {
+    float imv[E];
+    if (!position_loss<N, T, LOSS, true>(a, k, cf, imv, red)) {
       if (threadIdx.x == 0 && a.lz_part) a.lz_part[k] = 0.0;
       continue;
     }
@@ -716,7 +892,7 @@ __device__ __forceinline__ void small_body_near(const CallArgs& a, SmallShared<N
           else pass(T0{}, T0{});
         }
       }
-      probe_gradients<N, T>(a, k, m, wk, v, sb, pacc_b, red, wacc);
+      probe_gradients<N, T>(a, k, m, wk, v, sb, pacc_b, false, wacc);
     }
     if (want_lz) {
       const double tot = block_sum<T>(lz, red);
