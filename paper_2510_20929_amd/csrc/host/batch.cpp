@@ -188,8 +188,8 @@ ptyhip_status ptyhip_batch_create(const ptyhip_desc* descs, const int32_t* K, in
     if (tune) t = *tune;
     t.mode_groups = 0;  // a batch runs whole positions per workgroup
     t.grid = std::max(b->n_wg[i], prop.multiProcessorCount);
-    // the body each class's launch runs: 128^2 the register-resident patch layout with
-    // recomputed far fields (several modes), the others the default layout
+    // the body each class's launch runs: 128^2 the LDS-resident frame (far fields
+    // recomputed), the others the default layout
     t.variant = batch_variant(descs[i].frame);
     t.recompute = (descs[i].frame == 128 && descs[i].n_modes > 1) ? 1 : 0;
     if (t.plain_chunk <= 0) t.plain_chunk = 128;

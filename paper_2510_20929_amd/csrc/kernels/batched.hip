@@ -7,7 +7,7 @@
 // positions; every workgroup reads its
 // dataset's call arguments from a device descriptor table (sorted by class, then by
 // first workgroup) and runs the same per-position body as the per-plan kernels (512
-// threads for 64^2; 1024 for 128^2, with the patch in registers; 1024 and 512 for the
+// threads for 64^2; 1024 for 128^2, with the frame in LDS; 1024 and 512 for the
 // four-step frames 256^2 and 512^2). Gathers, probe reductions and final reductions follow, one
 // launch each for all datasets of the class; they too read their pointers from the
 // table, so a captured graph stays valid when the caller rebinds buffers.
@@ -16,19 +16,20 @@
 #include "big_body.hpp"
 #include "gather.hpp"
 #include "launch.hpp"
-#include "small_body.hpp"
+#include "lds_body.hpp"
 
 namespace ptyhip {
 
-constexpr int BT128 = 1024;  // 128^2: the register-resident patch layout (tuning variant 4)
-
+// 128^2: the frame resident in LDS, dl/dI in registers (640 positions of 2 modes and 263 of 4:
+// 546 us, 572 with patch and frame in registers)
 template <int LOSS>
-__global__ __launch_bounds__(BT128) void batched_128_kernel(const BatchEntry* __restrict__ tab, int n) {
-  __shared__ SmallShared<128, BT128> sh;
+__global__ __launch_bounds__(1024) void batched_128_kernel(const BatchEntry* __restrict__ tab, int n) {
+  __shared__ LdsShared<128, 1024> sh;
   const int d = batch_dataset(tab, n);
   const CallArgs a = tab[d].a;
   const int wg = int(blockIdx.x) - tab[d].first_wg, nwg = tab[d].n_wg;
-  small_body<128, BT128, LOSS, true, false>(a, sh, wg, nwg);
+  if (a.mode == MODE_FWD_ADJ) lds_body<128, 1024, LOSS, true, true>(a, sh, wg, nwg);
+  else lds_body<128, 1024, LOSS, true, false>(a, sh, wg, nwg);
 }
 
 template <int N, int T, int LOSS>
@@ -43,7 +44,7 @@ __global__ __launch_bounds__(T, N == 256 ? 4 : 2) void batched_big_kernel(const 
 
 int batch_class(int N, int loss) { return 2 * (N <= 64 ? 0 : (N == 128 ? 1 : (N == 256 ? 2 : 3))) + (loss ? 1 : 0); }
 
-int batch_variant(int N) { return N == 128 ? 4 : 0; }
+int batch_variant(int N) { return N == 128 ? 6 : 0; }
 
 size_t batched_scratch_elems(int N, int M, int E, int recompute, size_t* pacc_off) {
   if (N <= 128) return fused_small_scratch_elems(N, 1, M, E, recompute, pacc_off, batch_variant(N));
@@ -74,8 +75,8 @@ __global__ __launch_bounds__(256 * GP) void batch_gather_kernel(const BatchEntry
 }
 
 // probe gradients of every dataset of a class (blockIdx.y: dataset): the sum of the
-// dataset's workgroup accumulators; the on-chip bodies store element i of thread t at
-// i*T + t, the four-step bodies in natural order
+// dataset's workgroup accumulators; the 64^2 body stores element i of thread t at
+// i*T + t, the others in natural order
 template <int N, int T = 512>
 __global__ void batch_probe_reduce_kernel(const BatchEntry* __restrict__ tab) {
   const BatchEntry& e = tab[blockIdx.y];
@@ -100,7 +101,7 @@ __global__ void batch_probe_reduce_kernel(const BatchEntry* __restrict__ tab) {
     }
     for (; w < groups; ++w) s = cadd(s, src[size_t(w) * a.scratch_stride]);
     size_t pix = r;
-    if constexpr (N <= 128) pix = size_t(SmallCtx<N, T>::a_pix(int(r % T), int(r / T)));
+    if constexpr (N < 128) pix = size_t(SmallCtx<N, T>::a_pix(int(r % T), int(r / T)));
     out[em * NN + pix] = s;
   }
 }
