@@ -233,7 +233,7 @@ class Plan:
         K = self._inputs(obj, probe, positions, weights)
         _need(I_meas, "I_meas", torch.float32, (K, self.N, self.N))
         if loss is None:
-            loss = torch.zeros(1, dtype=torch.float64, device=obj.device)
+            loss = (torch.empty if K > 0 else torch.zeros)(1, dtype=torch.float64, device=obj.device)
         if I_pred is not None:
             _need(I_pred, "I_pred", torch.float32, (K, self.N, self.N))
         st = _lib().ptyhip_forward(self._h, _stream(stream), K, _ptr(obj), _ptr(probe), _ptr(weights),
@@ -247,29 +247,32 @@ class Plan:
         _need(I_meas, "I_meas", torch.float32, (K, self.N, self.N))
         dev = obj.device
         out = dict(out or {})
+        # the fused form writes every element of its outputs: no fills (three launches less in
+        # a minibatch step of 24 frames of 64^2: 145 us with them, 83-100 without)
+        alloc = torch.zeros if accumulate or plain or K == 0 else torch.empty
         if "loss" not in out:
-            out["loss"] = torch.zeros(1, dtype=torch.float64, device=dev)
+            out["loss"] = alloc(1, dtype=torch.float64, device=dev)
         flags = 0
         if "obj" in grads:
             flags |= GRAD_OBJ
             if "g_obj" not in out:
-                out["g_obj"] = torch.zeros((self.S, self.H, self.W), dtype=torch.complex64, device=dev)
+                out["g_obj"] = alloc((self.S, self.H, self.W), dtype=torch.complex64, device=dev)
         if "probe" in grads:
             flags |= GRAD_PROBE
             if "g_probe" not in out:
-                out["g_probe"] = torch.zeros((self.E, self.M, self.N, self.N), dtype=torch.complex64, device=dev)
+                out["g_probe"] = alloc((self.E, self.M, self.N, self.N), dtype=torch.complex64, device=dev)
         if "pos" in grads:
             flags |= GRAD_POS
             if "g_pos" not in out:
-                out["g_pos"] = torch.zeros((K, 2), dtype=torch.float32, device=dev)
+                out["g_pos"] = alloc((K, 2), dtype=torch.float32, device=dev)
         if "weights" in grads:
             flags |= GRAD_WEIGHTS
             if "g_weights" not in out:
-                out["g_weights"] = torch.zeros((K, self.E), dtype=torch.float32, device=dev)
+                out["g_weights"] = alloc((K, self.E), dtype=torch.float32, device=dev)
         if "lambda_z" in grads:
             flags |= GRAD_LAMBDA_Z
             if "g_lambda_z" not in out:
-                out["g_lambda_z"] = torch.zeros(1, dtype=torch.float64, device=dev)
+                out["g_lambda_z"] = alloc(1, dtype=torch.float64, device=dev)
         if accumulate:
             flags |= ACCUMULATE
         if plain:
