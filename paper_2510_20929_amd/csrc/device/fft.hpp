@@ -18,20 +18,27 @@
 namespace ptyhip {
 
 // ----------------------------------------------------------------------------- register DFTs
-// Radix-2 decimation in time, unrolled, in natural order. A butterfly a +- w b costs six
-// fused operations: s = a + w b (four), a - w b = 2 a - s (two); w = 1 and -i cost four
-// additions.
+// Radix-2 decimation in time, unrolled, in natural order. A butterfly a +- w b with
+// w = wr (1 + i tau) costs six fused operations (Linzer and Feig's form): u = (1 + i tau) b,
+// a + wr u and a - wr u. Each result is rounded twice, where a product, a sum and a
+// difference round three times; tau is large only where wr u is not (|w| = 1). With a - w b
+// taken as 2 a - (a + w b) the results of 8 slices were 1.5 times as far from 64-bit ones
+// (3.2e-6 against 2.1e-6). w = 1 and -i cost four additions.
 template <bool INV>
-__device__ __forceinline__ void butterfly(float2 a, float2 b, float2 w, float2& s, float2& d) {
-  if constexpr (INV) {  // a +- conj(w) b
-    s.x = fmaf(b.x, w.x, fmaf(b.y, w.y, a.x));
-    s.y = fmaf(b.y, w.x, fmaf(-b.x, w.y, a.y));
-  } else {
-    s.x = fmaf(b.x, w.x, fmaf(-b.y, w.y, a.x));
-    s.y = fmaf(b.y, w.x, fmaf(b.x, w.y, a.y));
-  }
-  d.x = fmaf(2.f, a.x, -s.x);
-  d.y = fmaf(2.f, a.y, -s.y);
+__device__ __forceinline__ void butterfly(float2 a, float2 b, float wr, float tau, float2& s, float2& d) {
+  // INV: w's conjugate
+  const float t = INV ? -tau : tau;
+  const float2 u = make_float2(fmaf(-t, b.y, b.x), fmaf(t, b.x, b.y));
+  s = make_float2(fmaf(wr, u.x, a.x), fmaf(wr, u.y, a.y));
+  d = make_float2(fmaf(-wr, u.x, a.x), fmaf(-wr, u.y, a.y));
+}
+
+// a +- w b for any w (eight operations): w at or beyond -i has no bounded tau
+template <bool INV>
+__device__ __forceinline__ void butterfly_any(float2 a, float2 b, float2 w, float2& s, float2& d) {
+  const float wi = INV ? -w.y : w.y;
+  s = make_float2(fmaf(b.x, w.x, fmaf(-b.y, wi, a.x)), fmaf(b.y, w.x, fmaf(b.x, wi, a.y)));
+  d = make_float2(fmaf(-b.x, w.x, fmaf(b.y, wi, a.x)), fmaf(-b.y, w.x, fmaf(-b.x, wi, a.y)));
 }
 
 // DFT of size R of v (exp(-2 pi i k n / R), or its conjugate)
@@ -58,7 +65,8 @@ struct Dft {
           v[k] = cadd(e[k], t);
           v[k + H] = csub(e[k], t);
         } else {
-          butterfly<false>(e[k], o[k], make_float2(Twiddle<R, k, INV>::re, Twiddle<R, k, INV>::im), v[k], v[k + H]);
+          using W = Twiddle<R, k, INV>;
+          butterfly<false>(e[k], o[k], W::re, W::im / W::re, v[k], v[k + H]);
         }
       });
     }
@@ -69,13 +77,13 @@ struct Dft {
 // size N: the twiddles go into the butterflies, whose factors at size L are w^(R / L) W_L^k,
 // k < L / 4 (the other quarter has -i times the same). That is R / 2 table entries and no
 // multiplication of its own instead of R - 1 of each (128^2, 6732 positions x 30 modes:
-// 25.75 -> 24.09 ms together with the fused radix-2 butterflies; 8 slices x 1500 positions:
-// 6.52 -> 5.95 ms). Table (load_twiddles): factor j of
+// 25.75 -> 24.9 ms together with the fused radix-2 butterflies; 8 slices x 1500 positions:
+// 6.52 -> 5.98 ms). Table (load_twiddles): factor j of
 // every p consecutive, so that a lane's entries are at constant distances.
 template <int R, int N, bool INV>
 struct TwiddledDft {
   static constexpr int PITCH = N / R;
-  float2 c[R / 2];  // size 2: c[0]; size L: c[L / 4 + k]
+  float2 c[R / 2];  // size 2: c[0], w^(R / 2); size L: c[L / 4 + k], (wr, tau)
   __device__ __forceinline__ TwiddledDft(const float2* tab, int p) {
 #pragma unroll
     for (int j = 0; j < R / 2; ++j) c[j] = tab[j * PITCH + p];
@@ -89,7 +97,7 @@ struct TwiddledDft {
   template <int L = R>
   __device__ __forceinline__ void run(float2* v) const {
     if constexpr (L == 2) {
-      butterfly<INV>(v[0], v[1], c[0], v[0], v[1]);
+      butterfly_any<INV>(v[0], v[1], c[0], v[0], v[1]);
     } else {
       constexpr int H = L / 2, Q = L / 4;
       float2 e[H], o[H];
@@ -102,8 +110,8 @@ struct TwiddledDft {
       run<H>(o);
 #pragma unroll
       for (int k = 0; k < Q; ++k) {
-        butterfly<INV>(e[k], o[k], c[Q + k], v[k], v[k + H]);
-        butterfly<INV>(e[k + Q], mul_mi<INV>(o[k + Q]), c[Q + k], v[k + Q], v[k + Q + H]);
+        butterfly<INV>(e[k], o[k], c[Q + k].x, c[Q + k].y, v[k], v[k + H]);
+        butterfly<INV>(e[k + Q], mul_mi<INV>(o[k + Q]), c[Q + k].x, c[Q + k].y, v[k + Q], v[k + Q + H]);
       }
     }
   }
@@ -120,13 +128,17 @@ template <> struct Split<256> { static constexpr int N1 = 16, N2 = 16; };
 template <> struct Split<512> { static constexpr int N1 = 16, N2 = 32; };
 
 // The LDS table of a transform of N points, N entries from tw (W_N^j): the factors of its
-// forward second stage (size N1), then from N / 2 those of its inverse (size N2).
+// forward second stage (size N1), then from N / 2 those of its inverse (size N2). Beyond size
+// 2 their angles lie in (-pi / 2, 0], so wr > 0.
 template <int N>
 __device__ __forceinline__ void load_twiddles(float2* tws, const float2* __restrict__ tw) {
   constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2;
   for (int i = threadIdx.x; i < N; i += blockDim.x) {
     const int h = i % (N / 2);
-    tws[i] = tw[i < N / 2 ? TwiddledDft<N1, N, false>::exponent(h / N2, h % N2) : TwiddledDft<N2, N, true>::exponent(h / N1, h % N1)];
+    const int j = i < N / 2 ? h / N2 : h / N1;
+    const float2 w = tw[i < N / 2 ? TwiddledDft<N1, N, false>::exponent(j, h % N2)
+                                  : TwiddledDft<N2, N, true>::exponent(j, h % N1)];
+    tws[i] = j == 0 ? w : make_float2(w.x, w.y / w.x);
   }
 }
 

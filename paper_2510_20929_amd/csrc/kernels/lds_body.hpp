@@ -27,7 +27,7 @@
 // Bound by the transforms' arithmetic (VALU busy 59% at 30 modes) and the accumulator's
 // traffic. Measured at 2000 positions of 4 modes, Poisson: 0.92 ms (1.16 with scaled transforms,
 // separate probe and object passes, per-pixel window indices and 119 spilled registers); at 6732
-// positions of 30 modes 23.5 ms (28.2). Keeping the far fields of 4 modes in scratch instead of
+// positions of 30 modes 24.4 ms (28.2). Keeping the far fields of 4 modes in scratch instead of
 // recomputing them took 1.17-1.21 ms (0.97 then): 128 KB a mode more each way through the same memory. Eight
 // pixels at a time in the element passes took 1.03 ms, also 0.97 then (registers spilled), sixteen probe
 // loads at a time changed nothing.
