@@ -21,9 +21,9 @@ namespace ptyhip {
 // Radix-2 decimation in time, unrolled, in natural order. A butterfly a +- w b with
 // w = wr (1 + i tau) costs six fused operations (Linzer and Feig's form): u = (1 + i tau) b,
 // a + wr u and a - wr u. Each result is rounded twice, where a product, a sum and a
-// difference round three times; tau is large only where wr u is not (|w| = 1). With a - w b
-// taken as 2 a - (a + w b) the results of 8 slices were 1.5 times as far from 64-bit ones
-// (3.2e-6 against 2.1e-6). w = 1 and -i cost four additions.
+// difference round three times; tau is large only where wr u is not (|w| = 1). (a - w b
+// as 2 a - (a + w b) carries the sum's rounding: 4 modes 3.7e-7 from 64-bit results, 3.3e-7
+// this way.) w = 1 and -i cost four additions.
 template <bool INV>
 __device__ __forceinline__ void butterfly(float2 a, float2 b, float wr, float tau, float2& s, float2& d) {
   // INV: w's conjugate
@@ -73,14 +73,103 @@ struct Dft {
   }
 };
 
+// The same with radix-4 butterflies of plain sums and one constant twiddle between them: a value
+// meets fewer rounded constants on its way, so that chained transforms gain and lose less
+// (TwiddledDft with SEP).
+// multiply by the constant twiddle W_R^J, with the trivial angles special-cased
+template <int R, int J, bool INV>
+__device__ __forceinline__ float2 twiddle_const(float2 a) {
+  constexpr int j = J % R;
+  if constexpr (j == 0) {
+    return a;
+  } else if constexpr (4 * j == R) {
+    return mul_mi<INV>(a);
+  } else if constexpr (2 * j == R) {
+    return make_float2(-a.x, -a.y);
+  } else if constexpr (4 * j == 3 * R) {
+    return mul_mi<!INV>(a);
+  } else {
+    return cmul(a, make_float2(Twiddle<R, J, INV>::re, Twiddle<R, J, INV>::im));
+  }
+}
+
+template <int R, bool INV>
+struct Dft4;
+
+template <bool INV>
+struct Dft4<1, INV> {
+  __device__ __forceinline__ static void run(float2*) {}
+};
+
+template <bool INV>
+struct Dft4<2, INV> {
+  __device__ __forceinline__ static void run(float2* v) {
+    float2 a = v[0], b = v[1];
+    v[0] = cadd(a, b);
+    v[1] = csub(a, b);
+  }
+};
+
+template <bool INV>
+struct Dft4<4, INV> {
+  __device__ __forceinline__ static void run(float2* v) {
+    float2 s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
+    float2 s13 = cadd(v[1], v[3]), d13 = mul_mi<INV>(csub(v[1], v[3]));
+    v[0] = cadd(s02, s13);
+    v[2] = csub(s02, s13);
+    v[1] = cadd(d02, d13);
+    v[3] = csub(d02, d13);
+  }
+};
+
+// Cooley-Tukey split R = A * B with constant twiddles (register renaming only).
+template <int A, int B, bool INV>
+__device__ __forceinline__ void dft4_split(float2* v) {
+  constexpr int R = A * B;
+  float2 t[R];
+  static_for<0, A>([&](auto n1c) {
+    constexpr int n1 = decltype(n1c)::value;
+    float2 u[B];
+#pragma unroll
+    for (int n2 = 0; n2 < B; ++n2) u[n2] = v[n1 + A * n2];
+    Dft4<B, INV>::run(u);
+    static_for<0, B>([&](auto k2c) {
+      constexpr int k2 = decltype(k2c)::value;
+      t[n1 * B + k2] = twiddle_const<R, n1 * k2, INV>(u[k2]);
+    });
+  });
+#pragma unroll
+  for (int k2 = 0; k2 < B; ++k2) {
+    float2 u[A];
+#pragma unroll
+    for (int n1 = 0; n1 < A; ++n1) u[n1] = t[n1 * B + k2];
+    Dft4<A, INV>::run(u);
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) v[k2 + B * k1] = u[k1];
+  }
+}
+
+template <bool INV>
+struct Dft4<8, INV> {
+  __device__ __forceinline__ static void run(float2* v) { dft4_split<2, 4, INV>(v); }
+};
+template <bool INV>
+struct Dft4<16, INV> {
+  __device__ __forceinline__ static void run(float2* v) { dft4_split<4, 4, INV>(v); }
+};
+template <bool INV>
+struct Dft4<32, INV> {
+  __device__ __forceinline__ static void run(float2* v) { dft4_split<4, 8, INV>(v); }
+};
+
 // DFT of size R of v[n] w^n with w = W_N^p (p < N / R), the second factor of a transform of
 // size N: the twiddles go into the butterflies, whose factors at size L are w^(R / L) W_L^k,
 // k < L / 4 (the other quarter has -i times the same). That is R / 2 table entries and no
 // multiplication of its own instead of R - 1 of each (128^2, 6732 positions x 30 modes:
-// 25.75 -> 24.9 ms together with the fused radix-2 butterflies; 8 slices x 1500 positions:
-// 6.52 -> 5.98 ms). Table (load_twiddles): factor j of
+// 25.75 -> 24.9 ms together with the fused radix-2 butterflies; 300 near-field positions: 464 ->
+// 440 us). Table (load_twiddles): factor j of
 // every p consecutive, so that a lane's entries are at constant distances.
-template <int R, int N, bool INV>
+template <int R, int N, bool INV, bool SEP = false>
 struct TwiddledDft {
   static constexpr int PITCH = N / R;
   float2 c[R / 2];  // size 2: c[0], w^(R / 2); size L: c[L / 4 + k], (wr, tau)
@@ -117,6 +206,29 @@ struct TwiddledDft {
   }
 };
 
+// The same with every element multiplied by its own entry w^n, n < R (an element is then
+// multiplied by one rounded twiddle, not by a product of log2 R of them): the transforms of
+// models that chain many (multislice), whose gain errors add up (8 slices: 2.0e-6 from 64-bit
+// results and 6.2 ms; 3.2e-6 and 5.9 ms with the twiddles in the butterflies), and of the
+// per-step form.
+template <int R, int N, bool INV>
+struct TwiddledDft<R, N, INV, true> {
+  static constexpr int PITCH = N / R;
+  const float2* c;
+  __device__ __forceinline__ TwiddledDft(const float2* tab, int p) : c(tab + p) {}
+  __device__ __forceinline__ void run(float2* v) const {
+#pragma unroll
+    for (int n = 1; n < R; ++n) v[n] = INV ? cmul_conjb(v[n], c[n * PITCH]) : cmul(v[n], c[n * PITCH]);
+    Dft4<R, INV>::run(v);
+  }
+};
+// first stage of a split transform
+template <int R, bool INV, bool SEP>
+__device__ __forceinline__ void first_dft(float2* v) {
+  if constexpr (SEP) Dft4<R, INV>::run(v);
+  else Dft<R, INV>::run(v);
+}
+
 // ----------------------------------------------------------------------------- factorisations
 template <int N>
 struct Split;
@@ -141,6 +253,18 @@ __device__ __forceinline__ void load_twiddles(float2* tws, const float2* __restr
     tws[i] = j == 0 ? w : make_float2(w.x, w.y / w.x);
   }
 }
+// The separate twiddles (TwiddledDft with SEP): W_N^{n p} at n N2 + p of the forward second
+// stage, and at n N1 + p of the inverse one.
+template <int N>
+__device__ __forceinline__ void load_separate_twiddles(float2* fwd, const float2* __restrict__ tw) {
+  constexpr int N2 = Split<N>::N2;
+  for (int i = threadIdx.x; i < N; i += blockDim.x) fwd[i] = tw[(i / N2) * (i % N2)];
+}
+template <int N>
+__device__ __forceinline__ void load_separate_inverse_twiddles(float2* inv, const float2* __restrict__ tw) {
+  constexpr int N1 = Split<N>::N1;
+  for (int i = threadIdx.x; i < N; i += blockDim.x) inv[i] = tw[(i / N1) * (i % N1)];
+}
 
 // ----------------------------------------------------------------------------- on-chip 2D frame
 // A whole N x N frame spread over T threads (N <= 128). Each thread owns E elements.
@@ -153,7 +277,8 @@ __device__ __forceinline__ void load_twiddles(float2* tws, const float2* __restr
 // LDS holds N rows of pitch P = N + N1 float2. Inside a row, the row-stage exchange
 // stores element (n1, k2) at N1 k2 + (n1 ^ (k2 mod N1)) so that both the writes and
 // the reads of that exchange touch distinct banks within each 16-lane group.
-template <int N, int T>
+// SEP: separate twiddles (a table of 2 N entries, forward then inverse)
+template <int N, int T, bool SEP = false>
 struct Frame2D {
   static_assert(WAVE % Split<N>::N1 == 0 && (T % WAVE == 0 || T == N * Split<N>::N1),
                 "the N1 threads of a row must share a wavefront");
@@ -193,7 +318,7 @@ struct Frame2D {
     for (int l = 0; l < L; ++l) {
       const int s = t + T * l, y = s / N1, n1 = s % N1;
       float2* u = &v[l * N2];
-      Dft<N2, false>::run(u);
+      first_dft<N2, false, SEP>(u);
 #pragma unroll
       for (int k2 = 0; k2 < N2; ++k2) lds[y * P + sw(n1, k2)] = u[k2];
     }
@@ -208,7 +333,7 @@ struct Frame2D {
         float2* u = &v[l * N2 + jj * N1];
 #pragma unroll
         for (int n1 = 0; n1 < N1; ++n1) u[n1] = lds[y * P + sw(n1, k2)];
-        TwiddledDft<N1, N, false>(tw, k2).run(u);
+        TwiddledDft<N1, N, false, SEP>(tw, k2).run(u);
       }
     }
     wave_fence();
@@ -228,7 +353,7 @@ struct Frame2D {
       float2 u[N2];
 #pragma unroll
       for (int m2 = 0; m2 < N2; ++m2) u[m2] = lds[(m1 + N1 * m2) * P + kx];
-      Dft<N2, false>::run(u);
+      first_dft<N2, false, SEP>(u);
 #pragma unroll
       for (int l2 = 0; l2 < N2; ++l2) lds[(m1 + N1 * l2) * P + kx] = u[l2];
     }
@@ -243,7 +368,7 @@ struct Frame2D {
         float2* u = &v[l * N2 + jj * N1];
 #pragma unroll
         for (int n1 = 0; n1 < N1; ++n1) u[n1] = lds[(n1 + N1 * l2) * P + kx];
-        TwiddledDft<N1, N, false>(tw, l2).run(u);
+        TwiddledDft<N1, N, false, SEP>(tw, l2).run(u);
 #pragma unroll
         for (int l1 = 0; l1 < N1; ++l1) u[l1] = cscale(u[l1], scale);
       }
@@ -257,7 +382,7 @@ struct Frame2D {
 #pragma unroll
     for (int l = 0; l < L; ++l)
 #pragma unroll
-      for (int jj = 0; jj < N2 / N1; ++jj) Dft<N1, true>::run(&v[l * N2 + jj * N1]);
+      for (int jj = 0; jj < N2 / N1; ++jj) first_dft<N1, true, SEP>(&v[l * N2 + jj * N1]);
     __syncthreads();
 #pragma unroll
     for (int l = 0; l < L; ++l) {
@@ -277,7 +402,7 @@ struct Frame2D {
       float2 u[N2];
 #pragma unroll
       for (int l2 = 0; l2 < N2; ++l2) u[l2] = lds[(m1 + N1 * l2) * P + kx];
-      TwiddledDft<N2, N, true>(tw + N / 2, m1).run(u);
+      TwiddledDft<N2, N, true, SEP>(tw + (SEP ? N : N / 2), m1).run(u);
 #pragma unroll
       for (int m2 = 0; m2 < N2; ++m2) lds[(m1 + N1 * m2) * P + kx] = u[m2];
     }
@@ -291,7 +416,7 @@ struct Frame2D {
         float2* u = &v[l * N2 + jj * N1];
 #pragma unroll
         for (int k1 = 0; k1 < N1; ++k1) u[k1] = lds[y * P + q + N1 * jj + N2 * k1];
-        Dft<N1, true>::run(u);
+        first_dft<N1, true, SEP>(u);
       }
     }
     wave_fence();
@@ -313,7 +438,7 @@ struct Frame2D {
       float2* u = &v[l * N2];
 #pragma unroll
       for (int k2 = 0; k2 < N2; ++k2) u[k2] = lds[y * P + sw(n1, k2)];
-      TwiddledDft<N2, N, true>(tw + N / 2, n1).run(u);
+      TwiddledDft<N2, N, true, SEP>(tw + (SEP ? N : N / 2), n1).run(u);
 #pragma unroll
       for (int n2 = 0; n2 < N2; ++n2) u[n2] = cscale(u[n2], scale);
     }
@@ -363,7 +488,7 @@ struct LineTile {
         float2 u[N2];
 #pragma unroll
         for (int n2 = 0; n2 < N2; ++n2) u[n2] = base[(q + N1 * n2) * ES];
-        Dft<N2, false>::run(u);
+        first_dft<N2, false, true>(u);
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) base[sw(q, k2) * ES] = u[k2];
       }
@@ -378,7 +503,7 @@ struct LineTile {
           float2* u = &w[r][jj * N1];
 #pragma unroll
           for (int n1 = 0; n1 < N1; ++n1) u[n1] = base[sw(n1, k2) * ES];
-          TwiddledDft<N1, N, false>(tw, k2).run(u);
+          TwiddledDft<N1, N, false, true>(tw, k2).run(u);
         }
       }
       __syncthreads();
@@ -400,7 +525,7 @@ struct LineTile {
           float2* u = &w[r][jj * N1];
 #pragma unroll
           for (int k1 = 0; k1 < N1; ++k1) u[k1] = base[(q + N1 * jj + N2 * k1) * ES];
-          Dft<N1, true>::run(u);
+          first_dft<N1, true, true>(u);
         }
       }
       __syncthreads();
@@ -421,7 +546,7 @@ struct LineTile {
         float2 u[N2];
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) u[k2] = base[sw(q, k2) * ES];
-        TwiddledDft<N2, N, true>(tw + N / 2, q).run(u);
+        TwiddledDft<N2, N, true, true>(tw + N, q).run(u);
 #pragma unroll
         for (int n2 = 0; n2 < N2; ++n2) base[(q + N1 * n2) * ES] = u[n2];
       }
@@ -530,7 +655,8 @@ struct WaveLines {
 // Transforms are unnormalised (tws: load_twiddles' table). Cells are addressed by byte
 // offsets: a row and a column pitch of 2^a + 2^b bytes make the XOR of the swizzle an XOR
 // of offsets, one instruction per cell and none for its position.
-template <int N, int T>
+// SEP: separate twiddles (load_separate_twiddles).
+template <int N, int T, bool SEP = false>
 struct FrameLds {
   static constexpr int N1 = Split<N>::N1;
   static constexpr int N2 = Split<N>::N2;
@@ -574,7 +700,7 @@ struct FrameLds {
   // inputs of k2 = q + N1 jj transformed to X[k2 + N2 k1] at jj N1 + k1 on return.
   template <bool INV, bool COLS>
   __device__ __forceinline__ static void line(const Line<COLS>& L, float2* lds, const float2* tws, float2 (&u)[N2]) {
-    Dft<N2, INV>::run(u);
+    first_dft<N2, INV, SEP>(u);
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) at(lds, L.mid1(k2)) = u[k2];
     wave_fence();
@@ -582,7 +708,7 @@ struct FrameLds {
     for (int jj = 0; jj < N2 / N1; ++jj) {
 #pragma unroll
       for (int n1 = 0; n1 < N1; ++n1) u[jj * N1 + n1] = at(lds, L.mid2(n1, jj));
-      TwiddledDft<N1, N, INV>(tws, L.q + N1 * jj).run(&u[jj * N1]);
+      TwiddledDft<N1, N, INV, SEP>(tws, L.q + N1 * jj).run(&u[jj * N1]);
     }
   }
   // every line of the frame transformed in place, its stage-1 input in u (`from`) or read

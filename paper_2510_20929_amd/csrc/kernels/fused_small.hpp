@@ -35,18 +35,19 @@ __global__ __launch_bounds__(T) void fused_small_near_kernel(CallArgs a) {
 // transforms anyway: one more transform (of psi_s) per slice and mode.
 template <int N, int T, int LOSS, bool LZ>
 __global__ __launch_bounds__(T) void fused_small_ms_kernel(CallArgs a) {
-  using F = Frame2D<N, T>;
+  using F = Frame2D<N, T, true>;
   using C = SmallCtx<N, T>;
   constexpr int E = C::E;
   constexpr size_t FR = size_t(E) * T;  // one frame in scratch
   __shared__ float2 lds[F::LDS_ELEMS];
-  __shared__ float2 tws[N];
+  __shared__ float2 tws[2 * N];
   __shared__ double red[2 * (T / WAVE)];
   __shared__ float wsh[MAX_EIG];
   __shared__ double wacc[MAX_EIG * (T / WAVE)];
   const int tid = threadIdx.x;
   const int S = a.S;
-  load_twiddles<N>(tws, a.tw);
+  load_separate_twiddles<N>(tws, a.tw);
+  load_separate_inverse_twiddles<N>(tws + N, a.tw);
   const float inv_n = 1.f / float(N);
   const bool fwd = a.mode != MODE_APPLY_AH;
   const bool adj = a.mode == MODE_FWD_ADJ || a.mode == MODE_APPLY_AH;

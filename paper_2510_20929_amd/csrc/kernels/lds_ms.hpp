@@ -16,7 +16,7 @@
 // window, and the last mode's far field is scaled in the registers that hold it after
 // the forward pass. The transforms are unnormalised; 1/N^2 (a power of two) is applied with
 // the transfer function and with dl/dI. Measured at 1500 positions of 2 modes and 8 slices:
-// 5.55 ms, 8.03 ms with every mode reading and writing every slice's gradient and 8-byte
+// 5.8 ms, 8.03 ms with every mode reading and writing every slice's gradient and 8-byte
 // accesses.
 // FA: a forward + adjoint call (a.mode). LZ: also dL/d(lambda z) of the slice spacing, from F g_psi_s and F psi_s for s > 0.
 #pragma once
@@ -75,7 +75,7 @@ __device__ __forceinline__ void lds_probe_side(const CallArgs& a, int k, int m, 
 
 template <int N, int T, int LOSS, bool LZ, bool FA>
 __device__ __forceinline__ void lds_ms_body(const CallArgs& a, LdsShared<N, T>& sh, int wg, int nwg) {
-  using F = FrameLds<N, T>;
+  using F = FrameLds<N, T, true>;
   constexpr int EL = F::EL;
   constexpr int NN = N * N;
   constexpr int P = F::P;
@@ -95,7 +95,7 @@ __device__ __forceinline__ void lds_ms_body(const CallArgs& a, LdsShared<N, T>& 
   const bool recompute = a.recompute || !fwd;
   const bool want_pos = (a.want & WANT_POS) && fa;
   const bool want_probe = (a.want & WANT_PROBE) != 0;
-  load_twiddles<N>(tws, a.tw);
+  load_separate_twiddles<N>(tws, a.tw);
   float2* scr = a.scratch + size_t(wg) * a.scratch_stride;
   constexpr int FB = int(FR * sizeof(float2));  // bytes of a frame: S patches, S patch gradients, M S waves
   const auto op_b = [&](int s) { return s * FB; };
