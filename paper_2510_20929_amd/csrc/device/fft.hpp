@@ -3,8 +3,8 @@
 // A length-N transform is split as N = N1 * N2 (N1 <= N2): with input index
 // n = n1 + N1 n2 and output index k = k2 + N2 k1,
 //   X[k2 + N2 k1] = sum_n1 W_N^{n1 k2} W_N1^{n1 k1} sum_n2 x[n1 + N1 n2] W_N2^{n2 k2},
-// i.e. N1 register DFTs of size N2, then N2 register DFTs of size N1 whose butterflies
-// carry the twiddles W_N^{n1 k2}. The two register stages exchange data through LDS. A 2D
+// i.e. N1 register DFTs of size N2, a twiddle W_N^{n1 k2}, then N2 register DFTs of size
+// N1. The two register stages exchange data through LDS. A 2D
 // N x N transform runs that over the rows and then over the columns (4 register stages, 3 LDS
 // exchanges). The inverse runs the adjoint stages in reverse order, so a forward
 // transform leaves each thread holding exactly the frequencies its inverse needs,
@@ -18,64 +18,14 @@
 namespace ptyhip {
 
 // ----------------------------------------------------------------------------- register DFTs
-// Radix-2 decimation in time, unrolled, in natural order. A butterfly a +- w b with
-// w = wr (1 + i tau) costs six fused operations (Linzer and Feig's form): u = (1 + i tau) b,
-// a + wr u and a - wr u. Each result is rounded twice, where a product, a sum and a
-// difference round three times; tau is large only where wr u is not (|w| = 1). (a - w b
-// as 2 a - (a + w b) carries the sum's rounding: 4 modes 3.7e-7 from 64-bit results, 3.3e-7
-// this way.) w = 1 and -i cost four additions.
-template <bool INV>
-__device__ __forceinline__ void butterfly(float2 a, float2 b, float wr, float tau, float2& s, float2& d) {
-  // INV: w's conjugate
-  const float t = INV ? -tau : tau;
-  const float2 u = make_float2(fmaf(-t, b.y, b.x), fmaf(t, b.x, b.y));
-  s = make_float2(fmaf(wr, u.x, a.x), fmaf(wr, u.y, a.y));
-  d = make_float2(fmaf(-wr, u.x, a.x), fmaf(-wr, u.y, a.y));
-}
+// Radix-4 butterflies of plain sums with one constant twiddle between them: a value meets few
+// rounded constants on its way. (Radix-2 butterflies of six fused operations with the second
+// stage's twiddles inside them carried log2 R rounded factors per value: relative error of a 2D
+// transform of 128^2 1.39e-7 instead of 1.27e-7, and its gain error, which adds up over the
+// transforms of a position, -6.2e-8 instead of -4.2e-8; 256^2 1.57e-7 and -8.1e-8 instead of
+// 1.40e-7 and -5.3e-8. 6732 positions of 30 modes took 24.8 ms with them instead of 25.8, 331 forward
+// positions of 256^2 504 us instead of 477.)
 
-// a +- w b for any w (eight operations): w at or beyond -i has no bounded tau
-template <bool INV>
-__device__ __forceinline__ void butterfly_any(float2 a, float2 b, float2 w, float2& s, float2& d) {
-  const float wi = INV ? -w.y : w.y;
-  s = make_float2(fmaf(b.x, w.x, fmaf(-b.y, wi, a.x)), fmaf(b.y, w.x, fmaf(b.x, wi, a.y)));
-  d = make_float2(fmaf(-b.x, w.x, fmaf(b.y, wi, a.x)), fmaf(-b.y, w.x, fmaf(-b.x, wi, a.y)));
-}
-
-// DFT of size R of v (exp(-2 pi i k n / R), or its conjugate)
-template <int R, bool INV>
-struct Dft {
-  __device__ __forceinline__ static void run(float2* v) {
-    if constexpr (R > 1) {
-      constexpr int H = R / 2;
-      float2 e[H], o[H];
-#pragma unroll
-      for (int i = 0; i < H; ++i) {
-        e[i] = v[2 * i];
-        o[i] = v[2 * i + 1];
-      }
-      Dft<H, INV>::run(e);
-      Dft<H, INV>::run(o);
-      static_for<0, H>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        if constexpr (k == 0) {
-          v[0] = cadd(e[0], o[0]);
-          v[H] = csub(e[0], o[0]);
-        } else if constexpr (4 * k == R) {
-          const float2 t = mul_mi<INV>(o[k]);
-          v[k] = cadd(e[k], t);
-          v[k + H] = csub(e[k], t);
-        } else {
-          using W = Twiddle<R, k, INV>;
-          butterfly<false>(e[k], o[k], W::re, W::im / W::re, v[k], v[k + H]);
-        }
-      });
-    }
-  }
-};
-
-// The same with radix-4 butterflies of plain sums and one constant twiddle between them: a value
-// meets fewer rounded constants on its way, so that chained transforms gain and lose less
-// (TwiddledDft with SEP).
 // multiply by the constant twiddle W_R^J, with the trivial angles special-cased
 template <int R, int J, bool INV>
 __device__ __forceinline__ float2 twiddle_const(float2 a) {
@@ -94,15 +44,15 @@ __device__ __forceinline__ float2 twiddle_const(float2 a) {
 }
 
 template <int R, bool INV>
-struct Dft4;
+struct Dft;
 
 template <bool INV>
-struct Dft4<1, INV> {
+struct Dft<1, INV> {
   __device__ __forceinline__ static void run(float2*) {}
 };
 
 template <bool INV>
-struct Dft4<2, INV> {
+struct Dft<2, INV> {
   __device__ __forceinline__ static void run(float2* v) {
     float2 a = v[0], b = v[1];
     v[0] = cadd(a, b);
@@ -111,7 +61,7 @@ struct Dft4<2, INV> {
 };
 
 template <bool INV>
-struct Dft4<4, INV> {
+struct Dft<4, INV> {
   __device__ __forceinline__ static void run(float2* v) {
     float2 s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
     float2 s13 = cadd(v[1], v[3]), d13 = mul_mi<INV>(csub(v[1], v[3]));
@@ -124,7 +74,7 @@ struct Dft4<4, INV> {
 
 // Cooley-Tukey split R = A * B with constant twiddles (register renaming only).
 template <int A, int B, bool INV>
-__device__ __forceinline__ void dft4_split(float2* v) {
+__device__ __forceinline__ void dft_split(float2* v) {
   constexpr int R = A * B;
   float2 t[R];
   static_for<0, A>([&](auto n1c) {
@@ -132,7 +82,7 @@ __device__ __forceinline__ void dft4_split(float2* v) {
     float2 u[B];
 #pragma unroll
     for (int n2 = 0; n2 < B; ++n2) u[n2] = v[n1 + A * n2];
-    Dft4<B, INV>::run(u);
+    Dft<B, INV>::run(u);
     static_for<0, B>([&](auto k2c) {
       constexpr int k2 = decltype(k2c)::value;
       t[n1 * B + k2] = twiddle_const<R, n1 * k2, INV>(u[k2]);
@@ -143,91 +93,40 @@ __device__ __forceinline__ void dft4_split(float2* v) {
     float2 u[A];
 #pragma unroll
     for (int n1 = 0; n1 < A; ++n1) u[n1] = t[n1 * B + k2];
-    Dft4<A, INV>::run(u);
+    Dft<A, INV>::run(u);
 #pragma unroll
     for (int k1 = 0; k1 < A; ++k1) v[k2 + B * k1] = u[k1];
   }
 }
 
 template <bool INV>
-struct Dft4<8, INV> {
-  __device__ __forceinline__ static void run(float2* v) { dft4_split<2, 4, INV>(v); }
+struct Dft<8, INV> {
+  __device__ __forceinline__ static void run(float2* v) { dft_split<2, 4, INV>(v); }
 };
 template <bool INV>
-struct Dft4<16, INV> {
-  __device__ __forceinline__ static void run(float2* v) { dft4_split<4, 4, INV>(v); }
+struct Dft<16, INV> {
+  __device__ __forceinline__ static void run(float2* v) { dft_split<4, 4, INV>(v); }
 };
 template <bool INV>
-struct Dft4<32, INV> {
-  __device__ __forceinline__ static void run(float2* v) { dft4_split<4, 8, INV>(v); }
+struct Dft<32, INV> {
+  __device__ __forceinline__ static void run(float2* v) { dft_split<4, 8, INV>(v); }
 };
 
 // DFT of size R of v[n] w^n with w = W_N^p (p < N / R), the second factor of a transform of
-// size N: the twiddles go into the butterflies, whose factors at size L are w^(R / L) W_L^k,
-// k < L / 4 (the other quarter has -i times the same). That is R / 2 table entries and no
-// multiplication of its own instead of R - 1 of each (128^2, 6732 positions x 30 modes:
-// 25.75 -> 24.9 ms together with the fused radix-2 butterflies; 300 near-field positions: 464 ->
-// 440 us). Table (load_twiddles): factor j of
-// every p consecutive, so that a lane's entries are at constant distances.
-template <int R, int N, bool INV, bool SEP = false>
-struct TwiddledDft {
-  static constexpr int PITCH = N / R;
-  float2 c[R / 2];  // size 2: c[0], w^(R / 2); size L: c[L / 4 + k], (wr, tau)
-  __device__ __forceinline__ TwiddledDft(const float2* tab, int p) {
-#pragma unroll
-    for (int j = 0; j < R / 2; ++j) c[j] = tab[j * PITCH + p];
-  }
-  // W_N's exponent of factor j
-  __device__ __forceinline__ static int exponent(int j, int p) {
-    if (j == 0) return (R / 2) * p;
-    const int lg = 31 - __builtin_clz(j);  // j = L / 4 + k
-    return ((R / 4) >> lg) * p + (j - (1 << lg)) * ((N / 4) >> lg);
-  }
-  template <int L = R>
-  __device__ __forceinline__ void run(float2* v) const {
-    if constexpr (L == 2) {
-      butterfly_any<INV>(v[0], v[1], c[0], v[0], v[1]);
-    } else {
-      constexpr int H = L / 2, Q = L / 4;
-      float2 e[H], o[H];
-#pragma unroll
-      for (int i = 0; i < H; ++i) {
-        e[i] = v[2 * i];
-        o[i] = v[2 * i + 1];
-      }
-      run<H>(e);
-      run<H>(o);
-#pragma unroll
-      for (int k = 0; k < Q; ++k) {
-        butterfly<INV>(e[k], o[k], c[Q + k].x, c[Q + k].y, v[k], v[k + H]);
-        butterfly<INV>(e[k + Q], mul_mi<INV>(o[k + Q]), c[Q + k].x, c[Q + k].y, v[k + Q], v[k + Q + H]);
-      }
-    }
-  }
-};
-
-// The same with every element multiplied by its own entry w^n, n < R (an element is then
-// multiplied by one rounded twiddle, not by a product of log2 R of them): the transforms of
-// models that chain many (multislice), whose gain errors add up (8 slices: 2.0e-6 from 64-bit
-// results and 6.2 ms; 3.2e-6 and 5.9 ms with the twiddles in the butterflies), and of the
-// per-step form.
+// size N: every element is multiplied by its own table entry w^n, one rounded twiddle.
+// Table (load_twiddles): entry n of every p consecutive, so that the entries of a lane are at
+// constant distances.
 template <int R, int N, bool INV>
-struct TwiddledDft<R, N, INV, true> {
+struct TwiddledDft {
   static constexpr int PITCH = N / R;
   const float2* c;
   __device__ __forceinline__ TwiddledDft(const float2* tab, int p) : c(tab + p) {}
   __device__ __forceinline__ void run(float2* v) const {
 #pragma unroll
     for (int n = 1; n < R; ++n) v[n] = INV ? cmul_conjb(v[n], c[n * PITCH]) : cmul(v[n], c[n * PITCH]);
-    Dft4<R, INV>::run(v);
+    Dft<R, INV>::run(v);
   }
 };
-// first stage of a split transform
-template <int R, bool INV, bool SEP>
-__device__ __forceinline__ void first_dft(float2* v) {
-  if constexpr (SEP) Dft4<R, INV>::run(v);
-  else Dft<R, INV>::run(v);
-}
 
 // ----------------------------------------------------------------------------- factorisations
 template <int N>
@@ -239,31 +138,18 @@ template <> struct Split<128> { static constexpr int N1 = 8,  N2 = 16; };
 template <> struct Split<256> { static constexpr int N1 = 16, N2 = 16; };
 template <> struct Split<512> { static constexpr int N1 = 16, N2 = 32; };
 
-// The LDS table of a transform of N points, N entries from tw (W_N^j): the factors of its
-// forward second stage (size N1), then from N / 2 those of its inverse (size N2). Beyond size
-// 2 their angles lie in (-pi / 2, 0], so wr > 0.
+// The LDS tables of a transform of N points, N entries each from tw (W_N^j): W_N^{n p} at
+// n N2 + p for a second stage of size N1, and at n N1 + p for one of size N2 (the inverse of Frame2D
+// and LineTile).
 template <int N>
 __device__ __forceinline__ void load_twiddles(float2* tws, const float2* __restrict__ tw) {
-  constexpr int N1 = Split<N>::N1, N2 = Split<N>::N2;
-  for (int i = threadIdx.x; i < N; i += blockDim.x) {
-    const int h = i % (N / 2);
-    const int j = i < N / 2 ? h / N2 : h / N1;
-    const float2 w = tw[i < N / 2 ? TwiddledDft<N1, N, false>::exponent(j, h % N2)
-                                  : TwiddledDft<N2, N, true>::exponent(j, h % N1)];
-    tws[i] = j == 0 ? w : make_float2(w.x, w.y / w.x);
-  }
-}
-// The separate twiddles (TwiddledDft with SEP): W_N^{n p} at n N2 + p of the forward second
-// stage, and at n N1 + p of the inverse one.
-template <int N>
-__device__ __forceinline__ void load_separate_twiddles(float2* fwd, const float2* __restrict__ tw) {
   constexpr int N2 = Split<N>::N2;
-  for (int i = threadIdx.x; i < N; i += blockDim.x) fwd[i] = tw[(i / N2) * (i % N2)];
+  for (int i = threadIdx.x; i < N; i += blockDim.x) tws[i] = tw[(i / N2) * (i % N2)];
 }
 template <int N>
-__device__ __forceinline__ void load_separate_inverse_twiddles(float2* inv, const float2* __restrict__ tw) {
+__device__ __forceinline__ void load_inverse_twiddles(float2* tws, const float2* __restrict__ tw) {
   constexpr int N1 = Split<N>::N1;
-  for (int i = threadIdx.x; i < N; i += blockDim.x) inv[i] = tw[(i / N1) * (i % N1)];
+  for (int i = threadIdx.x; i < N; i += blockDim.x) tws[i] = tw[(i / N1) * (i % N1)];
 }
 
 // ----------------------------------------------------------------------------- on-chip 2D frame
@@ -277,8 +163,8 @@ __device__ __forceinline__ void load_separate_inverse_twiddles(float2* inv, cons
 // LDS holds N rows of pitch P = N + N1 float2. Inside a row, the row-stage exchange
 // stores element (n1, k2) at N1 k2 + (n1 ^ (k2 mod N1)) so that both the writes and
 // the reads of that exchange touch distinct banks within each 16-lane group.
-// SEP: separate twiddles (a table of 2 N entries, forward then inverse)
-template <int N, int T, bool SEP = false>
+// `tw`: 2 N entries, load_twiddles' table and from N load_inverse_twiddles'.
+template <int N, int T>
 struct Frame2D {
   static_assert(WAVE % Split<N>::N1 == 0 && (T % WAVE == 0 || T == N * Split<N>::N1),
                 "the N1 threads of a row must share a wavefront");
@@ -318,7 +204,7 @@ struct Frame2D {
     for (int l = 0; l < L; ++l) {
       const int s = t + T * l, y = s / N1, n1 = s % N1;
       float2* u = &v[l * N2];
-      first_dft<N2, false, SEP>(u);
+      Dft<N2, false>::run(u);
 #pragma unroll
       for (int k2 = 0; k2 < N2; ++k2) lds[y * P + sw(n1, k2)] = u[k2];
     }
@@ -333,7 +219,7 @@ struct Frame2D {
         float2* u = &v[l * N2 + jj * N1];
 #pragma unroll
         for (int n1 = 0; n1 < N1; ++n1) u[n1] = lds[y * P + sw(n1, k2)];
-        TwiddledDft<N1, N, false, SEP>(tw, k2).run(u);
+        TwiddledDft<N1, N, false>(tw, k2).run(u);
       }
     }
     wave_fence();
@@ -353,7 +239,7 @@ struct Frame2D {
       float2 u[N2];
 #pragma unroll
       for (int m2 = 0; m2 < N2; ++m2) u[m2] = lds[(m1 + N1 * m2) * P + kx];
-      first_dft<N2, false, SEP>(u);
+      Dft<N2, false>::run(u);
 #pragma unroll
       for (int l2 = 0; l2 < N2; ++l2) lds[(m1 + N1 * l2) * P + kx] = u[l2];
     }
@@ -368,7 +254,7 @@ struct Frame2D {
         float2* u = &v[l * N2 + jj * N1];
 #pragma unroll
         for (int n1 = 0; n1 < N1; ++n1) u[n1] = lds[(n1 + N1 * l2) * P + kx];
-        TwiddledDft<N1, N, false, SEP>(tw, l2).run(u);
+        TwiddledDft<N1, N, false>(tw, l2).run(u);
 #pragma unroll
         for (int l1 = 0; l1 < N1; ++l1) u[l1] = cscale(u[l1], scale);
       }
@@ -382,7 +268,7 @@ struct Frame2D {
 #pragma unroll
     for (int l = 0; l < L; ++l)
 #pragma unroll
-      for (int jj = 0; jj < N2 / N1; ++jj) first_dft<N1, true, SEP>(&v[l * N2 + jj * N1]);
+      for (int jj = 0; jj < N2 / N1; ++jj) Dft<N1, true>::run(&v[l * N2 + jj * N1]);
     __syncthreads();
 #pragma unroll
     for (int l = 0; l < L; ++l) {
@@ -402,7 +288,7 @@ struct Frame2D {
       float2 u[N2];
 #pragma unroll
       for (int l2 = 0; l2 < N2; ++l2) u[l2] = lds[(m1 + N1 * l2) * P + kx];
-      TwiddledDft<N2, N, true, SEP>(tw + (SEP ? N : N / 2), m1).run(u);
+      TwiddledDft<N2, N, true>(tw + N, m1).run(u);
 #pragma unroll
       for (int m2 = 0; m2 < N2; ++m2) lds[(m1 + N1 * m2) * P + kx] = u[m2];
     }
@@ -416,7 +302,7 @@ struct Frame2D {
         float2* u = &v[l * N2 + jj * N1];
 #pragma unroll
         for (int k1 = 0; k1 < N1; ++k1) u[k1] = lds[y * P + q + N1 * jj + N2 * k1];
-        first_dft<N1, true, SEP>(u);
+        Dft<N1, true>::run(u);
       }
     }
     wave_fence();
@@ -438,7 +324,7 @@ struct Frame2D {
       float2* u = &v[l * N2];
 #pragma unroll
       for (int k2 = 0; k2 < N2; ++k2) u[k2] = lds[y * P + sw(n1, k2)];
-      TwiddledDft<N2, N, true, SEP>(tw + (SEP ? N : N / 2), n1).run(u);
+      TwiddledDft<N2, N, true>(tw + N, n1).run(u);
 #pragma unroll
       for (int n2 = 0; n2 < N2; ++n2) u[n2] = cscale(u[n2], scale);
     }
@@ -488,7 +374,7 @@ struct LineTile {
         float2 u[N2];
 #pragma unroll
         for (int n2 = 0; n2 < N2; ++n2) u[n2] = base[(q + N1 * n2) * ES];
-        first_dft<N2, false, true>(u);
+        Dft<N2, false>::run(u);
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) base[sw(q, k2) * ES] = u[k2];
       }
@@ -503,7 +389,7 @@ struct LineTile {
           float2* u = &w[r][jj * N1];
 #pragma unroll
           for (int n1 = 0; n1 < N1; ++n1) u[n1] = base[sw(n1, k2) * ES];
-          TwiddledDft<N1, N, false, true>(tw, k2).run(u);
+          TwiddledDft<N1, N, false>(tw, k2).run(u);
         }
       }
       __syncthreads();
@@ -525,7 +411,7 @@ struct LineTile {
           float2* u = &w[r][jj * N1];
 #pragma unroll
           for (int k1 = 0; k1 < N1; ++k1) u[k1] = base[(q + N1 * jj + N2 * k1) * ES];
-          first_dft<N1, true, true>(u);
+          Dft<N1, true>::run(u);
         }
       }
       __syncthreads();
@@ -546,7 +432,7 @@ struct LineTile {
         float2 u[N2];
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) u[k2] = base[sw(q, k2) * ES];
-        TwiddledDft<N2, N, true, true>(tw + N, q).run(u);
+        TwiddledDft<N2, N, true>(tw + N, q).run(u);
 #pragma unroll
         for (int n2 = 0; n2 < N2; ++n2) base[(q + N1 * n2) * ES] = u[n2];
       }
@@ -568,19 +454,11 @@ template <int N>
 struct WaveLines {
   static constexpr int N1 = 16, N2 = N / 16;
   static_assert(N2 == 16 || N2 == 32, "256- and 512-point lines");
-  // Where the twiddles W_N^{n1 k2} are applied. Inside the butterflies of the second stage
-  // (8 or 16 factors of a lane live through it) at 512 threads; one by one at the exchange
-  // where a thread has 128 registers and 32 pixels (256^2: the eight factors make the loss of
-  // the forward kernel spill, 533 against 509 us over 331 positions x 3 modes).
-  static constexpr bool STAGE1 = N == 256;
-
-  // table in LDS: W_N^{n1 k2} at k2 16 + n1, or load_twiddles' table
+  // table in LDS: W_N^{n1 k2} at k2 16 + n1. The twiddles are applied one by one at the
+  // exchange, four at a time (a thread of a 256^2 frame has 128 registers and 32 pixels: eight or
+  // more factors live through a stage make the loss of the forward kernel spill).
   __device__ __forceinline__ static void table(float2* tws, const float2* __restrict__ tw) {
-    if constexpr (STAGE1) {
-      for (int i = threadIdx.x; i < N; i += blockDim.x) tws[i] = tw[(i & 15) * (i >> 4)];
-    } else {
-      load_twiddles<N>(tws, tw);
-    }
+    for (int i = threadIdx.x; i < N; i += blockDim.x) tws[i] = tw[(i & 15) * (i >> 4)];
   }
   __device__ __forceinline__ static int cell0(int line, int i) {  // XORed with (k2, n1 ^ k2) parts
     return line * N + 16 * (line & 1) + (i ^ ((line >> 1) << 3));
@@ -595,9 +473,9 @@ struct WaveLines {
     wave_fence();
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) {
-      if (STAGE1 && k2 > 0) u[k2] = cmul(u[k2], tw[k2 * 16 + n1]);
+      if (k2 > 0) u[k2] = cmul(u[k2], tw[k2 * 16 + n1]);
       ex[c1 ^ (16 * k2 + (k2 & 15))] = u[k2];
-      if (STAGE1 && k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
     wave_fence();
 #pragma unroll
@@ -606,8 +484,7 @@ struct WaveLines {
       float2 w[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i) w[i] = ex[c2 ^ i];
-      if constexpr (STAGE1) Dft<16, false>::run(w);
-      else TwiddledDft<16, N, false>(tw, kq + 16 * jj).run(w);
+      Dft<16, false>::run(w);
 #pragma unroll
       for (int k1 = 0; k1 < 16; ++k1) v[jj + (N2 / 16) * k1] = w[k1];
     }
@@ -631,12 +508,11 @@ struct WaveLines {
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) {
       u[k2] = ex[c1 ^ (16 * k2 + (k2 & 15))];
-      if (STAGE1 && k2 > 0) u[k2] = cmul_conjb(u[k2], tw[k2 * 16 + n1]);
-      if (STAGE1 && k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      if (k2 > 0) u[k2] = cmul_conjb(u[k2], tw[k2 * 16 + n1]);
+      if (k2 % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
     wave_fence();
-    if constexpr (STAGE1) Dft<N2, true>::run(u);
-    else TwiddledDft<N2, N, true>(tw + N / 2, n1).run(u);
+    Dft<N2, true>::run(u);
   }
 };
 
@@ -655,8 +531,7 @@ struct WaveLines {
 // Transforms are unnormalised (tws: load_twiddles' table). Cells are addressed by byte
 // offsets: a row and a column pitch of 2^a + 2^b bytes make the XOR of the swizzle an XOR
 // of offsets, one instruction per cell and none for its position.
-// SEP: separate twiddles (load_separate_twiddles).
-template <int N, int T, bool SEP = false>
+template <int N, int T>
 struct FrameLds {
   static constexpr int N1 = Split<N>::N1;
   static constexpr int N2 = Split<N>::N2;
@@ -700,7 +575,7 @@ struct FrameLds {
   // inputs of k2 = q + N1 jj transformed to X[k2 + N2 k1] at jj N1 + k1 on return.
   template <bool INV, bool COLS>
   __device__ __forceinline__ static void line(const Line<COLS>& L, float2* lds, const float2* tws, float2 (&u)[N2]) {
-    first_dft<N2, INV, SEP>(u);
+    Dft<N2, INV>::run(u);
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) at(lds, L.mid1(k2)) = u[k2];
     wave_fence();
@@ -708,7 +583,7 @@ struct FrameLds {
     for (int jj = 0; jj < N2 / N1; ++jj) {
 #pragma unroll
       for (int n1 = 0; n1 < N1; ++n1) u[jj * N1 + n1] = at(lds, L.mid2(n1, jj));
-      TwiddledDft<N1, N, INV, SEP>(tws, L.q + N1 * jj).run(&u[jj * N1]);
+      TwiddledDft<N1, N, INV>(tws, L.q + N1 * jj).run(&u[jj * N1]);
     }
   }
   // every line of the frame transformed in place, its stage-1 input in u (`from`) or read

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(T) void fused_small_near_kernel(CallArgs a) {
 // transforms anyway: one more transform (of psi_s) per slice and mode.
 template <int N, int T, int LOSS, bool LZ>
 __global__ __launch_bounds__(T) void fused_small_ms_kernel(CallArgs a) {
-  using F = Frame2D<N, T, true>;
+  using F = Frame2D<N, T>;
   using C = SmallCtx<N, T>;
   constexpr int E = C::E;
   constexpr size_t FR = size_t(E) * T;  // one frame in scratch
@@ -46,8 +46,8 @@ __global__ __launch_bounds__(T) void fused_small_ms_kernel(CallArgs a) {
   __shared__ double wacc[MAX_EIG * (T / WAVE)];
   const int tid = threadIdx.x;
   const int S = a.S;
-  load_separate_twiddles<N>(tws, a.tw);
-  load_separate_inverse_twiddles<N>(tws + N, a.tw);
+  load_twiddles<N>(tws, a.tw);
+  load_inverse_twiddles<N>(tws + N, a.tw);
   const float inv_n = 1.f / float(N);
   const bool fwd = a.mode != MODE_APPLY_AH;
   const bool adj = a.mode == MODE_FWD_ADJ || a.mode == MODE_APPLY_AH;

@@ -75,7 +75,7 @@ __device__ __forceinline__ void lds_probe_side(const CallArgs& a, int k, int m, 
 
 template <int N, int T, int LOSS, bool LZ, bool FA>
 __device__ __forceinline__ void lds_ms_body(const CallArgs& a, LdsShared<N, T>& sh, int wg, int nwg) {
-  using F = FrameLds<N, T, true>;
+  using F = FrameLds<N, T>;
   constexpr int EL = F::EL;
   constexpr int NN = N * N;
   constexpr int P = F::P;
@@ -95,7 +95,7 @@ __device__ __forceinline__ void lds_ms_body(const CallArgs& a, LdsShared<N, T>& 
   const bool recompute = a.recompute || !fwd;
   const bool want_pos = (a.want & WANT_POS) && fa;
   const bool want_probe = (a.want & WANT_PROBE) != 0;
-  load_separate_twiddles<N>(tws, a.tw);
+  load_twiddles<N>(tws, a.tw);
   float2* scr = a.scratch + size_t(wg) * a.scratch_stride;
   constexpr int FB = int(FR * sizeof(float2));  // bytes of a frame: S patches, S patch gradients, M S waves
   const auto op_b = [&](int s) { return s * FB; };

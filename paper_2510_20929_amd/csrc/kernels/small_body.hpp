@@ -449,7 +449,7 @@ __device__ __forceinline__ void finish_position(const CallArgs& a, int k, double
 template <int N, int T>
 struct SmallShared {
   float2 lds[Frame2D<N, T>::LDS_ELEMS + (N == WAVE ? Frame2D<N, T>::P : 0)];  // a window's rows at 64^2
-  float2 tws[N];
+  float2 tws[2 * N];
   double red[2 * (T / WAVE)];
   float wsh[MAX_EIG];
   double wacc[MAX_EIG * (T / WAVE)];  // weight-gradient sums, one slot per eigenprobe and wave
@@ -486,6 +486,7 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
   const bool adj = a.mode == MODE_FWD_ADJ || a.mode == MODE_APPLY_AH;
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   load_twiddles<N>(tws, a.tw);
+  load_inverse_twiddles<N>(tws + N, a.tw);
   // scratch (RV = false): patch [NN], patch-gradient accumulator [NN], far fields of
   //   modes 0..M-2 [M-1][NN] (unless recomputed), probe accumulator [E][M][NN]
   // scratch (RV = true): dl/dI [NN floats], far fields [M-1][NN], probe accumulator
@@ -782,6 +783,7 @@ __device__ __forceinline__ void small_body_near(const CallArgs& a, SmallShared<N
   const bool want_pos = (a.want & WANT_POS) && adj;
   const bool want_lz = (a.want & WANT_LZ) && adj && a.lz_part != nullptr;
   load_twiddles<N>(tws, a.tw);
+  load_inverse_twiddles<N>(tws + N, a.tw);
   float2* scr = a.scratch + size_t(wg) * a.scratch_stride;
   const BufFrame sb(scr, uint32_t(a.scratch_stride * sizeof(float2)));
   constexpr int GACC_B = C::NN * 8;
