@@ -560,7 +560,7 @@ __device__ __forceinline__ void big_body(const CallArgs& a, BigShared<N, TT>& sh
           // at 2500 positions of 8 eigenprobes); after the wave's last group it is left in LDS for the
           // next wave.
           float2 left = make_float2(0.f, 0.f);
-          float fy = 0.f, fx = 0.f;  // a row group's few terms per thread in FP32, then FP64
+          float fy = 0.f, fx = 0.f;  // the terms of four pixels per thread in FP32, then FP64
           const int up_lane = ((lane + 48) & 63) * 4;
           // a window column of this row: position terms of h and of the difference d along x
           // against the object, then the window value
@@ -617,6 +617,9 @@ __device__ __forceinline__ void big_body(const CallArgs& a, BigShared<N, TT>& sh
                 pos_terms(lo2(A0[j]), lo2(A1[j]), h[2 * j], d[2 * j]);
                 pos_terms(hi2(A0[j]), hi2(A1[j]), h[2 * j + 1], d[2 * j + 1]);
               }
+              gy += double(fy);
+              gx += double(fx);
+              fy = fx = 0.f;
             }
             if (want_obj) {
               float4 above[WB];

@@ -284,7 +284,9 @@ __device__ __forceinline__ void load_window(const PatchWindow& pw, const PosInfo
 // the row above stays in registers, so a window pixel costs two LDS reads and no index
 // arithmetic. h = (1 - fx) g[x] + fx g[x - 1]; the window is (1 - fy) h[y] + fy h[y - 1], and
 // the position terms are its derivatives against the object (requested only with a full
-// window). Call between block barriers.
+// window), interpolated differences of g: the difference of two interpolated rows would carry
+// their roundings (2 modes of 128^2: 3.0e-7 from 64-bit position gradients, 2.0e-7 this way).
+// Call between block barriers.
 template <int N, int T, int P>
 __device__ __forceinline__ void window_rows(const CallArgs& a, const PosInfo& p, const float2* lds,
                                             const BufFrame& win, float2* gwin, double& gy, double& gx) {
@@ -298,62 +300,63 @@ __device__ __forceinline__ void window_rows(const CallArgs& a, const PosInfo& p,
   const int y0 = wave * R;
   const float ay = 1.f - p.fy, ax = 1.f - p.fx;
   const float2 z = make_float2(0.f, 0.f);
-  float fy = 0.f, fx = 0.f;  // the thread's few terms in FP32, then FP64
-  float2 hp[J], dp[J];       // the row above: interpolated along x, difference along x
-  const auto row = [&](int y, float2 (&h)[J], float2 (&d)[J]) {
+  float fy = 0.f, fx = 0.f;  // the terms of the thread's pixels of a row in FP32, then FP64
+  // g at a pixel and at the one to its left, and h
+  struct Px {
+    float2 c, l, h;
+  };
+  const auto px = [&](float2 c, float2 l) {
+    return Px{c, l, make_float2(fmaf(p.fx, l.x, ax * c.x), fmaf(p.fx, l.y, ax * c.y))};
+  };
+  const auto row = [&](int y, Px (&q)[J]) {
     const float2* r = lds + y * P + lane;
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const float2 c = r[WAVE * j];
-      float2 l = j > 0 || lane > 0 ? r[WAVE * j - (j > 0 || lane > 0 ? 1 : 0)] : z;
-      h[j].x = fmaf(p.fx, l.x, ax * c.x);
-      h[j].y = fmaf(p.fx, l.y, ax * c.y);
-      d[j] = csub(l, c);
-    }
+    for (int j = 0; j < J; ++j)
+      q[j] = px(r[WAVE * j], j > 0 || lane > 0 ? r[WAVE * j - (j > 0 || lane > 0 ? 1 : 0)] : z);
   };
-  const auto emit = [&](float2 h, float2 d, float2 hup, float2 dup, int y, int x) {
+  // window pixel of q below u, the object there in A
+  const auto emit = [&](const Px& q, const Px& u, float2* o, auto&& object) {
     if (want_obj) {
-      const f2v_t o = {fmaf(p.fy, hup.x, ay * h.x), fmaf(p.fy, hup.y, ay * h.y)};
-      __builtin_nontemporal_store(o, reinterpret_cast<f2v_t*>(gwin + y * WN + x));
+      const f2v_t w = {fmaf(p.fy, u.h.x, ay * q.h.x), fmaf(p.fy, u.h.y, ay * q.h.y)};
+      __builtin_nontemporal_store(w, reinterpret_cast<f2v_t*>(o));
     }
     if (want_pos) {
-      const float2 A = win.ld(x * 8, y * a.W * 8);
-      fy += cdotre(csub(hup, h), A);
-      fx += cdotre(make_float2(fmaf(p.fy, dup.x, ay * d.x), fmaf(p.fy, dup.y, ay * d.y)), A);
+      const float2 A = object();
+      const float2 dc = csub(u.c, q.c), dl = csub(u.l, q.l), dq = csub(q.l, q.c), du = csub(u.l, u.c);
+      fy += cdotre(make_float2(fmaf(p.fx, dl.x, ax * dc.x), fmaf(p.fx, dl.y, ax * dc.y)), A);
+      fx += cdotre(make_float2(fmaf(p.fy, du.x, ay * dq.x), fmaf(p.fy, du.y, ay * dq.y)), A);
     }
   };
+  const auto emit_at = [&](const Px& q, const Px& u, int y, int x) {
+    emit(q, u, gwin + y * WN + x, [&] { return win.ld(x * 8, y * a.W * 8); });
+  };
+  const Px none = {z, z, z};
+  Px up[J];  // the row above
 #pragma unroll
-  for (int j = 0; j < J; ++j) hp[j] = dp[j] = z;
-  if (wave > 0) row(y0 - 1, hp, dp);
+  for (int j = 0; j < J; ++j) up[j] = none;
+  if (wave > 0) row(y0 - 1, up);
 #pragma unroll 2
   for (int r = 0; r < R; ++r) {
-    float2 h[J], d[J];
-    row(y0 + r, h, d);
+    Px q[J];
+    row(y0 + r, q);
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-      emit(h[j], d[j], hp[j], dp[j], y0 + r, lane + WAVE * j);
-      hp[j] = h[j];
-      dp[j] = d[j];
+      emit_at(q[j], up[j], y0 + r, lane + WAVE * j);
+      up[j] = q[j];
     }
+    gy += double(fy);
+    gx += double(fx);
+    fy = fx = 0.f;
   }
   if (wave == NW - 1) {  // row N
 #pragma unroll
-    for (int j = 0; j < J; ++j) emit(z, z, hp[j], dp[j], N, lane + WAVE * j);
+    for (int j = 0; j < J; ++j) emit_at(none, up[j], N, lane + WAVE * j);
   }
   // column N of the wave's rows (and of row N), one row a lane
   if (lane < R + (wave == NW - 1 ? 1 : 0)) {
     const int y = y0 + lane;
-    const float2 c = y < N ? lds[y * P + N - 1] : z, u = y > 0 ? lds[(y - 1) * P + N - 1] : z;
-    const float2 h = cscale(c, p.fx), hu = cscale(u, p.fx);
-    if (want_obj) {
-      const f2v_t o = {fmaf(p.fy, hu.x, ay * h.x), fmaf(p.fy, hu.y, ay * h.y)};
-      __builtin_nontemporal_store(o, reinterpret_cast<f2v_t*>(gwin + y * WN + N));
-    }
-    if (want_pos) {
-      const float2 A = win.ld((y * a.W + N) * 8, 0);
-      fy += cdotre(csub(hu, h), A);
-      fx += cdotre(make_float2(fmaf(p.fy, u.x, ay * c.x), fmaf(p.fy, u.y, ay * c.y)), A);
-    }
+    const float2 l = y < N ? lds[y * P + N - 1] : z, u = y > 0 ? lds[(y - 1) * P + N - 1] : z;
+    emit(px(z, l), px(z, u), gwin + y * WN + N, [&] { return win.ld((y * a.W + N) * 8, 0); });
   }
   gy += double(fy);
   gx += double(fx);
