@@ -447,7 +447,7 @@ __device__ __forceinline__ void big_body(const CallArgs& a, BigShared<N, TT>& sh
 
     // adjoint, one mode at a time. Staged probe-wave gradients leave the weight gradients to
     // the contraction of the staged frames; otherwise the terms are summed in FP32 over a
-    // thread's pixels of a row group (one eigenprobe) or batch, then in FP64.
+    // thread's pixels of a batch, then in FP64.
     const bool want_w = (a.want & WANT_WEIGHTS) && a.weights && !a.gpstage;
     float2* gwin = a.gwin ? a.gwin + size_t(it) * WN * WN : nullptr;
     const bool want_obj = (a.want & WANT_OBJ) && gwin != nullptr;
@@ -476,7 +476,6 @@ __device__ __forceinline__ void big_body(const CallArgs& a, BigShared<N, TT>& sh
         }
 #pragma unroll
         for (int i = 0; i < N2; i += 2) swap_pair(g[i], g[i + 1]);
-        float tw1 = 0.f;
 #pragma unroll
         for (int i0 = 0; i0 < N2 / 2; i0 += BP) {
           const int b0 = 2 * i0;
@@ -496,7 +495,7 @@ __device__ __forceinline__ void big_body(const CallArgs& a, BigShared<N, TT>& sh
 #pragma unroll
             for (int j = 0; j < BP; ++j) tf += cdotre(gP[2 * j], lo2(u[j])) + cdotre(gP[2 * j + 1], hi2(u[j]));
             if (a.E == 1) {
-              tw1 += tf;
+              gw += double(tf);
             } else {
               const double t = wave_sum(double(tf));
               if (lane == 0) sh.wred[e * NW + wave] += t;
@@ -548,7 +547,6 @@ __device__ __forceinline__ void big_body(const CallArgs& a, BigShared<N, TT>& sh
           }
           __builtin_amdgcn_sched_barrier(0);
         }
-        gw += double(tw1);
         if (lastj && (want_obj || want_pos)) {
           // Window rows of this group: the transpose of the bilinear gather, along x
           // (h = (1 - fx) g[x] + fx g[x - 1], x = 0..N) and then along y
