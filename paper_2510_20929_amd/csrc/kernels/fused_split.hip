@@ -326,7 +326,7 @@ __global__ __launch_bounds__(T) void split_forward_lds_kernel(CallArgs a) {
       __syncthreads();
       F::cols_to_regs(sh.lds, sh.tws, u);
 #pragma unroll
-      for (int e = 0; e < EL; ++e) cf[e] = fmaf(u[e].x, u[e].x, fmaf(u[e].y, u[e].y, cf[e]));
+      for (int e = 0; e < EL; ++e) cf[e] += cabs2(u[e]);
       if (a.far) store_pairs<EL, T>(a.far + (size_t(k) * a.M + m) * NN, u);
       __syncthreads();  // column phase done before the next exit wave
     }
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(T) void split_adjoint_lds_kernel(CallArgs a) {
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          go[i0 + u] = cmulc_add(Pm[u], gm[u], go[i0 + u]);
+          go[i0 + u] = cadd(go[i0 + u], cmulc(Pm[u], gm[u]));
           pin(go[i0 + u]);
           st.st(cmulc(o[i0 + u], gm[u]), vp + 8 * N1 * (i0 + u), 0);  // (no room without staging: dropped)
         }

@@ -166,7 +166,7 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
         __syncthreads();
         F::cols_to_regs(lds, tws, v);
 #pragma unroll
-        for (int e = 0; e < EL; ++e) cf[e] = fmaf(v[e].x, v[e].x, fmaf(v[e].y, v[e].y, cf[e]));
+        for (int e = 0; e < EL; ++e) cf[e] += cabs2(v[e]);
         if (apply_a) {
           const int t = opaque_tid();
 #pragma unroll
@@ -303,7 +303,7 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
         // object side: the running patch gradient
 #pragma unroll
         for (int i = 0; i < EL; ++i) {
-          go[i] = cmulc_add(probe_px(wc, wk, m, vp, i), c0[N1 * i], go[i]);
+          go[i] = cadd(go[i], cmulc(probe_px(wc, wk, m, vp, i), c0[N1 * i]));
           pin(go[i]);
           chunk(i);
         }
@@ -328,12 +328,12 @@ __device__ __forceinline__ void lds_body(const CallArgs& a, LdsShared<N, T>& sh,
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            go[i0 + u] = cmulc_add(Pm[u], g[u], go[i0 + u]);
+            go[i0 + u] = cadd(go[i0 + u], cmulc(Pm[u], g[u]));
             pin(go[i0 + u]);
           }
           if (want_probe) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) st.st(cmulc_add(o[i0 + u], g[u], acc[u]), vp + 8 * N1 * (i0 + u), 0);
+            for (int u = 0; u < 4; ++u) st.st(cadd(acc[u], cmulc(o[i0 + u], g[u])), vp + 8 * N1 * (i0 + u), 0);
           }
           __builtin_amdgcn_sched_barrier(0);
         }

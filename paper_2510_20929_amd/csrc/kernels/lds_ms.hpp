@@ -256,7 +256,7 @@ __device__ __forceinline__ void lds_ms_body(const CallArgs& a, LdsShared<N, T>& 
         const int t = opaque_tid();
 #pragma unroll
         for (int e = 0; e < EL; ++e) {
-          cf[e] = fmaf(X[e].x, X[e].x, fmaf(X[e].y, X[e].y, cf[e]));
+          cf[e] += cabs2(X[e]);
           if (!FA && a.mode == MODE_APPLY_A) a.psi_out[(size_t(k) * a.M + m) * NN + fpix(t, e)] = cscale(X[e], inv_n);
         }
       }

@@ -161,7 +161,7 @@ __device__ __forceinline__ void lds_near_body(const CallArgs& a, LdsShared<N, T>
       if (FA && (m < a.M - 1 || want_lz)) store_frame(z_b(m), X);
       inv_t(X, v);
 #pragma unroll
-      for (int i = 0; i < EL; ++i) cf[i] = fmaf(v[i].x, v[i].x, fmaf(v[i].y, v[i].y, cf[i]));
+      for (int i = 0; i < EL; ++i) cf[i] += cabs2(v[i]);
     }
     // loss and dl/dI (detector in natural order, the thread's own pixels)
     {
