@@ -185,13 +185,14 @@ ptyhip_status plan_init(Plan* p, const ptyhip_desc& d, int maxK, const ptyhip_tu
     if ((st = dalloc(p, &p->eig_part, size_t(p->eig_splits) * E * M * NN)) != PTYHIP_OK) return st;
   }
   p->window_bytes = size_t(p->fchunk) * S * (N + 1) * (N + 1) * sizeof(float2) * G;
-  // weight-gradient partials: one per mode group, or the splits of the staged contraction
-  // (n positions take at most 1024 / ceil(n / 32) splits, so n splits <= 32 * 1024 for a
-  // call of one chunk)
-  size_t nw = kk * G;
-  if (stage && !p->on_chip)
-    nw = std::max(nw, std::max(kk * weight_contract_splits(std::min(int(kk), p->fchunk), M, N), size_t(32) * 1024));
-  if ((st = dalloc(p, &p->w_part, nw * E)) != PTYHIP_OK) return st;
+  // weight-gradient partials: one per mode group, or (staged four-step frames) one, for which a
+  // chunk of n <= fchunk positions takes n splits(n) <= min(n L / 16 K, 32 K) partial sums, or n
+  const bool contract = stage && !p->on_chip;
+  if ((st = dalloc(p, &p->w_part, kk * E * (contract ? 1 : G))) != PTYHIP_OK) return st;
+  if (contract) {
+    const size_t n = size_t(p->fchunk), per = size_t(weight_contract_splits(1, M, N));
+    if ((st = dalloc(p, &p->w_split, std::max(n, std::min(n * per, size_t(32) * 1024)) * E)) != PTYHIP_OK) return st;
+  }
 
   // per-step path buffers, chunked to a bounded footprint
   const size_t per_pos = NN * sizeof(float2) * (size_t(S) * 2 + size_t(M) * 2 + (S > 1 ? size_t(S) * M : 0)) +
@@ -415,7 +416,7 @@ static ptyhip_status run_call(Plan* p, const CallArgs& a, bool plain, bool acc, 
         if (launch_window_gather(g, st) != hipSuccess) return PTYHIP_EHIP;
       }
       if (wsplits && launch_weight_contract(p->gpstage, a.probe, p->kvalid, n, d.n_eig, d.n_modes, N, wsplits,
-                                            a.w_part + size_t(d.n_eig) * wsplits * k0, st) != hipSuccess)
+                                            p->w_split, a.w_part + size_t(d.n_eig) * k0, st) != hipSuccess)
         return PTYHIP_EHIP;
       if (want_probe &&
           launch_eig_stage_reduce(p->gpstage, c.weights, p->kvalid, n, d.n_eig, d.n_modes, N, p->eig_splits,
@@ -454,7 +455,7 @@ static ptyhip_status run_call(Plan* p, const CallArgs& a, bool plain, bool acc, 
       if (launch_window_gather(g, st) != hipSuccess) return PTYHIP_EHIP;
     }
     if (wsplits && launch_weight_contract(p->gpstage, a.probe, p->wvalid, n, d.n_eig, d.n_modes, N, wsplits,
-                                          a.w_part + size_t(d.n_eig) * wsplits * k0, st) != hipSuccess)
+                                          p->w_split, a.w_part + size_t(d.n_eig) * k0, st) != hipSuccess)
       return PTYHIP_EHIP;
     if (c.gpstage && want_probe &&
         launch_eig_stage_reduce(p->gpstage, c.weights, p->wvalid, n, d.n_eig, d.n_modes, N, p->eig_splits,
@@ -590,8 +591,7 @@ static ptyhip_status enqueue_forward_adjoint(Plan* p, hipStream_t st, int K, uin
   f.E = d.n_eig;
   f.accumulate = acc ? 1 : 0;
   f.rep = (fused && p->groups > 1) ? p->groups : 1;
-  const int wsplits = fused ? staged_weight_splits(p, K, want_w) : 0;
-  f.wrep = wsplits ? wsplits : f.rep;
+  f.wrep = fused && staged_weight_splits(p, K, want_w) ? 1 : f.rep;
   return launch_finalize(f, st) == hipSuccess ? PTYHIP_OK : PTYHIP_EHIP;
 }
 

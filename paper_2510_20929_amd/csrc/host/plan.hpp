@@ -36,6 +36,7 @@ struct Plan {
   double* loss_part = nullptr;
   double* pos_part = nullptr;
   double* w_part = nullptr;
+  double* w_split = nullptr;  // large frames with staged gradients: a chunk's split partial weight sums
   float2* gprobe_part = nullptr;
   size_t probe_elems = 0;
   size_t obj_elems = 0;

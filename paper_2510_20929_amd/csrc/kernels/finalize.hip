@@ -28,8 +28,8 @@ __global__ __launch_bounds__(256) void finalize_elems_kernel(FinalArgs f) {
     }
   }
   const size_t tid = size_t(blockIdx.x) * blockDim.x + threadIdx.x, stride = size_t(gridDim.x) * blockDim.x;
-  // with rep > 1 every position has rep partial sums (one per mode group), added in order;
-  // likewise wrep for the weights (mode groups, or splits of the staged contraction)
+  // with rep > 1 (weights: wrep) every position has that many partial sums, one per mode group,
+  // added in order
   const int rep = f.rep > 1 ? f.rep : 1;
   if (f.g_pos && f.pos_part)
     for (size_t i = tid; i < size_t(f.K) * 2; i += stride) {
@@ -39,18 +39,12 @@ __global__ __launch_bounds__(256) void finalize_elems_kernel(FinalArgs f) {
       f.g_pos[i] = f.accumulate ? f.g_pos[i] + float(v) : float(v);
     }
   const int wrep = f.wrep > 1 ? f.wrep : 1;
-  if (f.g_w && f.w_part && wrep == 1)
+  if (f.g_w && f.w_part)
     for (size_t i = tid; i < size_t(f.K) * f.E; i += stride) {
-      const float v = float(f.w_part[i]);
-      f.g_w[i] = f.accumulate ? f.g_w[i] + v : v;
-    }
-  else if (f.g_w && f.w_part)  // a wave per output: its lanes take the partial sums in turn
-    for (size_t i = tid / WAVE; i < size_t(f.K) * f.E; i += stride / WAVE) {
       const size_t k = i / f.E, e = i % f.E;
       double v = 0.0;
-      for (int g = threadIdx.x & (WAVE - 1); g < wrep; g += WAVE) v += f.w_part[(k * wrep + g) * f.E + e];
-      v = wave_sum(v);
-      if ((threadIdx.x & (WAVE - 1)) == 0) f.g_w[i] = f.accumulate ? f.g_w[i] + float(v) : float(v);
+      for (int g = 0; g < wrep; ++g) v += f.w_part[(k * wrep + g) * f.E + e];
+      f.g_w[i] = f.accumulate ? f.g_w[i] + float(v) : float(v);
     }
   if (f.g_probe && f.gprobe_part) {
     for (size_t i = tid; i < f.probe_elems; i += stride) {
@@ -64,8 +58,7 @@ __global__ __launch_bounds__(256) void finalize_elems_kernel(FinalArgs f) {
 hipError_t launch_finalize(const FinalArgs& f, hipStream_t st) {
   size_t n = 0;
   if (f.g_pos) n = size_t(f.K) * 2;
-  const size_t nw = f.g_w ? size_t(f.K) * f.E * (f.wrep > 1 ? WAVE : 1) : 0;
-  if (nw > n) n = nw;
+  if (f.g_w && size_t(f.K) * f.E > n) n = size_t(f.K) * f.E;
   if (f.g_probe && f.probe_elems > n) n = f.probe_elems;
   if (n == 0 && !f.loss && !(f.g_lz && f.lz_part)) return hipSuccess;
   size_t blocks = (n + 255) / 256;

@@ -163,8 +163,8 @@ hipError_t launch_eig_stage_reduce(const float2* gp, const float* w, const int* 
 // a row load 16 bytes each, and which four floats meet in one product is the same for both
 // operands, so their order does not matter. The FP32 accumulators hold 8 products before
 // they are added in FP64: a sum of n equal products is off by 5.4e-8 rms for 8, 1.1e-7 for 16,
-// 4.6e-7 for 64; the four waves and (in the final reduction) the splits are
-// added in order. Bound by reading the staged frames once.
+// 4.6e-7 for 64; the four waves are added in order, and
+// weight_split_kernel adds the splits. Bound by reading the staged frames once.
 typedef float f4_t __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256) void weight_contract_kernel(const float* __restrict__ gp, const float* __restrict__ U,
@@ -221,6 +221,19 @@ __global__ __launch_bounds__(256) void weight_contract_kernel(const float* __res
   }
 }
 
+// The splits of a position added up, a wave per result whose lanes take them in turn. A launch of its
+// own after each chunk, so that the partial sums need room for one chunk only.
+__global__ __launch_bounds__(256) void weight_split_kernel(const double* __restrict__ part, int splits, int E, int n,
+                                                           double* __restrict__ out) {
+  const int i = blockIdx.x * (256 / WAVE) + threadIdx.x / WAVE;
+  if (i >= n) return;
+  const size_t k = i / E, e = i % E;
+  double v = 0.0;
+  for (int s = threadIdx.x & (WAVE - 1); s < splits; s += WAVE) v += part[(k * splits + s) * E + e];
+  v = wave_sum(v);
+  if ((threadIdx.x & (WAVE - 1)) == 0) out[i] = v;
+}
+
 // enough splits for about eight waves per CU, none below 16 K floats
 int weight_contract_splits(int n, int M, int N) {
   const size_t L = size_t(2) * M * N * N;
@@ -229,11 +242,13 @@ int weight_contract_splits(int n, int M, int N) {
 }
 
 hipError_t launch_weight_contract(const float2* gp, const float2* U, const int* valid, int n, int E, int M,
-                                  int N, int splits, double* part, hipStream_t st) {
+                                  int N, int splits, double* part, double* out, hipStream_t st) {
   const size_t L = size_t(2) * M * N * N;
   hipLaunchKernelGGL(weight_contract_kernel, dim3(unsigned((n + 31) / 32), unsigned(splits)), dim3(256), 0, st,
                      reinterpret_cast<const float*>(gp), reinterpret_cast<const float*>(U), valid, n, E, L,
                      splits, part);
+  hipLaunchKernelGGL(weight_split_kernel, dim3(unsigned((n * E + 3) / 4)), dim3(256), 0, st, (const double*)part, splits,
+                     E, n * E, out);
   return hipGetLastError();
 }
 

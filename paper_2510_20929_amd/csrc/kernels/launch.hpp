@@ -26,7 +26,7 @@ struct FinalArgs {
   double* loss;             // device scalar or nullptr
   const double* pos_part;   // [K][2] or nullptr
   float* g_pos;             // [K][2] or nullptr
-  const double* w_part;     // [K][E] or nullptr
+  const double* w_part;     // [K][wrep][E] or nullptr
   float* g_w;               // [K][E] or nullptr
   const float2* gprobe_part;  // [copies][E*M*N*N] or nullptr
   float2* g_probe;          // [E*M*N*N] or nullptr
@@ -125,11 +125,11 @@ int split_loss_chunks(int N);
 hipError_t launch_fused_big_split(const CallArgs& a, int N, int variant, int grid, double* lpart, hipStream_t st);
 hipError_t launch_eig_stage_reduce(const float2* gp, const float* w, const int* valid, int n, int E, int M, int N,
                                    int splits, float2* part, float2* g_probe, int accumulate, hipStream_t st);
-// weight gradients of a chunk from its staged probe-wave gradients: `splits` partial sums
-// per position (part [n][splits][E])
+// weight gradients [n][E] of a chunk from its staged probe-wave gradients, by way of `splits`
+// partial sums per position (part [n][splits][E])
 int weight_contract_splits(int n, int M, int N);
 hipError_t launch_weight_contract(const float2* gp, const float2* U, const int* valid, int n, int E, int M,
-                                  int N, int splits, double* part, hipStream_t st);
+                                  int N, int splits, double* part, double* out, hipStream_t st);
 hipError_t launch_probe_reduce_big(const CallArgs& a, int N, int grid, float2* g_probe, int accumulate,
                                    hipStream_t st);
 
