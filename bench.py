@@ -38,6 +38,8 @@ KERNEL_SOURCES = [
     "paper_2510_20929_amd/csrc/kernels/small_body.hpp",
     "paper_2510_20929_amd/csrc/kernels/lds_body.hpp",
     "paper_2510_20929_amd/csrc/kernels/lds_ms.hpp",
+    "paper_2510_20929_amd/csrc/kernels/lds_near.hpp",
+    "paper_2510_20929_amd/csrc/kernels/args.hpp",
     "paper_2510_20929_amd/csrc/device/fft.hpp",
     "paper_2510_20929_amd/csrc/device/model.hpp",
     "paper_2510_20929_amd/csrc/device/common.hpp",
@@ -231,6 +233,25 @@ def kernel_name(plan, prob, tune):
     if getattr(prob, "det_lambda_z", None) is not None:
         return "fused_small_near_kernel<%d, %d, %d>" % (prob.N, info["threads"], loss)
     return "fused_small_kernel<%d, %d, %d, %s, %s>" % (prob.N, info["threads"], loss, rv, goreg)
+
+
+# template arguments that kernel_name leaves out: a forward + adjoint call (true), without the
+# gradient of the slice spacing (false)
+INSTANCE_ARGS = {
+    "fused_big_kernel": "true",
+    "fused_small_lds_kernel": "true",
+    "fused_small_lds_near_kernel": "true",
+    "fused_small_lds_ms_kernel": "false, true",
+    "fused_small_ms_kernel": "false",
+}
+
+
+def kernel_instance(plan, prob, tune):
+    """kernel_name as the library's symbols and a profiler's trace spell the instance that a
+    forward + adjoint call runs (the mode-split form: its passes, as kernel_name)."""
+    name = kernel_name(plan, prob, tune)
+    extra = INSTANCE_ARGS.get(name.split("<")[0])
+    return f"{name[:-1]}, {extra}>" if extra else name
 
 
 def measured_intensities(truth, dev, torch, t, Plan):
@@ -441,7 +462,7 @@ def main():
     hbm_alg_gbs = bytes_pp * K / (k_step_ms * 1e-3) / 1e9
     khash = kernel_hash()
     headline = args.workload == "c1"
-    traffic = read_traffic(khash, kernel_name(plan, start, tune)) if headline else None
+    traffic = read_traffic(khash, kernel_instance(plan, start, tune)) if headline else None
     copy_gbs = copy_bandwidth(torch, dev)  # achievable HBM bandwidth, outside the timed region
 
     plain = None
@@ -503,7 +524,7 @@ def main():
                    "positions_per_call": B, "calls_per_step": len(calls), "graph_replay": bool(args.graphs)},
         "roofline": {"bound": "alu", "achieved": achieved_tflops, "peak": FP32_VECTOR_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved_tflops / FP32_VECTOR_PEAK_TFLOPS,
-                     "traffic": traffic, "kernel": kernel_name(plan, start, tune),
+                     "traffic": traffic, "kernel": kernel_instance(plan, start, tune),
                      "kernel_ms": k_avg_ms, "launches_per_step": launches, "kernel_ms_per_step": k_step_ms,
                      "flops_per_pattern": flops_pp},
         "hbm": {"alg_bytes_per_pattern": bytes_pp, "alg_GBs": hbm_alg_gbs, "frac_of_peak": hbm_alg_gbs / HBM_PEAK_GBS,
