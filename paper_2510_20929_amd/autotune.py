@@ -8,7 +8,8 @@ candidate once and keeps it only if its loss and gradients agree with the per-st
 form on the same inputs (forward <= 1e-5, gradients <= 1e-4 relative L2), then times
 the survivors with HIP events (median of several launches) and caches the fastest
 in a JSON file keyed by GPU architecture, a hash of the library sources and the
-problem shape: an entry timed on other kernel sources is never used.
+problem shape. An entry also holds the source hash at the time of its measurement, beside the
+choice: one that was timed on other kernel sources is never used, whatever its key says.
 """
 from __future__ import annotations
 
@@ -77,6 +78,17 @@ def save_cache(cache: Dict[str, dict], path: str = DEFAULT_CACHE) -> None:
     with open(tmp, "w") as fh:
         json.dump(cache, fh, indent=1, sort_keys=True)
     os.replace(tmp, path)
+
+
+def cached_choice(cache: Dict[str, dict], key: str) -> Optional[dict]:
+    """The choice stored under a key, if it was timed on the current sources."""
+    e = cache.get(key)
+    return e["tune"] if e and e.get("src") == source_hash() else None
+
+
+def _entry(best, results) -> dict:
+    return {"tune": best[0], "ms": best[1], "when": time.strftime("%Y-%m-%d %H:%M:%S"), "src": source_hash(),
+            "candidates": results}
 
 
 def plan_candidates(N: int, M: int, S: int, K: int = 0, split_ok: bool = True, E: int = 1,
@@ -168,9 +180,9 @@ def tune_plan(shape: dict, obj, probe, positions, I_meas, weights=None, grads=("
         store = False
     else:
         store = True
-    cache = load_cache(cache_path) if (cache_path and use_cache) else {}
-    if use_cache and key in cache:
-        return cache[key]["tune"], {"key": key, "cached": True}
+    known = cached_choice(load_cache(cache_path), key) if (cache_path and use_cache) else None
+    if known is not None:
+        return known, {"key": key, "cached": True}
 
     def make(tune):
         return Plan(shape["N"], shape["M"], shape["E"], shape["S"], shape["H"], shape["W"], shape["loss"],
@@ -203,8 +215,7 @@ def tune_plan(shape: dict, obj, probe, positions, I_meas, weights=None, grads=("
         raise RuntimeError(f"no autotuner candidate passed parity for {key}: {results}")
     if cache_path and store:
         cache = load_cache(cache_path)
-        cache[key] = {"tune": best[0], "ms": best[1], "when": time.strftime("%Y-%m-%d %H:%M:%S"),
-                      "candidates": results}
+        cache[key] = _entry(best, results)
         save_cache(cache, cache_path)
     return best[0], {"key": key, "cached": False, "candidates": results}
 
@@ -225,10 +236,9 @@ def tune_batch(problems, tensors, grads=("obj", "probe", "pos"), reps: int = 3, 
     device. Every candidate must reproduce the per-call results of each dataset. The
     choice is cached under ``batch_key``. Returns (choice, report)."""
     key = batch_key(problems, grads)
-    if cache_path and use_cache:
-        cache = load_cache(cache_path)
-        if key in cache:
-            return cache[key]["tune"], {"key": key, "cached": True}
+    known = cached_choice(load_cache(cache_path), key) if (cache_path and use_cache) else None
+    if known is not None:
+        return known, {"key": key, "cached": True}
     cus = _cus()
     ref_b = Batch(problems)
     refs = [ref_b.bind(i, *t[:4], weights=t[4]) for i, t in enumerate(tensors)]
@@ -263,7 +273,6 @@ def tune_batch(problems, tensors, grads=("obj", "probe", "pos"), reps: int = 3, 
         best = ({"per_call": True}, ms)
     if cache_path:
         cache = load_cache(cache_path)
-        cache[key] = {"tune": best[0], "ms": best[1], "when": time.strftime("%Y-%m-%d %H:%M:%S"),
-                      "candidates": results}
+        cache[key] = _entry(best, results)
         save_cache(cache, cache_path)
     return best[0], {"key": key, "cached": False, "candidates": results}
