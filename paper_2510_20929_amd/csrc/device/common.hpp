@@ -24,7 +24,6 @@ __device__ __forceinline__ float2 cmulc(float2 a, float2 b) {
 __device__ __forceinline__ float2 cmul_conjb(float2 a, float2 b) {
   return make_float2(fmaf(a.x, b.x, a.y * b.y), fmaf(a.y, b.x, -a.x * b.y));
 }
-__device__ __forceinline__ float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
 __device__ __forceinline__ float cabs2(float2 a) { return fmaf(a.x, a.x, a.y * a.y); }
 // Re(conj(a) * b)
 __device__ __forceinline__ float cdotre(float2 a, float2 b) { return fmaf(a.x, b.x, a.y * b.y); }
@@ -88,11 +87,6 @@ __device__ __forceinline__ int opaque_scalar(int x) {  // the same for a value i
   asm volatile("" : "+s"(x));
   return x;
 }
-template <typename T>
-__device__ __forceinline__ const T* opaque_ptr(const T* p) {
-  asm volatile("" : "+s"(p));
-  return p;
-}
 // Computes a value here: without it the arithmetic may be sunk past following branches to
 // its first use, which keeps all of its operands live instead.
 __device__ __forceinline__ void pin(float2& x) { asm volatile("" : "+v"(x.x), "+v"(x.y)); }
@@ -151,29 +145,6 @@ __device__ __forceinline__ void atomic_add_c(float2* p, float2 v) {
   float* f = reinterpret_cast<float*>(p);
   atomic_add_f32(f, v.x);
   atomic_add_f32(f + 1, v.y);
-}
-
-// The accelerator complex die (XCD) this wave runs on (hardware register XCC_ID).
-// Each XCD has its own L2; an atomic at workgroup scope is resolved in that L2.
-__device__ __forceinline__ int xcc_id() {
-  return int(__builtin_amdgcn_s_getreg((20) | (0 << 6) | ((4 - 1) << 11))) & 7;
-}
-
-// Float add resolved in the issuing XCD's L2. Only valid on a buffer that no other
-// XCD touches during the kernel (a per-XCD partial copy); the kernel-end release
-// writes the L2 back before the next kernel reads the copies.
-__device__ __forceinline__ void atomic_add_c_l2(float2* p, float2 v) {
-  float* f = reinterpret_cast<float*>(p);
-  __hip_atomic_fetch_add(f, v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  __hip_atomic_fetch_add(f + 1, v.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Add into the partial copy of this XCD (l2 = true) or into one shared copy with
-// device-scope atomics (l2 = false).
-__device__ __forceinline__ void scatter_add(float2* base, size_t copy_stride, bool l2, int xcc, size_t i,
-                                            float2 v) {
-  if (l2) atomic_add_c_l2(base + size_t(xcc) * copy_stride + i, v);
-  else atomic_add_c(base + i, v);
 }
 
 // Workgroups go to the 8 XCDs in turn, each with its own L2. The place of workgroup `wg` of

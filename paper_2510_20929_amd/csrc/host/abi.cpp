@@ -144,9 +144,9 @@ ptyhip_status plan_init(Plan* p, const ptyhip_desc& d, int maxK, const ptyhip_tu
     p->big_fused_ready = S == 1 && d.propagation == PTYHIP_PROP_FAR && d.subpixel == PTYHIP_SUBPIXEL_BILINEAR;
     if (!p->big_fused_ready) p->scratch_stride = 0;  // no fused kernel: no workgroup scratch
   }
-  // persistent grid: one workgroup per CU (the on-chip frame or the line blocks of the
-  // four-step transforms fill most of a CU's LDS), two for the four-step layout with
-  // half-size blocks
+  // persistent grid: one workgroup per CU (a 128^2 frame or the exchange cells of the four-step
+  // transforms' waves fill most of a CU's LDS; smaller frames leave room for two, which
+  // tune.grid asks for), two for the four-step layout with half the waves
   const int per_cu = p->on_chip ? 1 : fused_big_wg_per_cu(p->tune.variant);
   int grid = p->tune.grid > 0 ? p->tune.grid : per_cu * p->cus;
   p->grid = grid;

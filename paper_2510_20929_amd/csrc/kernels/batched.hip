@@ -21,7 +21,7 @@
 namespace ptyhip {
 
 // 128^2: the frame resident in LDS, dl/dI in registers (640 positions of 2 modes and 263 of 4:
-// 546 us, 572 with patch and frame in registers)
+// 568 us; 546 against 572 with patch and frame in registers, both on other transforms)
 template <int LOSS>
 __global__ __launch_bounds__(1024) void batched_128_kernel(const BatchEntry* __restrict__ tab, int n) {
   __shared__ LdsShared<128, 1024> sh;
@@ -53,9 +53,11 @@ size_t batched_scratch_elems(int N, int M, int E, int recompute, size_t* pacc_of
 
 // Window gathers of every dataset of a class in one launch: the class's datasets own
 // consecutive ranges of workgroups (first_tile; gather_tiles() of tile side gts each, none
-// for a dataset without an object gradient). GP: two groups of threads per tile only if every
-// dataset asks for more than one (gather_groups; a dataset of few windows loses more by them
-// than another gains: 2 + 2 + 2 + 2 datasets of 64^2 to 512^2, 492 us with one, 552 with two).
+// for a dataset without an object gradient). GP: two groups of threads per tile if every dataset
+// asks for more than one (gather_groups; 4 dense scans of 64^2, 300 positions on 110^2: the whole launch
+// 124 us with two, 156 with one; 2 of 256^2, 400 positions on 500^2: 900 and 936), otherwise one (a
+// dataset of few windows loses more by two than another gains: 2 + 2 + 2 + 2 datasets of 64^2 to
+// 512^2, 492 us with one, 552 with two).
 template <int GP>
 __global__ __launch_bounds__(256 * GP) void batch_gather_kernel(const BatchEntry* __restrict__ tab, int n) {
   int d = 0;

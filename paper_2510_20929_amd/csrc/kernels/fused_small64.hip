@@ -5,7 +5,7 @@ namespace ptyhip {
 
 // 512 threads: the state of a thread's eight pixels fits in registers (variants 0 and 2). Bound by
 // the latency of a position's chain of loads and barriers: 625 positions on 512 workgroups
-// 35.3 us, 24 positions of 2 modes 23.4 (43.9 and 28.6 with the patch in scratch, four loads
+// 36.0 us, 24 positions of 2 modes 22.9 (43.9 and 28.6 with the patch in scratch, four loads
 // per pixel, the measured intensities loaded when needed, per-pixel window indices and the
 // accumulator cleared and read by every workgroup)
 hipError_t launch_fused_small64(const CallArgs& a, int variant, int grid, hipStream_t st) {

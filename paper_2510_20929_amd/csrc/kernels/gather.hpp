@@ -3,7 +3,7 @@
 // (or, for objects too small to fill the GPU with such tiles, 16 x 16) tile of one slice and
 // walks the positions in order (staged through LDS), adding the part of every valid window
 // that covers the tile. Every object pixel is written exactly once (no atomics, fixed
-// summation order). Bound by the read of the windows (2500 of 257^2: 1.3 GB, 353 us) where
+// summation order). Bound by the read of the windows (2500 of 257^2: 1.3 GB, 343 us) where
 // tiles fill the GPU, by the latency of a tile's walk where they do not (gather_groups).
 #pragma once
 #include <climits>
@@ -132,8 +132,8 @@ __device__ __forceinline__ void gather_tile_at(const V* __restrict__ win, const 
 
 // Tile b of a launch of gather_tiles() workgroups: the tile rows go round the eight XCDs
 // (workgroup b runs on XCD b mod 8), so that the lines which a tile's unaligned rows share
-// with its neighbours' are read into one L2 (6732 positions of 128^2: 299 -> 271 us; 2500
-// of 256^2: 418 -> 390). False: no tile.
+// with its neighbours' are read into one L2 (6732 positions of 128^2, four groups of threads: 299 ->
+// 271 us; 2500 of 256^2, one group: 418 -> 390). False: no tile.
 __device__ __forceinline__ bool gather_tile_of(int b, int tiles_x, int tiles_y, int S, int& bx, int& by, int& bz) {
   const int j = b >> 3, row = j / tiles_x * 8 + (b & 7);
   bx = j % tiles_x;

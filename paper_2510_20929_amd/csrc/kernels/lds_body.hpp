@@ -24,13 +24,15 @@
 // gradient is written into the frame, from which the window pass forms the window
 // gradient and the position gradient.
 //
-// Bound by the transforms' arithmetic (VALU busy 59% at 30 modes) and the accumulator's
-// traffic. Measured at 2000 positions of 4 modes, Poisson: 0.92 ms (1.16 with scaled transforms,
-// separate probe and object passes, per-pixel window indices and 119 spilled registers); at 6732
-// positions of 30 modes 24.4 ms (28.2). Keeping the far fields of 4 modes in scratch instead of
-// recomputing them took 1.17-1.21 ms (0.97 then): 128 KB a mode more each way through the same memory. Eight
-// pixels at a time in the element passes took 1.03 ms, also 0.97 then (registers spilled), sixteen probe
-// loads at a time changed nothing.
+// Bound by the transforms' arithmetic and the accumulator's traffic (2000 positions of 4 modes: VALU
+// busy 65%, 3.5 GB at 3.3 TB/s; 6732 positions of 30 modes: 59%, 76 GB at 2.9 TB/s). Measured at 2000
+// positions of 4 modes, Poisson: 1.08 ms; at 6732 positions of 30 modes 26.1 ms (28.2 with scaled
+// transforms, separate probe and object passes, per-pixel window indices and 119 spilled registers).
+// Of that 7% keep rounding down: radix-4 transforms with separate twiddles (fft.hpp), and sums that add one
+// rounded term at a time. Keeping the far fields of 4 modes in scratch instead of recomputing
+// them took 1.17-1.21 ms where recomputing took 0.97: 128 KB a mode more each way through the same memory.
+// Eight pixels at a time in the element passes took 1.03 (registers spilled), sixteen probe loads at a
+// time changed nothing.
 #pragma once
 #include "small_body.hpp"
 

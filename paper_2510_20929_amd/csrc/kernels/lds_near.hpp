@@ -11,7 +11,7 @@
 // transforms are unnormalised, 1/N^2 goes with H. Scratch: patch [NN], patch-gradient sum
 // [NN], z of every mode [M][NN], dl/dI [NN floats], probe accumulator.
 // Bound by the ten (two modes) transforms' arithmetic and LDS passes of a position and, for
-// few positions, by the last round of workgroups. 300 positions of 2 modes: 263 us, 396 with the
+// few positions, by the last round of workgroups. 300 positions of 2 modes: 275 us, 396 with the
 // frame in the registers of 512 threads, every spatial state through scratch and one more
 // transform per position.
 // FA: a forward + adjoint call (a.mode), otherwise the forward alone.
