@@ -34,6 +34,7 @@ KERNEL_SOURCES = [
     "paper_2510_20929_amd/csrc/kernels/fused_small.hip",
     "paper_2510_20929_amd/csrc/kernels/fused_small.hpp",
     "paper_2510_20929_amd/csrc/kernels/fused_small64.hip",
+    "paper_2510_20929_amd/csrc/kernels/fused_small128.hip",
     "paper_2510_20929_amd/csrc/kernels/fused_lds.hip",
     "paper_2510_20929_amd/csrc/kernels/small_body.hpp",
     "paper_2510_20929_amd/csrc/kernels/lds_body.hpp",

@@ -20,6 +20,7 @@ SOURCES = [
     "kernels/plain.hip",
     "kernels/fused_small.hip",
     "kernels/fused_small64.hip",
+    "kernels/fused_small128.hip",
     "kernels/fused_lds.hip",
     "kernels/fused_small_fs.hip",
     "kernels/fused_split.hip",

@@ -1,5 +1,5 @@
-// Dispatch of the fused kernels of on-chip frames (N <= 128), and those of 16^2, 32^2 and
-// 128^2 frames.
+// Dispatch of the fused kernels of on-chip frames (N <= 128), and those of 16^2 and 32^2
+// frames.
 #include "fused_small.hpp"
 
 namespace ptyhip {
@@ -47,11 +47,7 @@ hipError_t launch_fused_small(const CallArgs& a, int N, int variant, int grid, h
     case 64: return launch_fused_small64(a, variant, grid, st);
     case 128:
       if (variant >= 5 || a.near) return launch_fused_lds(a, variant, grid, st);
-      if (variant == 1) return launch_small_t<128, 1024>(a, grid, st);
-      if (variant == 3) return launch_small_t<128, 1024, true>(a, grid, st);
-      if (variant == 4) return launch_small_t<128, 1024, true, false>(a, grid, st);
-      if (variant == 2) return launch_small_t<128, 512, true>(a, grid, st);
-      return launch_small_t<128, 512>(a, grid, st);
+      return launch_fused_small128(a, variant, grid, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -62,11 +58,7 @@ hipError_t launch_probe_reduce_small(const CallArgs& a, int N, int variant, int 
     case 16: return probe_reduce_t<16, 64>(a, grid, g_probe, accumulate, st);
     case 32: return probe_reduce_t<32, 128>(a, grid, g_probe, accumulate, st);
     case 64: return launch_probe_reduce64(a, fused_small_threads(64, variant), grid, g_probe, accumulate, st);
-    case 128:
-      if (variant >= 5 || a.near) return probe_reduce_t<128, 1024, true>(a, grid, g_probe, accumulate, st);
-      return fused_small_threads(128, variant) == 1024
-                 ? probe_reduce_t<128, 1024>(a, grid, g_probe, accumulate, st)
-                 : probe_reduce_t<128, 512>(a, grid, g_probe, accumulate, st);
+    case 128: return launch_probe_reduce128(a, variant, grid, g_probe, accumulate, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -1,9 +1,9 @@
 // Fused forward + adjoint kernels for frames that stay on chip (N <= 128): the
 // single-slice kernel (a thin wrapper over small_body), the multislice kernel and the probe
-// reduction, with their launchers. The 64^2 kernels are compiled by themselves
-// (fused_small64.hip): beside instantiations of other frame sizes the compiler keeps more
-// values live across their loops (66 spilled registers instead of 23 with the state in
-// registers; 625 positions 43.8 us instead of 35.3).
+// reduction, with their launchers. The 64^2 and 128^2 kernels are compiled by themselves
+// (fused_small64.hip, fused_small128.hip): beside instantiations of other frame sizes the
+// compiler keeps more values live across their loops (64^2: 66 spilled registers instead of 23
+// with the state in registers; 625 positions 43.8 us instead of 35.3).
 #pragma once
 #include "launch.hpp"
 #include "small_body.hpp"

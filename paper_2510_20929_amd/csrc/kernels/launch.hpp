@@ -107,6 +107,9 @@ size_t fused_small_scratch_elems(int N, int S, int M, int E, int recompute, size
 hipError_t launch_fused_small64(const CallArgs& a, int variant, int grid, hipStream_t st);
 hipError_t launch_probe_reduce64(const CallArgs& a, int threads, int grid, float2* g_probe, int accumulate,
                                  hipStream_t st);
+hipError_t launch_fused_small128(const CallArgs& a, int variant, int grid, hipStream_t st);
+hipError_t launch_probe_reduce128(const CallArgs& a, int variant, int grid, float2* g_probe, int accumulate,
+                                  hipStream_t st);
 hipError_t launch_fused_small(const CallArgs& a, int N, int variant, int grid, hipStream_t st);
 // LDS-resident kernels (128^2, variants 5 and 6)
 hipError_t launch_fused_lds(const CallArgs& a, int variant, int grid, hipStream_t st);
