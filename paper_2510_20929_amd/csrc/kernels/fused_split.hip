@@ -62,7 +62,6 @@ __global__ __launch_bounds__(T) void split_forward_kernel(CallArgs a) {
   constexpr int E = C::E;
   __shared__ SmallShared<N, T> sh;
   load_twiddles<N>(sh.tws, a.tw);
-  load_inverse_twiddles<N>(sh.tws + N, a.tw);
   const float inv_n = 1.f / float(N);
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   const int items = a.K * a.groups;
@@ -186,7 +185,6 @@ __global__ __launch_bounds__(T) void split_adjoint_kernel(CallArgs a) {
   constexpr int E = C::E;
   __shared__ SmallShared<N, T> sh;
   float2* lds = sh.lds;
-  load_twiddles<N>(sh.tws, a.tw);
   load_inverse_twiddles<N>(sh.tws + N, a.tw);
   const float inv_n = 1.f / float(N);
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;

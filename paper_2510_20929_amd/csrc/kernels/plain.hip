@@ -31,8 +31,8 @@ __global__ __launch_bounds__(T) void fft_frames_kernel(float2* X, int nframes, c
   constexpr int E = F::E, N2 = F::N2;
   __shared__ float2 lds[F::LDS_ELEMS];
   __shared__ float2 tws[2 * N];
-  load_twiddles<N>(tws, tw);
-  load_inverse_twiddles<N>(tws + N, tw);
+  if constexpr (INV) load_inverse_twiddles<N>(tws + N, tw);
+  else load_twiddles<N>(tws, tw);
   __syncthreads();
   for (int f = blockIdx.x; f < nframes; f += gridDim.x) {
     float2* x = X + size_t(f) * N * N;
@@ -62,8 +62,8 @@ __global__ __launch_bounds__(T) void fft_rows_kernel(float2* X, const float2* __
   constexpr int LP = N + 1;
   __shared__ float2 tile[RB * LP];
   __shared__ float2 tws[2 * N];
-  load_twiddles<N>(tws, tw);
-  load_inverse_twiddles<N>(tws + N, tw);
+  if constexpr (INV) load_inverse_twiddles<N>(tws + N, tw);
+  else load_twiddles<N>(tws, tw);
   float2* x = X + size_t(blockIdx.y) * N * N + size_t(blockIdx.x) * RB * N;
   for (int i = threadIdx.x; i < RB * N; i += T) tile[(i / N) * LP + (i % N)] = x[i];
   __syncthreads();
@@ -78,8 +78,8 @@ __global__ __launch_bounds__(T) void fft_cols_kernel(float2* X, const float2* __
   constexpr int CP = CB + 1;
   __shared__ float2 tile[N * CP];
   __shared__ float2 tws[2 * N];
-  load_twiddles<N>(tws, tw);
-  load_inverse_twiddles<N>(tws + N, tw);
+  if constexpr (INV) load_inverse_twiddles<N>(tws + N, tw);
+  else load_twiddles<N>(tws, tw);
   float2* x = X + size_t(blockIdx.y) * N * N + size_t(blockIdx.x) * CB;
   for (int i = threadIdx.x; i < N * CB; i += T) tile[(i / CB) * CP + (i % CB)] = x[size_t(i / CB) * N + (i % CB)];
   __syncthreads();

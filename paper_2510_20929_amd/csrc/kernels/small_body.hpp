@@ -489,7 +489,7 @@ __device__ __forceinline__ void small_body(const CallArgs& a, SmallShared<N, T>&
   const bool adj = a.mode == MODE_FWD_ADJ || a.mode == MODE_APPLY_AH;
   const bool want_pos = (a.want & WANT_POS) && a.mode == MODE_FWD_ADJ;
   load_twiddles<N>(tws, a.tw);
-  load_inverse_twiddles<N>(tws + N, a.tw);
+  if (FS || adj) load_inverse_twiddles<N>(tws + N, a.tw);
   // scratch (RV = false): patch [NN], patch-gradient accumulator [NN], far fields of
   //   modes 0..M-2 [M-1][NN] (unless recomputed), probe accumulator [E][M][NN]
   // scratch (RV = true): dl/dI [NN floats], far fields [M-1][NN], probe accumulator
