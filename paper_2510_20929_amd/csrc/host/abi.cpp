@@ -186,7 +186,7 @@ ptyhip_status plan_init(Plan* p, const ptyhip_desc& d, int maxK, const ptyhip_tu
   }
   p->window_bytes = size_t(p->fchunk) * S * (N + 1) * (N + 1) * sizeof(float2) * G;
   // weight-gradient partials: one per mode group, or (staged four-step frames) one, for which a
-  // chunk of n <= fchunk positions takes n splits(n) <= min(n L / 16 K, 32 K) partial sums, or n
+  // chunk of n <= fchunk positions takes n splits(n) <= min(n splits(1), 32 K) partial sums, or n
   const bool contract = stage && !p->on_chip;
   if ((st = dalloc(p, &p->w_part, kk * E * (contract ? 1 : G))) != PTYHIP_OK) return st;
   if (contract) {

@@ -183,6 +183,7 @@ __global__ __launch_bounds__(256) void weight_contract_kernel(const float* __res
   const float* pb = gp + (ob ? size_t(kb) * L : 0) + sub * 4;
   const float* pu = U + (oe ? size_t(row) * L : 0) + sub * 4;
   const f4_t z = {0.f, 0.f, 0.f, 0.f};
+  const bool two = k0 + 16 < n;  // the second row block has positions
   double da[4] = {0, 0, 0, 0}, db[4] = {0, 0, 0, 0};
   for (size_t c = c0 + wave; c < c1; c += 4) {
     f4_t A[4], Bm[4], Uv[4];
@@ -198,12 +199,12 @@ __global__ __launch_bounds__(256) void weight_contract_kernel(const float* __res
 #pragma unroll
       for (int j = 2 * (i & 1); j < 2 * (i & 1) + 2; ++j) {
         xa = __builtin_amdgcn_mfma_f32_16x16x4f32(A[i / 2][j], Uv[i / 2][j], xa, 0, 0, 0);
-        xb = __builtin_amdgcn_mfma_f32_16x16x4f32(Bm[i / 2][j], Uv[i / 2][j], xb, 0, 0, 0);
+        if (two) xb = __builtin_amdgcn_mfma_f32_16x16x4f32(Bm[i / 2][j], Uv[i / 2][j], xb, 0, 0, 0);
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         da[u] += double(xa[u]);
-        db[u] += double(xb[u]);
+        if (two) db[u] += double(xb[u]);
       }
     }
   }
@@ -235,11 +236,15 @@ __global__ __launch_bounds__(256) void weight_split_kernel(const double* __restr
   if ((threadIdx.x & (WAVE - 1)) == 0) out[i] = v;
 }
 
-// enough splits for about eight waves per CU, none below 16 K floats
+// Enough splits for about eight waves per CU, none below 16 K floats; for few positions below
+// that, down to 4 K floats (sixteen runs a wave), until every CU has a workgroup: a wave's chain of
+// loads, products and FP64 sums is all that such a call waits for (10 positions of 256^2, 4 eigenprobes,
+// weights alone: 233 us a call with 8 splits of 64 products a sum, 259 with 8 products, 182 with 32
+// splits of those).
 int weight_contract_splits(int n, int M, int N) {
-  const size_t L = size_t(2) * M * N * N;
-  const size_t want = std::max<size_t>(1, 1024 / size_t((n + 31) / 32));
-  return int(std::max<size_t>(1, std::min<size_t>(want, L / 16384)));
+  const size_t L = size_t(2) * M * N * N, blocks = size_t((n + 31) / 32);
+  const size_t many = std::min<size_t>(1024 / blocks, L / 16384), few = std::min<size_t>(256 / blocks, L / 4096);
+  return int(std::max<size_t>(1, std::max(many, few)));
 }
 
 hipError_t launch_weight_contract(const float2* gp, const float2* U, const int* valid, int n, int E, int M,

@@ -52,3 +52,18 @@ def test_one_eigenprobe(N, variant):
     e = float(np.sqrt(np.mean((a / b - 1.0) ** 2)))
     print(f"N={N} variant={variant}: {e:.2e}", flush=True)
     assert e <= 9e-8
+
+
+@pytest.mark.parametrize("K", [1, 2, 16, 17, 32, 33, 257])
+@pytest.mark.parametrize("N,E", [(256, 2), (256, 16), (512, 3)])
+def test_few_positions(N, E, K):
+    """Edges of the contraction's two row blocks of 16 positions and of its splits, beside the
+    per-step form: every product, eight sums of one sign at most and the two results are rounded
+    to 2^-24 each, so 16 * 2^-24 = 9.5e-7 bounds the difference of any weight."""
+    torch_cuda()
+    from paper_2510_20929_amd import Plan
+    p = _constant_problem(N, E, K, 100 + K)
+    plan = Plan.for_problem(p)
+    e = float(np.max(np.abs(_weights(plan, p) / _weights(plan, p, plain=True) - 1.0)))
+    print(f"N={N} E={E} K={K}: {e:.2e}", flush=True)
+    assert e <= 16 * 2.0 ** -24
